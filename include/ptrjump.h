@@ -94,7 +94,8 @@ typedef struct pj_opts {
     int32_t validate;         /* 1: run the complete check of the output on the device */
     int32_t to_tail;          /* 1: list ranks count the distance to the tail (the paper's
                                  convention) instead of the distance from the head */
-    int32_t rounds_per_check; /* components: rounds enqueued between host convergence checks */
+    int32_t rounds_per_check; /* accepted and not used: a components solve needs no host
+                                 convergence check */
     int32_t use_graph;        /* batched list ranking and components: replay a captured
                                  hipGraph (see pj_graph_cache_clear) */
     int32_t *d_status;        /* optional device int32[instances]: PJ_OK / PJ_EBADLIST / PJ_ENOCONV */
@@ -126,7 +127,8 @@ typedef struct pj_stats {
     int32_t algo;                 /* algorithm actually run */
     int32_t levels;               /* ruling set: walk levels (recursion depth) */
     int32_t base_kind;            /* ruling set: 1 LDS workgroup, 2 device-wide pointer jumping */
-    int32_t rounds;               /* components: Shiloach-Vishkin rounds run;
+    int32_t rounds;               /* components: the hooks, and the parent steps of the deepest
+                                     vertex a shortcut pass found (1 + steps);
                                      Wyllie: pointer-jumping rounds, ceil(log2) of the
                                      longest list */
     int64_t level_nodes[PJ_MAX_LEVELS + 1]; /* nodes at each level (level 0 = input) */
@@ -307,17 +309,13 @@ int pj_connected_components_batched_ex(const int32_t *src, const int32_t *dst,
 
 /*
  * Components with opts->use_graph = 1 (plain or batched, not with
- * opts->stats) capture the solve once into a hipGraph: the batched pair
- * rewrite and initialisation, the first 8 rounds (a round that follows one
- * without change returns at once on the device) and the canonicalisation,
- * which runs only if the solve converged within those rounds.  A call
- * launches the graph, reads the 8th round's change flag (one stream
- * synchronisation) and, only if it is raised, finishes the remaining rounds
- * and the canonicalisation without the graph, on the same state.  The cache
- * key holds the device, every array address, n, m and G (and whether the
- * status is read back); the arrays' contents may change between calls.  The
- * cache owns the workspace and holds up to 8 graphs; pj_graph_cache_clear()
- * frees them with the list-ranking graphs.
+ * opts->stats) capture the solve's launches once into a hipGraph and replay
+ * them with one hipGraphLaunch.  The cache key holds the device, every array
+ * address, n, m and G, whether the status is read back, and the path the
+ * solve takes (which follows from the sizes of the largest graph); the
+ * arrays' contents may change between calls.  The cache owns the workspace
+ * and holds up to 8 graphs; pj_graph_cache_clear() frees them with the
+ * list-ranking graphs.
  */
 
 /* Bytes of workspace a components call needs (G = 1: enough for both the plain
