@@ -1,6 +1,8 @@
 """Components at the edges of the solver's paths: chunks of 2048 pairs, parts
 of the pairs (2 m < 3 n or not), class bytes (n >= 3 * 2^19, m >= 3 n) used and
-not used, and chains as long as the graph.  Labels are exact."""
+not used, chains as long as the graph, and the one-workgroup solver (16384 and
+65536 vertices, rows and chunks of pairs, 512 graphs at a time, heavy graphs
+first).  Labels are exact."""
 
 import numpy as np
 import pytest
@@ -67,3 +69,73 @@ def test_device_wide_path(pj, case):
     src, dst, n = device_wide_graph(case)
     want = oracle.connected_components(src.astype(np.int32), dst.astype(np.int32), n)
     assert np.array_equal(solve(pj, src, dst, n), want)
+
+
+@pytest.mark.parametrize("n,m", [(1, 1), (2, 3), (63, 64), (500, 511), (500, 512), (500, 513),
+                                 (16384, 20_000), (16385, 20_000), (65_535, 30_001),
+                                 (65_536, 70_000), (65_537, 30_000)])
+def test_one_workgroup_graph(pj, n, m):
+    src, dst = W.random_graph(n, m, n + 7 * m)
+    src[-1] = dst[-1] = n - 1           # the last vertex is read and written
+    assert np.array_equal(solve(pj, src, dst, n), oracle.connected_components(src, dst, n))
+
+
+def test_one_workgroup_chain(pj):
+    n = 65_536                          # blind hooks make one chain of the whole LDS
+    i = np.arange(n - 1, dtype=np.int32)
+    assert (solve(pj, i, i + 1, n) == 0).all()
+    back = i[::-1].copy()
+    assert (solve(pj, back + 1, back, n) == 0).all()
+
+
+def batch(case):
+    rng = np.random.default_rng(5)
+    if case == "tiny":                  # more graphs than one workgroup takes at a time
+        sizes = rng.integers(0, 4, 1500)
+        pairs = np.where(sizes > 0, rng.integers(0, 5, 1500), 0)
+    elif case == "capacity":            # a graph that fills LDS between small ones
+        sizes = np.array([100, 0, 65_536, 1, 65_535, 2000, 16_384])
+        pairs = np.array([150, 0, 70_000, 2, 66_000, 0, 20_001])
+    elif case == "heavy":               # more workgroups than CUs and a few heavy graphs
+        sizes = np.concatenate([rng.integers(100, 4000, 400), [30_000, 50, 40_000]])
+        pairs = np.concatenate([rng.integers(100, 4000, 400), [50_000, 60, 80_000]])
+    else:                               # one graph too large for LDS: all device-wide
+        sizes = np.array([300, 65_537, 40])
+        pairs = np.array([400, 80_000, 50])
+    voff = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    eoff = np.concatenate([[0], np.cumsum(pairs)]).astype(np.int64)
+    bound = np.repeat(sizes, pairs)
+    src = (rng.random(bound.shape[0]) * bound).astype(np.int32)
+    dst = (rng.random(bound.shape[0]) * bound).astype(np.int32)
+    return src, dst, voff, eoff
+
+
+@pytest.mark.parametrize("case", ["tiny", "capacity", "heavy", "too_large"])
+@pytest.mark.parametrize("tables", ["host", "device", "graph"])
+def test_batch_of_one_workgroup_graphs(pj, case, tables):
+    src, dst, voff, eoff = batch(case)
+    G = voff.shape[0] - 1
+    want = oracle.connected_components_batched(src, dst, voff, eoff)
+    bad = int(np.argmax(np.diff(eoff)))           # and then one pair out of range
+    broken = dst.copy()
+    broken[eoff[bad]] = voff[bad + 1] - voff[bad]
+    kw = {} if tables == "device" else {"h_vtx_off": voff, "h_edge_off": eoff}
+    if tables == "graph":
+        kw["use_graph"] = True
+    st = torch.empty(G, dtype=torch.int32, device="cuda")
+    ds, dd = dev(src), dev(dst)
+    dv, de = torch.from_numpy(voff).cuda(), torch.from_numpy(eoff).cuda()
+    lab = torch.empty(int(voff[-1]), dtype=torch.int32, device="cuda")
+    for pairs, code in ((dst, pj.PJ_OK), (broken, pj.PJ_EINVAL), (dst, pj.PJ_OK)):
+        dd.copy_(dev(pairs))
+        lab.fill_(-1)
+        st.fill_(7)
+        pj.connected_components_batched(ds, dd, dv, de, lab, status=st, **kw)
+        torch.cuda.synchronize()
+        got, status = lab.cpu().numpy(), st.cpu().numpy()
+        assert status[bad] == code and (np.delete(status, bad) == pj.PJ_OK).all()
+        keep = np.ones(got.shape[0], dtype=bool)
+        if code != pj.PJ_OK:
+            keep[voff[bad]:voff[bad + 1]] = False
+        assert np.array_equal(got[keep], want[keep])
+    pj.graph_cache_clear()
