@@ -423,23 +423,6 @@ __device__ __forceinline__ int lds_flatten(uint32_t* par, int nv) {
   return most;
 }
 
-// Number of entries of the non-decreasing table off[0..count) below `target`,
-// found by all threads of the workgroup together (kLdsThreads probes a step).
-__device__ __forceinline__ int64_t count_below(const int64_t* __restrict__ off, int64_t count,
-                                               int64_t target) {
-  int64_t lo = 0, hi = count;  // the answer lies in [lo, hi]
-  while (lo < hi) {
-    const int64_t step = (hi - lo + kLdsThreads - 1) / kLdsThreads;
-    const int64_t i = lo + threadIdx.x * step;
-    const int below = __syncthreads_count(i < hi && off[i] < target);
-    if (below == 0) return lo;
-    const int64_t last = lo + (below - 1) * step;  // the last probe below the target
-    hi = min(hi, last + step);
-    lo = last + 1;
-  }
-  return lo;
-}
-
 // voff == nullptr: one graph of n vertices and m pairs.  The host has checked
 // the tables it planned with; what the device's hold is checked here against
 // n, m and kCap, and graphs that do not fit get PJ_EINVAL.
@@ -462,8 +445,8 @@ __global__ void __launch_bounds__(kLdsThreads) cc_lds(
   const int block = (int)blockIdx.x % bins;
   int64_t g0 = 0, g1 = 1;
   if (voff) {
-    g0 = block == 0 ? 0 : count_below(voff, G, (int64_t)block * bin);
-    g1 = block == bins - 1 ? G : count_below(voff, G, (int64_t)(block + 1) * bin);
+    g0 = block == 0 ? 0 : count_below<kLdsThreads>(voff, G, (int64_t)block * bin);
+    g1 = block == bins - 1 ? G : count_below<kLdsThreads>(voff, G, (int64_t)(block + 1) * bin);
   }
   int deep = 0;
   for (int64_t ga = g0; ga < g1;) {

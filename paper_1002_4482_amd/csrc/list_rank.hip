@@ -1014,17 +1014,139 @@ __global__ void __launch_bounds__(1024) wy_final(const unsigned long long* __res
   }
 }
 
-// ------------------------------------------------------- small one-group
-// A whole batch of at most kMaxCutoff nodes ranked by one workgroup:
-// predecessor links in LDS, pointer jumping along them with unit weights.
-// succ is read before any rank is written (in place allowed).  With weights,
-// a node's own term is its predecessor's weight instead of 1.
-__global__ void __launch_bounds__(kBaseThreads) lr_small(const int32_t* succ,
-                                                         const int32_t* weight,
-                                                         const int64_t* __restrict__ off, int L,
-                                                         int n, int32_t* rank,
-                                                         int to_tail, int32_t* ltails,
-                                                         int32_t* lerr) {
+// ------------------------------------------------- one workgroup's lists
+// Lists short enough for LDS: a workgroup reads its lists' successors once,
+// ranks them by pointer jumping in LDS and writes the ranks, one kernel in all.
+// A node's word holds (distance << 16 | node) to the node it has jumped to, so a
+// jump is one LDS read and one write; a tail points to itself at distance 0.
+// Jumping in place is safe: whatever version of a word a jump reads is a true
+// distance.  A list is one list exactly if no successor is out of range and
+// some node is size - 1 jumps away from a tail (with two tails, a branch or a
+// cycle no node is).
+//
+// A workgroup takes the lists that start in its block of `bin` consecutive
+// nodes, up to kSubLists lists and kCap nodes at a time.  Bound by LDS accesses
+// (ceil(log2 of the longest list) jumps a node) and, for one short list, by the
+// launch.  20000 lists of 2^3..2^10 nodes: 341 us on the sublist walks, 49 us
+// here; one list of 4096 nodes took 32 us a call with links and sums apart and a
+// kernel before it, and 12.6 us; of 16384 nodes 72 and 29 us.
+constexpr int kSubLists = 1024;
+
+template <int kCap, int kThreads>
+__global__ void __launch_bounds__(kThreads) lr_lds(const int32_t* succ, int n,
+                                                   const int64_t* __restrict__ off, int L,
+                                                   int bin, int to_tail, int32_t* rank,
+                                                   int32_t* lerr, int32_t* status) {
+  constexpr int kRows = kCap / kThreads;
+  __shared__ uint32_t word[kCap];
+  __shared__ int so[kSubLists + 1];
+  __shared__ uint32_t whole[kSubLists / 32], bad[kSubLists / 32];
+  __shared__ int longest;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int lane = lane_id();
+  int64_t l0 = 0, l1 = 1;
+  if (off) {
+    l0 = blockIdx.x == 0 ? 0 : count_below<kThreads>(off, L, (int64_t)blockIdx.x * bin);
+    l1 = blockIdx.x == gridDim.x - 1
+             ? L : count_below<kThreads>(off, L, (int64_t)(blockIdx.x + 1) * bin);
+  }
+  for (int64_t la = l0; la < l1;) {
+    int k = (int)min<int64_t>(l1 - la, kSubLists);
+    const int64_t v0 = off ? off[la] : 0;
+    __syncthreads();  // the last lists' tables and words are done with
+    for (int i = tid; i <= k; i += kThreads) {
+      const int64_t d = (off ? off[la + i] : i * (int64_t)n) - v0;
+      so[i] = (int)min<int64_t>(max<int64_t>(d, 0), INT32_MAX);
+    }
+    if (tid < kSubLists / 32) whole[tid] = bad[tid] = 0;
+    if (tid == 0) longest = 1;
+    __syncthreads();
+    int fit = 0;  // lists of the group that fit LDS together
+    for (int i0 = 0; i0 < k; i0 += kThreads)
+      fit += __syncthreads_count(i0 + tid < k && so[i0 + tid + 1] <= kCap);
+    const int take = max(fit, 1);
+    const int nv = so[take];
+    if (fit == 0 || v0 < 0 || v0 + nv > n) {  // not the table the host planned with
+      for (int i = tid; i < take; i += kThreads) {
+        if (status) status[la + i] = PJ_EBADLIST;
+        if (lerr) lerr[la + i] = kErrRange;
+      }
+      la += take;
+      continue;
+    }
+    k = take;
+    int most = 1;
+    for (int i = tid; i < k; i += kThreads) most = max(most, so[i + 1] - so[i]);
+    most = -wave_min(-most);
+    if (lane == 0) atomicMax(&longest, most);
+    // a wave owns rows of 64 consecutive nodes, so it looks a list up once and
+    // follows the boundaries forward
+    const int rows = (nv + kThreads - 1) / kThreads;
+    const int j0 = wave * rows * kWave + lane;
+    uint32_t mine[kRows];
+#pragma unroll
+    for (int t = 0; t < kRows; ++t)
+      if (t < rows && j0 + t * kWave < nv) mine[t] = (uint32_t)succ[v0 + j0 + t * kWave];
+    int l = k > 1 && j0 < nv ? lds_find(so, k, j0) : 0;
+#pragma unroll
+    for (int t = 0; t < kRows; ++t) {
+      const int j = j0 + t * kWave;
+      if (t < rows && j < nv) {
+        while (l < k - 1 && so[l + 1] <= j) ++l;
+        const int base = so[l], size = min(so[l + 1], nv) - base;
+        const int s = (int)mine[t];
+        const bool tail = (s == -1) | (s == j - base);
+        const bool range = s >= 0 && s < size;
+        if (!tail && !range) atomicOr(&bad[l >> 5], 1u << (l & 31));
+        mine[t] = tail || !range ? (uint32_t)j : 1u << 16 | (uint32_t)(base + s);
+        word[j] = mine[t];
+      }
+    }
+    __syncthreads();
+    for (int span = 1; span < longest; span *= 2) {
+#pragma unroll
+      for (int t = 0; t < kRows; ++t) {
+        const int j = j0 + t * kWave;
+        if (t < rows && j < nv) {
+          const uint32_t w = word[mine[t] & 0xffff];
+          const uint32_t next = (((mine[t] >> 16) + (w >> 16)) << 16) | (w & 0xffff);
+          if (next != mine[t]) word[j] = mine[t] = next;
+        }
+      }
+      __syncthreads();
+    }
+    l = k > 1 && j0 < nv ? lds_find(so, k, j0) : 0;
+#pragma unroll
+    for (int t = 0; t < kRows; ++t) {
+      const int j = j0 + t * kWave;
+      if (t < rows && j < nv) {
+        while (l < k - 1 && so[l + 1] <= j) ++l;
+        const int size = so[l + 1] - so[l], d = (int)(mine[t] >> 16), end = mine[t] & 0xffff;
+        if (d == size - 1 && (int)(word[end] & 0xffff) == end)
+          atomicOr(&whole[l >> 5], 1u << (l & 31));
+        rank[v0 + j] = to_tail ? d : size - 1 - d;
+      }
+    }
+    if (status || lerr) {
+      __syncthreads();
+      for (int i = tid; i < k; i += kThreads) {
+        const bool ok = so[i + 1] == so[i] || ((whole[i >> 5] & ~bad[i >> 5]) >> (i & 31) & 1);
+        if (status) status[la + i] = ok ? PJ_OK : PJ_EBADLIST;
+        if (lerr) lerr[la + i] = ok ? 0 : kErrBase;
+      }
+    }
+    la += k;
+  }
+}
+
+// Weighted: a whole batch of at most kMaxCutoff nodes in one workgroup,
+// predecessor links in LDS and pointer jumping along them, a node's own term
+// being its predecessor's weight.  succ is read before any rank is written (in
+// place allowed).
+__global__ void __launch_bounds__(kBaseThreads) lr_small_weighted(
+    const int32_t* succ, const int32_t* __restrict__ weight, const int64_t* __restrict__ off,
+    int L, int n, int32_t* rank, int32_t* ltails, int32_t* lerr) {
   __shared__ int lnk[kMaxCutoff];
   __shared__ int pre[kMaxCutoff];
   const int tid = threadIdx.x;
@@ -1074,7 +1196,7 @@ __global__ void __launch_bounds__(kBaseThreads) lr_small(const int32_t* succ,
   __syncthreads();
   for (int j = tid; j < n; j += kBaseThreads) {
     const int p = lnk[j];
-    pre[j] = p >= 0 ? (weight ? weight[p] : 1) : 0;
+    pre[j] = p >= 0 ? weight[p] : 0;
   }
   __syncthreads();
   int rounds = 0;
@@ -1107,18 +1229,16 @@ __global__ void __launch_bounds__(kBaseThreads) lr_small(const int32_t* succ,
   }
   if (j0 < n) {
     int l = find_instance(off, L, j0);
-    int base = (int)off[l], end = (int)off[l + 1];
+    int end = (int)off[l + 1];
     for (int t = 0; t < kPerThread; ++t) {
       const int j = j0 + t;
       if (j >= n) break;
       while (j >= end) {
         ++l;
-        base = end;
         end = (int)off[l + 1];
       }
       if (lnk[j] != -1) atomicOr(&lerr[l], kErrBase);
-      const int v = pre[j];
-      rank[j] = to_tail ? end - base - 1 - v : v;
+      rank[j] = pre[j];
     }
   }
 }
@@ -1218,7 +1338,7 @@ inline int grid_for(int64_t n, int block, int cap) {
 
 struct Plan {
   int algo = PJ_ALGO_RULING_SET;
-  bool small = false;
+  bool small = false;      // every list ranked in LDS
   int levels = 0;          // walk levels
   int base_kind = 1;       // 1 LDS, 2 device-wide
   int64_t bound[PJ_MAX_LEVELS + 2] = {};
@@ -1254,12 +1374,13 @@ inline int bits_for(int64_t v) {  // bits to hold values 0..v-1
   return b;
 }
 
-// pack = false keeps level 0 in the separate (sublist, offset) state, which
-// weighted calls need (an offset is then a weight sum, not a step count).
 // chosen > 0: level 0 has that many caller-chosen splitters (never the
 // one-workgroup path, so that they are used).
-Plan make_plan(int64_t n0, int64_t L, int64_t max_size, const pj_opts& o, bool pack = true,
-               int64_t chosen = 0) {
+Plan make_plan(int64_t n0, int64_t L, int64_t max_size, const pj_opts& o, bool weighted,
+               int64_t chosen) {
+  // weighted calls need the separate (sublist, offset) state: an offset is then
+  // a weight sum, not a step count
+  const bool pack = !weighted && o.level0_state != PJ_STATE_SEPARATE;
   Plan p;
   p.algo = o.algo == PJ_ALGO_WYLLIE ? PJ_ALGO_WYLLIE : PJ_ALGO_RULING_SET;
   p.bound[0] = n0;
@@ -1268,7 +1389,12 @@ Plan make_plan(int64_t n0, int64_t L, int64_t max_size, const pj_opts& o, bool p
     return p;
   }
   p.chosen = chosen;
-  if (n0 <= kMaxCutoff && n0 <= o.cutoff && chosen == 0) {
+  // One workgroup's lists: the whole input, or (unweighted) every list of a
+  // batch up to the cutoff.  The latter looks at ceil(log2) of the longest list
+  // only, which the key of a captured batch holds.
+  int64_t longest = 1;
+  while (longest < max_size) longest *= 2;
+  if (chosen == 0 && (n0 <= o.cutoff || (!weighted && longest <= o.cutoff))) {
     p.small = true;
     return p;
   }
@@ -1393,6 +1519,22 @@ size_t carve(const Plan& p, int64_t L, bool single, bool validate, bool want_sta
   return bytes;
 }
 
+// Lists ranked in LDS (see lr_lds).  The smaller instance lets eight workgroups
+// share a CU.  A workgroup's block of nodes leaves room for the longest list to
+// run over its end, or, for lists over half the capacity, is half the capacity.
+int launch_lds(const int32_t* succ, int64_t n, int64_t max_size, const int64_t* d_off, int64_t L,
+               int32_t* rank, int to_tail, int32_t* lerr, int32_t* status, hipStream_t stream) {
+  constexpr int kSmallCap = 4096;
+  const bool small = d_off && max_size <= kSmallCap;
+  const int cap = small ? kSmallCap : kMaxCutoff;
+  const int bin = (int)std::max<int64_t>(cap / 2, cap - max_size);
+  const auto k = small ? lr_lds<kSmallCap, 256> : lr_lds<kMaxCutoff, kBaseThreads>;
+  hipLaunchKernelGGL(k, dim3(d_off ? (unsigned)(n / bin + 1) : 1), dim3(small ? 256 : kBaseThreads),
+                     0, stream, succ, (int)n, d_off, (int)L, bin, to_tail, rank, lerr, status);
+  PJ_HIP(hipGetLastError());
+  return PJ_OK;
+}
+
 }  // namespace
 
 int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const int64_t* h_off,
@@ -1468,12 +1610,16 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
     o.max_walk = raw.max_walk > 0 ? std::max(raw.max_walk, 16) : o.max_walk;
     if (raw.block > 0) o.block = std::min(1024, (raw.block + 63) / 64 * 64);
   }
-  Plan p = make_plan(n0, L, max_size, o,
-                     weight == nullptr && o.level0_state != PJ_STATE_SEPARATE, chosen);
+  Plan p = make_plan(n0, L, max_size, o, weight != nullptr, chosen);
   if (chosen > 0 && !p.packed) return PJ_EINVAL;  // too many splitters for the packed state
   add_far_spacing(p, n0, L, far_spacing, o.max_walk);
   Buffers b;
   const size_t need = carve(p, L, single, o.validate != 0, want_status, nullptr, &b);
+  if (p.small && !weight && n0 > 0 && !o.validate && !(user && user->stats)) {
+    // one kernel, which also writes the statuses: no workspace, no init
+    if (o.workspace && o.workspace_bytes < need) return PJ_EINVAL;
+    return launch_lds(succ, n0, max_size, d_off, L, rank, o.to_tail, nullptr, o.d_status, stream);
+  }
   Workspace ws;
   PJ_TRY(workspace_acquire(ws, need, &o, stream));
   carve(p, L, single, o.validate != 0, want_status, &ws, &b);
@@ -1537,9 +1683,13 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
     }
     tm.mark("wyllie_final");
   } else if (n0 > 0 && p.small) {
-    hipLaunchKernelGGL(lr_small, dim3(1), dim3(kBaseThreads), 0, stream, succ, weight, off, Li,
-                       n, rank, o.to_tail, b.ltails, b.lerr);
-    check_tails = true;
+    if (weight) {
+      hipLaunchKernelGGL(lr_small_weighted, dim3(1), dim3(kBaseThreads), 0, stream, succ, weight,
+                         off, Li, n, rank, b.ltails, b.lerr);
+      check_tails = true;
+    } else {
+      PJ_TRY(launch_lds(succ, n0, max_size, d_off, L, rank, o.to_tail, b.lerr, nullptr, stream));
+    }
     tm.mark("small");
   } else if (n0 > 0) {
     // level 0 head find (and, in the packed form, the successor copy, which
@@ -1771,7 +1921,7 @@ size_t list_rank_workspace(int64_t n0, int64_t L, const pj_opts* user, bool sing
   pj_opts o = resolved_opts(&raw);
   const int64_t chosen = o.d_splitters && single && !weighted && n0 > 0
                              ? std::max<int64_t>(1, std::min(o.n_splitters, n0)) : 0;
-  Plan p = make_plan(n0, L, n0, o, !weighted && o.level0_state != PJ_STATE_SEPARATE, chosen);
+  Plan p = make_plan(n0, L, n0, o, weighted, chosen);
   Buffers b;
   return carve(p, L, single, o.validate != 0, o.validate && !o.d_status, nullptr, &b);
 }

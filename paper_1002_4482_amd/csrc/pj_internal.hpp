@@ -208,6 +208,36 @@ __device__ __forceinline__ int find_instance(const int64_t* __restrict__ off, in
   return lo;
 }
 
+// Number of entries of the non-decreasing table off[0..count) below `target`,
+// found by all kThreads threads of the workgroup together, kThreads probes a
+// step.
+template <int kThreads>
+__device__ __forceinline__ int64_t count_below(const int64_t* __restrict__ off, int64_t count,
+                                               int64_t target) {
+  int64_t lo = 0, hi = count;  // the answer lies in [lo, hi]
+  while (lo < hi) {
+    const int64_t step = (hi - lo + kThreads - 1) / kThreads;
+    const int64_t i = lo + threadIdx.x * step;
+    const int below = __syncthreads_count(i < hi && off[i] < target);
+    if (below == 0) return lo;
+    const int64_t last = lo + (below - 1) * step;  // the last probe below the target
+    hi = min(hi, last + step);
+    lo = last + 1;
+  }
+  return lo;
+}
+
+// Largest i in [0, k) with off[i] <= e, for a table in LDS with off[0] <= e.
+__device__ __forceinline__ int lds_find(const int* off, int k, int e) {
+  int lo = 0, hi = k - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (off[mid] <= e) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
 // Device-scope relaxed atomic store: written through to the device-coherent
 // level, so a store from one XCD is not lost behind another XCD's
 // write-back L2 when several workgroups write the same word.
