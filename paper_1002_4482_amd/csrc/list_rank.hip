@@ -768,6 +768,211 @@ __global__ void __launch_bounds__(kBaseThreads) lr_base_lds(const int2* __restri
   }
 }
 
+// The same for a few lists (at most kBaseLists), by the ruling set once more,
+// inside LDS: one splitter per kBaseBlock ids and the heads; a thread walks its
+// splitters' sublists, the splitters are ranked by pointer jumping, and a node
+// gets its splitter's rank + its offset.  Jumping over all nodes takes
+// ceil(log2 N) rounds of two LDS accesses a node, which set its time (12500
+// nodes: BASEOLD us); here a node costs three accesses, and only a quarter of
+// the nodes jump (BASENEW us).
+//
+// word[x]: {weight, next (| kStop)} at first; {offset, splitter | kSeen} once a walk has
+// passed x; of a splitter {weight of the sublists before it, ancestor} while
+// jumping.
+constexpr int kBaseBlock = 4;
+constexpr int kBaseLists = 1024;
+constexpr int kSeen = 1 << 30;
+constexpr int kStop = 1 << 29;  // the next node is a splitter
+constexpr unsigned long long kNoPred = ~0ull;
+
+__device__ __forceinline__ unsigned long long pack_w(int hi, uint32_t lo) {
+  return (unsigned long long)(unsigned)hi << 32 | lo;
+}
+
+__global__ void __launch_bounds__(kBaseThreads) lr_base_walk(const int2* __restrict__ link,
+                                                             int32_t* __restrict__ srank,
+                                                             LrCtl* ctl, int level, int L,
+                                                             int cap_prev) {
+  __shared__ unsigned long long word[kMaxCutoff];
+  __shared__ unsigned long long total;
+  __shared__ int taken;
+  const int N = level_nodes(ctl, level, L, cap_prev);
+  const int head_base = ctl->lv[level - 1].r;
+  const int tid = threadIdx.x;
+  if (tid == 0) {
+    total = 0ull;
+    taken = 0;
+  }
+  if (N > kMaxCutoff || head_base + L > N) {
+    if (tid == 0) atomicOr(&ctl->err, kErrBase);
+    return;
+  }
+  const auto block_splitter = [&](int b) {
+    const int x = b * kBaseBlock + (int)(mix32((uint32_t)b) >> 16) % kBaseBlock;
+    return x < N ? x : b * kBaseBlock;
+  };
+  const auto is_head = [&](int x) { return x >= head_base && x < head_base + L; };
+  const auto is_splitter = [&](int x) {
+    return x == block_splitter(x / kBaseBlock) || is_head(x);
+  };
+  bool bad = false;
+  unsigned long long mytotal = 0;
+  {
+    int2 in[kPerThread];
+#pragma unroll
+    for (int t = 0; t < kPerThread; ++t) {
+      const int j = tid + t * kBaseThreads;
+      in[t] = j < N ? link[j] : make_int2(-1, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < kPerThread; ++t) {
+      const int j = tid + t * kBaseThreads;
+      if (j >= N) continue;
+      const bool end = in[t].x < 0 || in[t].x >= N;
+      bad |= end && in[t].x != -1;
+      mytotal += (unsigned)in[t].y;
+      const bool stop = !end && is_splitter(in[t].x);
+      word[j] = pack_w(in[t].y, end ? ~0u : (uint32_t)in[t].x | (stop ? kStop : 0));
+    }
+  }
+  // the thread's splitters: one per row of blocks, then one head
+  constexpr int kRows = kMaxCutoff / kBaseBlock / kBaseThreads + 1;
+  const int blocks = (N + kBaseBlock - 1) / kBaseBlock;
+  int mine[kRows], reach[kRows], weight[kRows];
+#pragma unroll
+  for (int t = 0; t < kRows; ++t) {
+    mine[t] = -1;
+    if (t < kRows - 1) {
+      const int b = tid + t * kBaseThreads;
+      if (b < blocks) mine[t] = block_splitter(b);
+    } else if (tid < L) {
+      const int h = head_base + tid;
+      if (block_splitter(h / kBaseBlock) != h) mine[t] = h;
+    }
+  }
+  __syncthreads();
+  // Walks: a lane takes a splitter, follows its successors to the next one and
+  // leaves {sublist weight, next splitter or -1} in the splitter's word, which
+  // no other walk reads.
+  {
+    const int slots = blocks + L;
+    int own = -1, x = -1, acc = 0, steps = 0;
+    bool retired = false;
+    for (;;) {
+      const uint64_t idle = __ballot(own < 0 && !retired);
+      if (idle) {
+        int first = 0;
+        if (lane_id() == __builtin_ctzll(idle)) first = atomicAdd(&taken, (int)__popcll(idle));
+        first = __shfl(first, __builtin_ctzll(idle));
+        if (own < 0 && !retired) {
+          const int slot = first + lanes_below(idle);
+          retired = slot >= slots;
+          if (!retired) {
+            own = slot < blocks ? block_splitter(slot) : head_base + slot - blocks;
+            if (slot >= blocks && block_splitter(own / kBaseBlock) == own) {
+              own = -1;  // a head that is its block's splitter
+            } else {
+              const unsigned long long w = word[own];
+              x = (int)(uint32_t)w;
+              acc = (int)(w >> 32);
+            }
+          }
+        }
+      }
+      if (__ballot(!retired) == 0) break;
+#pragma unroll
+      for (int rep = 0; rep < 4; ++rep)
+        if (own >= 0) {
+          if (x < 0 || (x & kStop)) {
+            word[own] = pack_w(acc, x < 0 ? ~0u : (uint32_t)(x & ~kStop));
+            own = -1;
+          } else {
+            const unsigned long long w = word[x];
+            const int next = (int)(uint32_t)w;
+            if ((next >= 0 && (next & kSeen)) || ++steps > 2 * kMaxCutoff) {
+              bad = true;  // walked already (a branch), or a cycle without a splitter
+              x = -1;
+            } else {
+              word[x] = pack_w(acc, (uint32_t)(own | kSeen));
+              acc += (int)(w >> 32);
+              x = next;
+            }
+          }
+        }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < kRows; ++t)
+    if (mine[t] >= 0) {
+      const unsigned long long w = word[mine[t]];
+      reach[t] = (int)(uint32_t)w;
+      weight[t] = (int)(w >> 32);
+    }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < kRows; ++t)
+    if (mine[t] >= 0) word[mine[t]] = is_head(mine[t]) ? pack_w(0, (uint32_t)mine[t]) : kNoPred;
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < kRows; ++t)
+    if (mine[t] >= 0 && reach[t] >= 0)
+      bad |= atomicExch(&word[reach[t]], pack_w(weight[t], (uint32_t)mine[t])) != kNoPred;
+  __syncthreads();
+  unsigned long long at[kRows];
+#pragma unroll
+  for (int t = 0; t < kRows; ++t)
+    if (mine[t] >= 0) {
+      at[t] = word[mine[t]];
+      if (at[t] == kNoPred) bad = true;  // a head that is no list's
+    }
+  if (bad) atomicOr(&ctl->err, kErrBase);
+  // (a malformed forest may leave splitters without predecessor: they jump
+  // nowhere)
+#pragma unroll
+  for (int t = 0; t < kRows; ++t)
+    if (mine[t] >= 0 && at[t] == kNoPred) word[mine[t]] = at[t] = pack_w(0, (uint32_t)mine[t]);
+  __syncthreads();
+  for (int span = 1; span < 2 * (blocks + L); span *= 2) {
+    bool moved = false;
+#pragma unroll
+    for (int t = 0; t < kRows; ++t)
+      if (mine[t] >= 0) {
+        const unsigned long long w = word[(uint32_t)at[t]];
+        if ((uint32_t)w != (uint32_t)at[t]) {
+          at[t] = pack_w((int)(at[t] >> 32) + (int)(w >> 32), (uint32_t)w);
+          word[mine[t]] = at[t];
+          moved = true;
+        }
+      }
+    if (!__syncthreads_or(moved)) break;
+  }
+  mytotal = wave_sum(mytotal);
+  if (lane_id() == 0 && mytotal) atomicAdd(&total, mytotal);
+  bad = false;
+#pragma unroll
+  for (int t = 0; t < kPerThread; ++t) {
+    const int j = tid + t * kBaseThreads;
+    if (j >= N) continue;
+    unsigned long long w = word[j];
+    int v = (int)(w >> 32);
+    if (!is_splitter(j)) {
+      if (((int)(uint32_t)w & kSeen) == 0 || (uint32_t)w == ~0u) {
+        bad = true;  // no walk came by
+        w = pack_w(0, (uint32_t)head_base);
+      } else {
+        w = word[(int)(uint32_t)w & ~kSeen];
+        v += (int)(w >> 32);
+      }
+    }
+    bad |= !is_head((int)(uint32_t)w);
+    srank[j] = v;
+  }
+  if (bad) atomicOr(&ctl->err, kErrBase);
+  __syncthreads();
+  if (tid == 0) ctl->base_total = total;
+}
+
 // ---------------------------------------------------- base: device-wide
 // The same predecessor pointer jumping for forests too large for one
 // workgroup, one launch per round; (prefix, link) pairs are packed into one
@@ -1768,7 +1973,8 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
     const int top = p.levels;
     const int cap_prev = p.cap[top - 1];
     if (p.base_kind == 1) {
-      hipLaunchKernelGGL(lr_base_lds, dim3(1), dim3(kBaseThreads), 0, stream, b.link[top],
+      hipLaunchKernelGGL(L <= kBaseLists ? lr_base_walk : lr_base_lds, dim3(1),
+                         dim3(kBaseThreads), 0, stream, b.link[top],
                          b.srank[top], b.ctl, top, Li, cap_prev);
     } else {
       const int g = grid_for(p.bound[top], 256, gcap);
