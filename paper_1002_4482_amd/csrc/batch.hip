@@ -155,8 +155,13 @@ int graph_batched(const int32_t* succ, const int64_t* d_off, int64_t L, const in
     o.use_graph = 0;
     o.stats = nullptr;
     o.h_offsets = h_off;
-    const size_t bytes = std::max<size_t>(list_rank_workspace(n0, L, &o, false), 256);
-    PJ_HIP(hipMalloc(&e.ws, bytes));
+    // room for the recorded walk where the batch suits it and memory allows
+    size_t bytes = std::max<size_t>(list_rank_graph_workspace(n0, L, max_size, &o), 256);
+    if (hipMalloc(&e.ws, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      bytes = std::max<size_t>(list_rank_workspace(n0, L, &o, false), 256);
+      PJ_HIP(hipMalloc(&e.ws, bytes));
+    }
     o.workspace = e.ws;
     o.workspace_bytes = bytes;
     hipGraph_t graph = nullptr;

@@ -55,6 +55,12 @@ struct LrCtl {
 // A successor within kNear ids of its node counts as local (see lr_walk).
 constexpr int kNear = 64;
 
+// Most successors are not local: level 0 takes the far spacing, where the plan
+// has one.
+__device__ __forceinline__ bool far_chosen(const LrCtl* ctl, int N) {
+  return 2ull * ctl->near <= (unsigned long long)N;
+}
+
 // Node count of level `level` >= 1: static + virtual + granted cut points of
 // the level below.
 __device__ __forceinline__ int level_nodes(const LrCtl* ctl, int level, int L, int cap_prev) {
@@ -76,11 +82,49 @@ __device__ __forceinline__ bool is_static(int y, int N, int log2B, uint32_t seed
   return (uint32_t)(y - start) == splitter_offset((uint32_t)b, seed, (uint32_t)bsize);
 }
 
+// What a walk needs to know of a node's successor y (a global id), worked out
+// once by the head-find pass so that a step of the walk is a read and a sign
+// test: y, with the sign bit set if y is a static splitter.  A tail is -1.
+constexpr int kNoCopy = 0, kPlainCopy = 1, kCodedCopy = 2;
+
+__device__ __forceinline__ int step_code(int y, int N, int log2B, uint32_t seed) {
+  return is_static(y, N, log2B, seed) ? y | INT32_MIN : y;
+}
+
 __device__ __forceinline__ void store_pair(int2* p, int a, int b) { *p = make_int2(a, b); }
+
+// Recorded walk (see lr_walk_rec).
+constexpr int kStrip = 16;
+constexpr int kSlab = 256;
+constexpr int kXcds = 8;
+constexpr int kBinShift = 15;
+constexpr int kBinNodes = 1 << kBinShift;  // 128 KiB of ranks in LDS
+constexpr int kTileSlabs = 4;
+constexpr int kTileThreads = kTileSlabs * kSlab;
+constexpr int kTileBins = 2048;
+
+struct RecCtl {
+  int32_t slabs;             // slabs taken
+  int32_t listed[kXcds];     // entries of slab_of
+};
+
+struct RecArgs {
+  RecCtl* ctl;
+  int4* strips;         // kStrip node ids (-1: none) per strip
+  int2* head;           // {sublist id, offset of the strip's first node} per strip
+  int32_t* slab_of;     // [kXcds][max_slabs]
+  int32_t* used;        // strips used of each slab
+  int32_t* chunk_list;  // a batch: first list of each chunk
+  int32_t* cursor;      // entries of each bin
+  uint2* ent;           // {node, rank}, kBinNodes per bin
+  int max_slabs;
+  int log2B;            // splitter spacing
+  int if_far;           // only if the head-find pass found the list not local
+};
 
 // ------------------------------------------------------------------ init
 __global__ void lr_init(LrCtl* ctl, int n0, unsigned long long* lsum, int32_t* ltails,
-                        int32_t* lerr, int L, int64_t* off_single) {
+                        int32_t* lerr, int L, int64_t* off_single, RecArgs rec, int nbins) {
   int tid = blockIdx.x * blockDim.x + threadIdx.x;
   int stride = gridDim.x * blockDim.x;
   int32_t* c = reinterpret_cast<int32_t*>(ctl);
@@ -90,6 +134,8 @@ __global__ void lr_init(LrCtl* ctl, int n0, unsigned long long* lsum, int32_t* l
     ltails[i] = 0;
     lerr[i] = 0;
   }
+  if (rec.ctl && tid < (int)(sizeof(RecCtl) / 4)) reinterpret_cast<int32_t*>(rec.ctl)[tid] = 0;
+  for (int i = tid; i < nbins; i += stride) rec.cursor[i] = 0;
   if (tid == 0) {
     ctl->lv[0].n = n0;
     if (off_single) {
@@ -104,9 +150,9 @@ __global__ void lr_init(LrCtl* ctl, int n0, unsigned long long* lsum, int32_t* l
 // are exactly the non-tail successors, so
 //   head = size(size-1)/2 - sum of non-tail successors.
 // The same coalesced pass counts tails and flags out-of-range successors.
-template <bool kCopy>
-__global__ void __launch_bounds__(256) lr_headfind_single(const int32_t* __restrict__ succ, int n,
-                                                          int32_t* __restrict__ copy,
+template <int kCopy>
+__global__ void __launch_bounds__(256) lr_headfind_single(const int32_t* succ, int n,
+                                                          int32_t* copy, int log2B, uint32_t seed,
                                                           unsigned long long* lsum,
                                                           int32_t* ltails, int32_t* lerr,
                                                           unsigned long long* lnear) {
@@ -117,31 +163,27 @@ __global__ void __launch_bounds__(256) lr_headfind_single(const int32_t* __restr
   const bool vec = ((reinterpret_cast<uintptr_t>(succ) | reinterpret_cast<uintptr_t>(copy)) & 15) == 0;
   const int n4 = vec ? (n >> 2) : 0;
   const int4* s4 = reinterpret_cast<const int4*>(succ);
-  for (int q = tid; q < n4; q += stride) {
-    const int4 v = s4[q];
-    if (kCopy) reinterpret_cast<int4*>(copy)[q] = v;
-    int i = q << 2;
-    int vs[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      int s = vs[t];
-      bool tail = (s == -1) | (s == i + t);
-      bool range = (unsigned)s < (unsigned)n;
-      tails += tail;
-      bad |= (!tail & !range);
-      acc += (!tail & range) ? (unsigned long long)s : 0ull;
-      near += (!tail & range) & ((unsigned)(s - (i + t) + kNear) <= 2u * kNear);
-    }
-  }
-  for (int i = (n4 << 2) + tid; i < n; i += stride) {
-    int s = succ[i];
-    if (kCopy) copy[i] = s;
-    bool tail = (s == -1) | (s == i);
-    bool range = (unsigned)s < (unsigned)n;
+  const auto one = [&](int s, int i) {  // counts node i, returns its code
+    const bool tail = (s == -1) | (s == i);
+    const bool range = (unsigned)s < (unsigned)n;
     tails += tail;
     bad |= (!tail & !range);
     acc += (!tail & range) ? (unsigned long long)s : 0ull;
     near += (!tail & range) & ((unsigned)(s - i + kNear) <= 2u * kNear);
+    return kCopy != kCodedCopy ? s : (tail | !range) ? -1 : step_code(s, n, log2B, seed);
+  };
+  for (int q = tid; q < n4; q += stride) {
+    int4 v = s4[q];
+    const int i = q << 2;
+    v.x = one(v.x, i);
+    v.y = one(v.y, i + 1);
+    v.z = one(v.z, i + 2);
+    v.w = one(v.w, i + 3);
+    if (kCopy != kNoCopy) reinterpret_cast<int4*>(copy)[q] = v;
+  }
+  for (int i = (n4 << 2) + tid; i < n; i += stride) {
+    const int v = one(succ[i], i);
+    if (kCopy != kNoCopy) copy[i] = v;
   }
   acc = wave_sum(acc);
   tails = wave_sum(tails);
@@ -173,12 +215,16 @@ __global__ void __launch_bounds__(256) lr_headfind_single(const int32_t* __restr
 }
 
 // Batched form: each wave owns chunks of 64*kChunk consecutive positions and
-// tracks the owning list while it advances.
+// tracks the owning list while it advances.  Its sums go to the list's words
+// when it leaves the list, so a wave takes four chunks where there are enough
+// (headfind_grid): with one each, the atomics of a few long lists serialise (8
+// lists of 1.4 M nodes: 150 us, 60 us with several).
 constexpr int kHfChunk = 16;
-template <bool kCopy>
-__global__ void __launch_bounds__(256) lr_headfind_batched(const int32_t* __restrict__ succ,
+template <int kCopy>
+__global__ void __launch_bounds__(256) lr_headfind_batched(const int32_t* succ,
                                                            const int64_t* __restrict__ off, int L,
-                                                           int n, int32_t* __restrict__ copy,
+                                                           int n, int32_t* copy, int log2B,
+                                                           uint32_t seed,
                                                            unsigned long long* lsum,
                                                            int32_t* ltails, int32_t* lerr) {
   const int wave = (blockIdx.x * blockDim.x + threadIdx.x) / kWave;
@@ -191,13 +237,13 @@ __global__ void __launch_bounds__(256) lr_headfind_batched(const int32_t* __rest
   const int64_t per = (nchunks + nwaves - 1) / nwaves;
   const int64_t ci0 = (int64_t)wave * per;
   const int64_t ci1 = ci0 + per < nchunks ? ci0 + per : nchunks;
-  int l = ci0 < ci1 ? find_instance(off, L, ci0 * chunk) : 0;
+  if (ci0 >= ci1) return;
+  int l = find_instance(off, L, ci0 * chunk);
+  int64_t lbase = off[l], lend = off[l + 1];
+  unsigned long long acc = 0;
+  int tails = 0;
   for (int64_t ci = ci0; ci < ci1; ++ci) {
     const int64_t c0 = ci * chunk;
-    int64_t lend = off[l + 1];
-    int64_t lbase = off[l];
-    unsigned long long acc = 0;
-    int tails = 0;
     // all loads (and the copy) of the chunk first: the flushes below hold
     // atomics that would otherwise keep each load waiting for the last
     int sv[kHfChunk];
@@ -206,7 +252,7 @@ __global__ void __launch_bounds__(256) lr_headfind_batched(const int32_t* __rest
       const int64_t g = c0 + t * kWave + lane;
       sv[t] = g < n ? succ[g] : 0;
     }
-    if (kCopy) {
+    if (kCopy == kPlainCopy) {
 #pragma unroll
       for (int t = 0; t < kHfChunk; ++t) {
         const int64_t g = c0 + t * kWave + lane;
@@ -233,20 +279,22 @@ __global__ void __launch_bounds__(256) lr_headfind_batched(const int32_t* __rest
       tails += tail;
       if (!tail & !range) atomicOr(&lerr[l], kErrRange);
       acc += (!tail & range) ? (unsigned long long)s : 0ull;
+      if (kCopy == kCodedCopy)
+        copy[g] = (tail | !range) ? -1 : step_code((int)lbase + s, n, log2B, seed);
     }
-    // wave-combine when the whole wave ended in one list
-    int l0 = __shfl(l, 0);
-    if (__ballot(l != l0) == 0) {
-      acc = wave_sum(acc);
-      tails = wave_sum(tails);
-      if (lane == 0) {
-        if (acc) atomicAdd(&lsum[l], acc);
-        if (tails) atomicAdd(&ltails[l], tails);
-      }
-    } else {
+  }
+  // wave-combine when the whole wave ended in one list
+  const int l0 = __shfl(l, 0);
+  if (__ballot(l != l0) == 0) {
+    acc = wave_sum(acc);
+    tails = wave_sum(tails);
+    if (lane == 0) {
       if (acc) atomicAdd(&lsum[l], acc);
       if (tails) atomicAdd(&ltails[l], tails);
     }
+  } else {
+    if (acc) atomicAdd(&lsum[l], acc);
+    if (tails) atomicAdd(&ltails[l], tails);
   }
 }
 
@@ -276,6 +324,7 @@ struct WalkArgs {
   int cap_prev;  // cut points the level below could create
   int kbits;     // level 0 packed form: bits of the in-sublist offset
   uint32_t seed;
+  int if_near;   // only if the successors are local (the recorded walk took the others)
 };
 
 // kPacked (level 0): the successors are read from a.work, a copy made by the
@@ -297,10 +346,15 @@ __global__ void __launch_bounds__(1024) lr_walk(WalkArgs a) {
   // the final scatter's splitter-rank gathers hit in L2.  The plan is sized
   // for the smaller spacing.
   const bool far =
-      kLevel0 && a.log2B_far > 0 && 2ull * ctl->near <= (unsigned long long)N;
+      kLevel0 && a.log2B_far > 0 && far_chosen(ctl, N);
+  if (kLevel0 && far && a.if_near) return;
   const int log2B = far ? a.log2B_far : a.log2B;
   const int kbits = far ? a.kbits_far : a.kbits;
   const int max_walk = far ? a.max_walk_far : a.max_walk;
+  // One list, packed: the work array holds step codes, made for the far spacing
+  // when there is one.
+  constexpr bool kCoded = kLevel0 && !kBatched && kPacked;
+  const bool coded = a.log2B_far == 0 || far;
   const int r = (int)(((int64_t)N + (1 << log2B) - 1) >> log2B);
   const int head_base = kLevel0 ? 0 : ctl->lv[a.level - 1].r;
   if (blockIdx.x == 0 && threadIdx.x == 0) ctl->lv[a.level].r = r;
@@ -442,7 +496,18 @@ __global__ void __launch_bounds__(1024) lr_walk(WalkArgs a) {
     for (int rep = 0; rep < kWalkBurst && sid >= 0; ++rep) {
       int y, w;
       bool tail;
-      if (kLevel0) {
+      bool stop = false;  // y is a static splitter
+      if (kCoded) {
+        const int s = a.work[x];
+        tail = s == -1;
+        y = s & INT32_MAX;
+        if (!tail && y >= N) {  // a state: a malformed input led here twice
+          errbits |= kErrRange;
+          tail = true;
+        }
+        w = 1;
+        stop = coded ? s < 0 : is_static(y, N, log2B, seed);
+      } else if (kLevel0) {
         const int s = kPacked ? a.work[x] : a.succ0[x];
         const int xl = (int)(x - base);
         tail = (s == -1) | (s == xl);
@@ -462,13 +527,14 @@ __global__ void __launch_bounds__(1024) lr_walk(WalkArgs a) {
         y = in.x;
         w = in.y;
       }
+      if (!kCoded) stop = is_static(y, N, log2B, seed);
       if (kLevel0 && kPacked) a.work[x] = (sid << kbits) | k;
       else store_pair(&a.state[x], sid, k);
       k += w;
       if (tail) {
         store_pair(&a.link_out[sid], -1, k);
         sid = -1;
-      } else if (is_static(y, N, log2B, seed)) {
+      } else if (stop) {
         store_pair(&a.link_out[sid], y >> log2B, k);
         sid = -1;
       } else if (++steps >= max_walk) {
@@ -491,6 +557,371 @@ __global__ void __launch_bounds__(1024) lr_walk(WalkArgs a) {
     }
   }
   if (errbits) atomicOr(&ctl->err, errbits);
+}
+
+// ------------------------------------------------------ recorded walk
+// Level 0 where in-place states do not pay.  The walk (lr_walk_rec) only reads
+// the successors and records the nodes it meets, in strips of kStrip
+// consecutive nodes of one sublist; lr_bin deals the recorded nodes, with
+// their ranks, to bins of kBinNodes consecutive ids, and lr_place puts a bin's
+// ranks in order in LDS and writes them.  Writing the state over each successor
+// (lr_walk) makes every step a write of a 32-byte sector besides the read of a
+// 128-byte line, and its random reads alone run 1.65 times as fast (2^26 random
+// nodes: 1.21 ms against 1.99); what is recorded moves in whole lines.
+//
+// A batch whose lists each fit an XCD's L2 gains more.  Workgroup ids are dealt
+// round-robin over the XCDs, and each XCD takes chunks of consecutive splitter
+// blocks (and the heads of the lists that start in them) from its own eighth
+// of the nodes in order, so the lists its lanes walk at one time are a few
+// neighbours, which stay in its L2.  Nothing but the hit rate depends on the
+// mapping.  256 lists of 2^18 nodes, following successors: 69 G nodes/s over
+// all XCDs, 220 G/s list by list.
+//
+// Strips are handed out in slabs of kSlab per wave, from one counter; slab_of
+// lists the slabs of each XCD in the order they were taken.
+// First list of every chunk of kWalkChunk splitter blocks (a batch).
+__global__ void __launch_bounds__(256) lr_rec_chunks(const int64_t* __restrict__ off, int L,
+                                                     int nchunks, int log2_chunk,
+                                                     int32_t* __restrict__ chunk_list) {
+  for (int c = blockIdx.x * 256 + threadIdx.x; c <= nchunks; c += gridDim.x * 256) {
+    int lo = 0, hi = L;  // entries of off[0..L) below the chunk's first node
+    const int64_t target = (int64_t)c << log2_chunk;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (off[mid] < target) lo = mid + 1;
+      else hi = mid;
+    }
+    chunk_list[c] = c == nchunks ? L : lo;
+  }
+}
+
+template <bool kBatched>
+__global__ void __launch_bounds__(256) lr_walk_rec(WalkArgs a, RecArgs rec) {
+  LrCtl* ctl = a.ctl;
+  const int N = ctl->lv[0].n;
+  if (!kBatched && rec.if_far && !far_chosen(ctl, N)) return;
+  const int log2B = rec.log2B;
+  const uint32_t seed = a.seed;
+  const int r = (int)(((int64_t)N + (1 << log2B) - 1) >> log2B);
+  if (blockIdx.x == 0 && threadIdx.x == 0) ctl->lv[0].r = r;
+  int* dyn = &ctl->lv[0].dyn;
+  const int nchunks = (r + kWalkChunk - 1) / kWalkChunk;
+  const int home = blockIdx.x % kXcds;
+  // the wave's chunks: every waves-th of its XCD's range
+  const int waves = gridDim.x / kXcds * (256 / kWave);
+  const int range_hi = (int)((int64_t)nchunks * (home + 1) / kXcds);
+  int chunk = (int)((int64_t)nchunks * home / kXcds) + blockIdx.x / kXcds * (256 / kWave) +
+              threadIdx.x / kWave;
+  chunk = __builtin_amdgcn_readfirstlane(chunk);
+  // the current chunk: static splitters first .. first + statics - 1, then the
+  // heads of the lists la .. la + heads - 1; next of them to be taken
+  int first = 0, statics = 0, la = 0, heads = 0, next = 0;
+  int slab = -1, cursor = kSlab;    // the wave's slab and the strips used of it
+  int ahead_la = 0, ahead_lb = 0;   // lists of the next chunk, read early
+  if (kBatched && chunk < range_hi) {
+    ahead_la = rec.chunk_list[chunk];
+    ahead_lb = rec.chunk_list[chunk + 1];
+  }
+
+  int sid = -1, x = 0, k = 0;
+  int errbits = 0;
+  for (;;) {
+    for (;;) {
+      const bool idle = sid < 0;
+      const uint64_t idle_mask = __ballot(idle);
+      if (idle_mask == 0) break;
+      if (next >= statics + heads) {  // the chunk is used up
+        if (chunk >= range_hi) break;
+        first = chunk * kWalkChunk;
+        statics = min(kWalkChunk, r - first);
+        next = 0;
+        if (kBatched) {
+          la = __builtin_amdgcn_readfirstlane(ahead_la);
+          heads = __builtin_amdgcn_readfirstlane(ahead_lb) - la;
+        } else {
+          heads = chunk == 0 ? 1 : 0;
+        }
+        chunk += waves;
+        if (kBatched && chunk < range_hi) {
+          ahead_la = rec.chunk_list[chunk];
+          ahead_lb = rec.chunk_list[chunk + 1];
+        }
+      }
+      const int item = next + lanes_below(idle_mask);
+      const int end = statics + heads;
+      next = min(end, next + (int)__popcll(idle_mask));
+      if (idle && item < statics) {
+        const int block = first + item;
+        const int start = block << log2B;
+        x = start + (int)splitter_offset((uint32_t)block, seed,
+                                         (uint32_t)min(1 << log2B, N - start));
+        sid = block;
+        k = 0;
+      } else if (idle && item < end) {  // the virtual splitter at a list's head
+        const int l = la + item - statics;
+        const int64_t base = kBatched ? a.off[l] : 0;
+        const int size = kBatched ? (int)(a.off[l + 1] - base) : N;
+        if (size == 0) {
+          store_pair(&a.link_out[r + l], -1, 0);
+        } else {
+          const unsigned long long tri =
+              (unsigned long long)size * (unsigned long long)(size - 1) / 2ull;
+          const long long h = (long long)(tri - a.lsum[l]);
+          if (a.ltails[l] != 1 || h < 0 || h >= size) {
+            atomicOr(&a.lerr[l], a.ltails[l] != 1 ? kErrTails : kErrHead);
+            store_pair(&a.link_out[r + l], -1, 0);
+          } else if (is_static((int)(base + h), N, log2B, seed)) {
+            store_pair(&a.link_out[r + l], (int)(base + h) >> log2B, 0);
+          } else {
+            x = (int)(base + h);
+            sid = r + l;
+            k = 0;
+          }
+        }
+      }
+    }
+    // kStrip steps, kept in registers
+    const uint64_t walking = __ballot(sid >= 0);
+    if (walking == 0) break;  // nothing left to take either
+    const bool walks = sid >= 0;
+    const int k0 = k;
+    bool over = !walks;
+    int node[kStrip];
+#pragma unroll
+    for (int t = 0; t < kStrip; ++t) {
+      node[t] = over ? -1 : x;
+      if (!over) {
+        x = a.work[x];
+        ++k;
+        over = x < 0;
+      }
+    }
+    if (walks && over)  // at a tail or the next static splitter
+      store_pair(&a.link_out[sid], x == -1 ? -1 : (x & INT32_MAX) >> log2B, k);
+    // the strips of the walking lanes; those past the slab's end go to a new one
+    const int count = (int)__popcll(walking);
+    const int mine = cursor + lanes_below(walking);
+    int strip = mine < kSlab ? slab * kSlab + mine : -1;
+    if (cursor + count > kSlab) {
+      int fresh = 0;
+      if (lane_id() == 0) {
+        if (slab >= 0) rec.used[slab] = kSlab;
+        fresh = atomicAdd(&rec.ctl->slabs, 1);
+        if (fresh < rec.max_slabs)
+          rec.slab_of[home * rec.max_slabs + atomicAdd(&rec.ctl->listed[home], 1)] = fresh;
+      }
+      fresh = __builtin_amdgcn_readfirstlane(fresh);
+      slab = fresh < rec.max_slabs ? fresh : -1;
+      if (strip < 0 && slab >= 0) strip = slab * kSlab + (mine - kSlab);
+      cursor -= kSlab;
+      if (slab < 0) cursor = kSlab - count;  // no slab: only a malformed input gets here
+    }
+    cursor += count;
+    if (walks) {
+      if (strip >= 0) {
+#pragma unroll
+        for (int t = 0; t < kStrip / 4; ++t)
+          rec.strips[(int64_t)strip * (kStrip / 4) + t] =
+              make_int4(node[4 * t], node[4 * t + 1], node[4 * t + 2], node[4 * t + 3]);
+        rec.head[strip] = make_int2(sid, k0);
+      } else {
+        errbits |= kErrOverflow;
+        if (!over) store_pair(&a.link_out[sid], -1, k);
+        over = true;
+      }
+      if (!over && k >= a.max_walk) {  // cut: the node reached becomes a splitter
+        const int t = atomicAdd(dyn, 1);
+        if (t >= a.cap) {
+          errbits |= kErrOverflow;
+          store_pair(&a.link_out[sid], -1, k);
+          over = true;
+        } else {
+          const int nid = r + a.L + t;
+          store_pair(&a.link_out[sid], nid, k);
+          sid = nid;
+          k = 0;
+        }
+      }
+      if (over) sid = -1;
+    }
+  }
+  if (lane_id() == 0 && slab >= 0) rec.used[slab] = cursor;
+  if (errbits) atomicOr(&ctl->err, errbits);
+}
+
+// Deals the recorded nodes to bins: entry {node, rank} of every node, where
+// rank = rank of the strip's sublist + place in it.  A bin's region of `ent`
+// holds one entry per node of the bin, which a valid input fills exactly.  A
+// tile of kTileSlabs slabs, a strip a thread, is sorted by bin in LDS, so that
+// its entries reach a bin as one run.  kTileBins bins from the tile's lowest on
+// are sorted; entries past them (slabs of distant lists in one tile) go to
+// their bins one by one.
+template <bool kBatched, bool kToTail>
+__global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
+                                                       const int32_t* __restrict__ srank,
+                                                       const int64_t* __restrict__ off, int L,
+                                                       int cap_here, LrCtl* ctl) {
+  __shared__ uint2 ent[kTileThreads * kStrip];
+  __shared__ int hist[kTileBins], start[kTileBins], to[kTileBins];
+  __shared__ int wsum[kTileThreads / kWave];
+  __shared__ int low, total;
+  const int N = ctl->lv[0].n;
+  if (!kBatched && rec.if_far && !far_chosen(ctl, N)) return;
+  const int Nup = level_nodes(ctl, 1, L, cap_here);
+  const int tid = threadIdx.x;
+  const int home = blockIdx.x % kXcds;
+  const int listed = rec.ctl->listed[home];
+  bool bad = false;
+  // the thread's strip of the tile at i0, read one tile ahead
+  int ahead[kStrip];
+  int2 ahead_head = make_int2(-1, 0);
+  const auto fetch = [&](int i0) {
+    ahead_head = make_int2(-1, 0);
+    const int i = i0 + tid / kSlab;
+    if (i < listed) {
+      const int slab = rec.slab_of[home * rec.max_slabs + i];
+      if (tid % kSlab < rec.used[slab]) {
+        const int64_t strip = (int64_t)slab * kSlab + tid % kSlab;
+        ahead_head = rec.head[strip];
+#pragma unroll
+        for (int t = 0; t < kStrip / 4; ++t) {
+          const int4 v = rec.strips[strip * (kStrip / 4) + t];
+          ahead[4 * t] = v.x;
+          ahead[4 * t + 1] = v.y;
+          ahead[4 * t + 2] = v.z;
+          ahead[4 * t + 3] = v.w;
+        }
+      }
+    }
+  };
+  const int step = gridDim.x / kXcds * kTileSlabs;
+  const int begin = blockIdx.x / kXcds * kTileSlabs;
+  if (begin < listed) fetch(begin);
+  for (int i0 = begin; i0 < listed; i0 += step) {
+    int node[kStrip], pos[kStrip];
+    const int2 h = ahead_head;
+    const bool have = h.x >= 0;
+    const bool known = (unsigned)h.x < (unsigned)Nup;
+    bad |= have && !known;
+#pragma unroll
+    for (int t = 0; t < kStrip; ++t) node[t] = known ? ahead[t] : -1;
+    int value = known ? srank[h.x] + h.y : 0;
+    if (kToTail && known) {
+      int size = N;
+      if (kBatched) {
+        const int l = find_instance(off, L, node[0]);
+        size = (int)(off[l + 1] - off[l]);
+      }
+      value = size - 1 - value;
+    }
+    if (i0 + step < listed) fetch(i0 + step);
+    if (tid == 0) low = INT32_MAX;
+    for (int b = tid; b < kTileBins; b += kTileThreads) hist[b] = 0;
+    __syncthreads();
+    int least = INT32_MAX;
+#pragma unroll
+    for (int t = 0; t < kStrip; ++t)
+      if (node[t] >= 0) least = min(least, node[t] >> kBinShift);
+    least = wave_min(least);
+    if (lane_id() == 0) atomicMin(&low, least);
+    __syncthreads();
+    const int lo = low;
+#pragma unroll
+    for (int t = 0; t < kStrip; ++t) {
+      pos[t] = -1;
+      if (node[t] >= 0) {
+        const int b = (node[t] >> kBinShift) - lo;
+        if (b < kTileBins) {
+          pos[t] = atomicAdd(&hist[b], 1);
+        } else {
+          const int at = atomicAdd(&rec.cursor[b + lo], 1);
+          if (at < kBinNodes)
+            rec.ent[((int64_t)(b + lo) << kBinShift) + at] =
+                make_uint2((unsigned)node[t], (unsigned)(kToTail ? value - t : value + t));
+        }
+      }
+    }
+    __syncthreads();
+    // exclusive prefix of the counts, kTileBins / kTileThreads bins a thread
+    constexpr int kPer = kTileBins / kTileThreads;
+    int cnt[kPer], sum = 0;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      cnt[q] = hist[tid * kPer + q];
+      sum += cnt[q];
+    }
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int u = __shfl_up(incl, o, kWave);
+      if (lane_id() >= o) incl += u;
+    }
+    if (lane_id() == kWave - 1) wsum[tid / kWave] = incl;
+    __syncthreads();
+    int excl = incl - sum;
+    for (int w = 0; w < tid / kWave; ++w) excl += wsum[w];
+    if (tid == kTileThreads - 1) total = excl + sum;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int b = tid * kPer + q;
+      start[b] = excl;
+      excl += cnt[q];
+    }
+    // (lanes on consecutive cursors)
+    for (int b = tid; b < kTileBins; b += kTileThreads) {
+      const int c = hist[b];
+      if (c) to[b] = atomicAdd(&rec.cursor[lo + b], c);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < kStrip; ++t)
+      if (pos[t] >= 0)
+        ent[start[(node[t] >> kBinShift) - lo] + pos[t]] =
+            make_uint2((unsigned)node[t], (unsigned)(kToTail ? value - t : value + t));
+    __syncthreads();
+    for (int e = tid; e < total; e += kTileThreads) {
+      const uint2 v = ent[e];
+      const int b = (int)(v.x >> kBinShift) - lo;
+      const int at = to[b] + e - start[b];
+      if (at < kBinNodes) rec.ent[((int64_t)(lo + b) << kBinShift) + at] = v;
+    }
+    __syncthreads();  // hist, start, to and ent are reused by the next tile
+  }
+  if (__ballot(bad) && lane_id() == 0) atomicOr(&ctl->err, kErrTotal);
+}
+
+// A bin's ranks put in order in LDS and written.
+__global__ void __launch_bounds__(kTileThreads) lr_place(RecArgs rec, int32_t* __restrict__ rank,
+                                                         LrCtl* ctl) {
+  __shared__ int32_t out[kBinNodes];
+  const int N = ctl->lv[0].n;
+  if (rec.if_far && !far_chosen(ctl, N)) return;
+  const int nbins = (int)(((int64_t)N + kBinNodes - 1) >> kBinShift);
+  for (int b = blockIdx.x; b < nbins; b += gridDim.x) {
+    const int64_t v0 = (int64_t)b << kBinShift;
+    const int size = (int)min<int64_t>(kBinNodes, N - v0);
+    const int filled = rec.cursor[b];
+    if (filled != size && threadIdx.x == 0) atomicOr(&ctl->err, kErrTotal);
+    const uint2* e = rec.ent + v0;
+    const int have = min(filled, kBinNodes);
+    constexpr int kIn = 8;  // entries in flight per thread
+    for (int q0 = threadIdx.x; q0 < have; q0 += kIn * kTileThreads) {
+      uint2 v[kIn];
+#pragma unroll
+      for (int u = 0; u < kIn; ++u) {
+        const int q = q0 + u * kTileThreads;
+        if (q < have) v[u] = e[q];
+      }
+#pragma unroll
+      for (int u = 0; u < kIn; ++u) {
+        const int q = q0 + u * kTileThreads;
+        if (q < have) out[v[u].x & (kBinNodes - 1)] = (int)v[u].y;
+      }
+    }
+    __syncthreads();
+    for (int q = threadIdx.x; q < size; q += kTileThreads) rank[v0 + q] = out[q];
+    __syncthreads();
+  }
 }
 
 // ------------------------------------------------- caller-chosen splitters
@@ -1071,11 +1502,11 @@ __global__ void __launch_bounds__(256) lr_expand0(const int2* __restrict__ state
                                                   int32_t* rank,
                                                   const int64_t* __restrict__ off, LrCtl* ctl,
                                                   int L, int cap_here, int kbits_near,
-                                                  int kbits_far) {
+                                                  int kbits_far, int if_near) {
   const int N = ctl->lv[0].n;
+  if (if_near && far_chosen(ctl, N)) return;
   // the walk's choice of packing (see lr_walk), from the same count
-  const int kbits = kbits_far > 0 && 2ull * ctl->near <= (unsigned long long)N ? kbits_far
-                                                                                 : kbits_near;
+  const int kbits = kbits_far > 0 && far_chosen(ctl, N) ? kbits_far : kbits_near;
   const int Nup = level_nodes(ctl, 1, L, cap_here);
   int bad = 0;
   // kExpandPer nodes per thread per pass, loads first: the splitter-rank
@@ -1541,6 +1972,14 @@ inline int grid_for(int64_t n, int block, int cap) {
   return (int)g;
 }
 
+// Workgroups of the batched head find: four chunks a wave, but no fewer than
+// two workgroups per CU while every wave has a chunk.
+inline int headfind_grid(int64_t n, int cap) {
+  const int64_t per = kHfChunk * kWave * (256 / kWave);  // nodes of a workgroup's chunks
+  const int64_t least = std::min<int64_t>(n / per + 1, 512);
+  return (int)std::min<int64_t>(cap, std::max(least, n / (4 * per) + 1));
+}
+
 struct Plan {
   int algo = PJ_ALGO_RULING_SET;
   bool small = false;      // every list ranked in LDS
@@ -1557,6 +1996,8 @@ struct Plan {
   int log2B_far = 0;       // > 0: level 0 may pick this on the device (see lr_walk),
   int kbits_far = 0;       // with these offset bits (packed form)
   int max_walk_far = 0;    // and this cut length
+  int rec_grid = 0, rec_log2B = 0, rec_chunks = 0, rec_bins = 0;
+  int max_slabs = 0;       // > 0: level 0 records its walks (see lr_walk_rec)
   int64_t chosen = 0;      // > 0: level 0 uses this many caller-chosen splitters
 };
 
@@ -1671,6 +2112,51 @@ void add_far_spacing(Plan& p, int64_t n0, int64_t L, int far, int max_walk) {
   }
 }
 
+// The plan with level 0 recorded (see lr_walk_rec), where that suits the input.
+//   * one list, from 11 M nodes on (9 M: 488 us in place, 524 recorded; 12 M: 600
+//     and 567; 2^26: 3140 and 2340), up to the nodes that kTileBins bins hold,
+//     and only if the head-find pass finds it not local;
+//   * a batch of 2^20 nodes or more (1.4 M: 194 and 176 us) whose lists stay
+//     near one L2.
+// Strips are 16 nodes long, so sublists are 32 nodes long at least (8.4 M nodes
+// in 200 lists: 387 us with 8, 334 with 32), and with 32 a batch walks as fast
+// as with 64 for fewer of its nodes in flight.  Few lanes walk at one time (two
+// workgroups a CU for one list, whose reads run at 55 G/s from 128 lanes a CU
+// on; one for a batch, which holds the lists walked at one time to an L2).
+constexpr int64_t kRecordList = int64_t(11) << 20;
+constexpr int64_t kRecordBatch = int64_t(1) << 20;
+constexpr int64_t kRecordLongest = int64_t(1) << 21;
+constexpr int kRecordSpacing = 32;
+
+bool recorded_plan(const Plan& in_place, int64_t n0, int64_t L, int64_t max_size, bool single,
+                   bool weighted, const pj_opts& o, bool spacing_given, Plan* out) {
+  const Plan& q = in_place;
+  if (weighted || q.algo != PJ_ALGO_RULING_SET || q.small || q.chosen > 0 ||
+      o.level0_state == PJ_STATE_SEPARATE || o.max_walk % kStrip != 0)
+    return false;
+  if (single ? !q.packed || n0 < kRecordList || n0 > (int64_t)kTileBins * kBinNodes
+             : n0 < kRecordBatch || max_size > kRecordLongest)
+    return false;
+  Plan p = in_place;
+  if (!single && !spacing_given && o.spacing < kRecordSpacing) {
+    pj_opts wide = o;
+    wide.spacing = kRecordSpacing;
+    p = make_plan(n0, L, max_size, wide, weighted, 0);
+  }
+  if (p.log2B_far > 0) p.log2B_far = std::max(p.log2B_far, ilog2(kRecordSpacing));
+  p.rec_grid = device_info().cus * (single ? 2 : 1) / kXcds * kXcds;
+  p.rec_log2B = p.log2B_far > 0 ? p.log2B_far : p.log2B[0];
+  // every sublist piece ends in one partly filled strip at most, and every
+  // wave in one partly filled slab
+  const int64_t r = (n0 + (1ll << p.rec_log2B) - 1) >> p.rec_log2B;
+  const int64_t strips = n0 / kStrip + r + L + n0 / o.max_walk + 64;
+  p.max_slabs = (int)(strips / kSlab + 1 + p.rec_grid * (256 / kWave));
+  p.rec_chunks = (int)((r + kWalkChunk - 1) / kWalkChunk);
+  p.rec_bins = (int)((n0 + kBinNodes - 1) >> kBinShift);
+  *out = p;
+  return true;
+}
+
 struct Buffers {
   LrCtl* ctl = nullptr;
   unsigned long long* lsum = nullptr;
@@ -1686,6 +2172,7 @@ struct Buffers {
   int32_t* chk = nullptr;
   int32_t* status_tmp = nullptr;
   int32_t* ssucc = nullptr;           // successors of caller-chosen splitters
+  RecArgs rec = {};
   int32_t* sub_max = nullptr;         // stats: longest level-0 sublist
 };
 
@@ -1711,9 +2198,23 @@ size_t carve(const Plan& p, int64_t L, bool single, bool validate, bool want_sta
   }
   if (p.small) return bytes;
   take(b->sub_max, 1);
+  if (p.max_slabs > 0) {
+    const size_t slabs = (size_t)p.max_slabs;
+    take(b->rec.ctl, 1);
+    take(b->rec.strips, slabs * kSlab * kStrip / 4);
+    take(b->rec.head, slabs * kSlab);
+    take(b->rec.slab_of, slabs * kXcds);
+    take(b->rec.used, slabs);
+    if (!single) take(b->rec.chunk_list, (size_t)p.rec_chunks + 1);
+    take(b->rec.cursor, (size_t)p.rec_bins);
+    take(b->rec.ent, (size_t)p.rec_bins * kBinNodes);
+    b->rec.max_slabs = p.max_slabs;
+    b->rec.log2B = p.rec_log2B;
+    b->rec.if_far = p.log2B_far > 0 ? 1 : 0;
+  }
   if (p.chosen > 0) take(b->ssucc, (size_t)p.chosen);
   for (int l = 0; l < p.levels; ++l) {
-    if (!(l == 0 && p.packed)) take(b->state[l], (size_t)p.bound[l]);
+    if (l > 0 || !(p.packed || (p.max_slabs > 0 && p.log2B_far == 0))) take(b->state[l], (size_t)p.bound[l]);
     take(b->link[l + 1], (size_t)p.bound[l + 1]);
     take(b->srank[l + 1], (size_t)p.bound[l + 1]);
   }
@@ -1804,12 +2305,14 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
     return PJ_EINVAL;
 
   int far_spacing = 0;
+  bool spacing_given = false;
   {  // ruling-set parameters left at zero come from the tune cache, if tuned
     pj_opts raw;
     pj_opts_init(&raw);
     if (user) raw = *user;
     apply_tuned(raw, n0, L);
     far_spacing = level0_spacing(raw.spacing, n0, single, &o.spacing);
+    spacing_given = raw.spacing > 0;
     o.spacing_up = raw.spacing_up > 0 ? raw.spacing_up : o.spacing_up;
     o.cutoff = raw.cutoff > 0 ? std::min(std::max(raw.cutoff, 64), 16384) : o.cutoff;
     o.max_walk = raw.max_walk > 0 ? std::max(raw.max_walk, 16) : o.max_walk;
@@ -1819,14 +2322,25 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
   if (chosen > 0 && !p.packed) return PJ_EINVAL;  // too many splitters for the packed state
   add_far_spacing(p, n0, L, far_spacing, o.max_walk);
   Buffers b;
-  const size_t need = carve(p, L, single, o.validate != 0, want_status, nullptr, &b);
+  size_t need = carve(p, L, single, o.validate != 0, want_status, nullptr, &b);
   if (p.small && !weight && n0 > 0 && !o.validate && !(user && user->stats)) {
     // one kernel, which also writes the statuses: no workspace, no init
     if (o.workspace && o.workspace_bytes < need) return PJ_EINVAL;
     return launch_lds(succ, n0, max_size, d_off, L, rank, o.to_tail, nullptr, o.d_status, stream);
   }
   Workspace ws;
-  PJ_TRY(workspace_acquire(ws, need, &o, stream));
+  // the recorded walk where its strips fit the caller's workspace or the pool
+  bool recorded = false;
+  Plan pr;
+  if (recorded_plan(p, n0, L, max_size, single, weight != nullptr, o, spacing_given, &pr)) {
+    const size_t more = carve(pr, L, single, o.validate != 0, want_status, nullptr, &b);
+    if (!o.workspace || o.workspace_bytes >= more)
+      recorded = workspace_acquire(ws, more, &o, stream) == PJ_OK;
+    if (!recorded) (void)hipGetLastError();  // no memory for it: in place
+  }
+  if (recorded) p = pr;
+  else PJ_TRY(workspace_acquire(ws, need, &o, stream));
+  b = Buffers{};
   carve(p, L, single, o.validate != 0, want_status, &ws, &b);
   const int64_t* off = single ? b.off1 : d_off;
   int32_t* status = o.d_status ? o.d_status : b.status_tmp;
@@ -1842,7 +2356,8 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
   const int gcap = cus * 16;
 
   hipLaunchKernelGGL(lr_init, dim3(grid_for(std::max<int64_t>(L, 64), 256, 1024)), dim3(256), 0,
-                     stream, b.ctl, n, b.lsum, b.ltails, b.lerr, Li, b.off1);
+                     stream, b.ctl, n, b.lsum, b.ltails, b.lerr, Li, b.off1,
+                     b.rec, recorded ? p.rec_bins : 0);
   PJ_HIP(hipGetLastError());
   tm.mark("init");
 
@@ -1850,13 +2365,13 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
   if (n0 > 0 && p.algo == PJ_ALGO_WYLLIE) {
     if (o.validate || o.d_status) {
       if (single)
-        hipLaunchKernelGGL(lr_headfind_single<false>, dim3(grid_for(n / 4 + 1, 256, 1024)),
-                           dim3(256), 0, stream, succ, n, nullptr, b.lsum, b.ltails, b.lerr,
+        hipLaunchKernelGGL(lr_headfind_single<kNoCopy>, dim3(grid_for(n / 4 + 1, 256, 1024)),
+                           dim3(256), 0, stream, succ, n, nullptr, 0, 0u, b.lsum, b.ltails, b.lerr,
                            nullptr);
       else
-        hipLaunchKernelGGL(lr_headfind_batched<false>,
-                           dim3(grid_for(n / (kHfChunk * 4) + 1, 256, gcap)), dim3(256), 0,
-                           stream, succ, off, Li, n, nullptr, b.lsum, b.ltails, b.lerr);
+        hipLaunchKernelGGL(lr_headfind_batched<kNoCopy>,
+                           dim3(headfind_grid(n, gcap)), dim3(256), 0,
+                           stream, succ, off, Li, n, nullptr, 0, 0u, b.lsum, b.ltails, b.lerr);
       check_tails = true;
       tm.mark("headfind");
     }
@@ -1899,16 +2414,24 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
   } else if (n0 > 0) {
     // level 0 head find (and, in the packed form, the successor copy, which
     // in place is already there)
-    int32_t* copy = p.packed ? rank : nullptr;
-    const bool copy_succ = p.packed && (const void*)succ != (const void*)rank;
+    int32_t* copy = p.packed || recorded ? rank : nullptr;
+    const bool copy_succ = copy && (const void*)succ != (const void*)rank;
     if (single) {
-      auto k = copy_succ ? lr_headfind_single<true> : lr_headfind_single<false>;
-      hipLaunchKernelGGL(k, dim3(grid_for(n / 4 + 1, 256, 1024)), dim3(256), 0, stream, succ, n,
-                         copy, b.lsum, b.ltails, b.lerr, &b.ctl->near);
+      auto k = copy && p.chosen == 0 ? lr_headfind_single<kCodedCopy>
+               : copy_succ ? lr_headfind_single<kPlainCopy> : lr_headfind_single<kNoCopy>;
+      // (a workgroup ends in up to four atomics on the same words: 2^20 nodes
+      // take 18.9 us with 1024 workgroups and 11.5 us with 256)
+      hipLaunchKernelGGL(k, dim3(grid_for(n / 4 + 1, 256, n <= 1 << 22 ? 256 : 1024)), dim3(256),
+                         0, stream, succ, n, copy,
+                         p.log2B_far > 0 ? p.log2B_far : p.log2B[0], level_seed(o.seed, 0),
+                         b.lsum, b.ltails, b.lerr, &b.ctl->near);
     } else {
-      auto k = copy_succ ? lr_headfind_batched<true> : lr_headfind_batched<false>;
-      hipLaunchKernelGGL(k, dim3(grid_for(n / (kHfChunk * 4) + 1, 256, gcap)), dim3(256), 0,
-                         stream, succ, off, Li, n, copy, b.lsum, b.ltails, b.lerr);
+      auto k = recorded ? lr_headfind_batched<kCodedCopy>
+                        : copy_succ ? lr_headfind_batched<kPlainCopy>
+                                    : lr_headfind_batched<kNoCopy>;
+      hipLaunchKernelGGL(k, dim3(headfind_grid(n, gcap)), dim3(256), 0,
+                         stream, succ, off, Li, n, copy, p.log2B[0], level_seed(o.seed, 0), b.lsum,
+                         b.ltails, b.lerr);
     }
     PJ_HIP(hipGetLastError());
     if (p.chosen > 0) {
@@ -1952,6 +2475,21 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
       if (lv > 0) kfn = lr_walk<false, false, false>;
       else if (single) kfn = p.packed ? lr_walk<true, false, true> : lr_walk<true, false, false>;
       else kfn = p.packed ? lr_walk<true, true, true> : lr_walk<true, true, false>;
+      if (lv == 0 && recorded) {
+        WalkArgs ra = a;
+        ra.max_walk = o.max_walk;
+        if (!single)
+          hipLaunchKernelGGL(lr_rec_chunks, dim3(grid_for(p.rec_chunks + 1, 256, gcap)), dim3(256),
+                             0, stream, off, Li, p.rec_chunks, p.rec_log2B + 6, b.rec.chunk_list);
+        hipLaunchKernelGGL(single ? lr_walk_rec<false> : lr_walk_rec<true>, dim3(p.rec_grid),
+                           dim3(256), 0, stream, ra, b.rec);
+        PJ_HIP(hipGetLastError());
+        if (!b.rec.if_far) {
+          tm.mark("walk0");
+          continue;
+        }
+        a.if_near = 1;
+      }
       const bool marked = lv == 0 && p.chosen > 0;
       const int64_t items =
           marked ? p.chosen + 1 : ((p.bound[lv] + (1ll << a.log2B) - 1) >> a.log2B) + L;
@@ -2000,7 +2538,8 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
     }
     tm.mark("expand_up");
     const int g0 = grid_for(n, 256, gcap);
-    void (*ex0)(const int2*, const int32_t*, int32_t*, const int64_t*, LrCtl*, int, int, int, int);
+    void (*ex0)(const int2*, const int32_t*, int32_t*, const int64_t*, LrCtl*, int, int, int, int,
+                int);
     if (single) {
       if (o.to_tail) ex0 = p.packed ? lr_expand0<false, true, true> : lr_expand0<false, true, false>;
       else ex0 = p.packed ? lr_expand0<false, false, true> : lr_expand0<false, false, false>;
@@ -2008,8 +2547,21 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
       if (o.to_tail) ex0 = p.packed ? lr_expand0<true, true, true> : lr_expand0<true, true, false>;
       else ex0 = p.packed ? lr_expand0<true, false, true> : lr_expand0<true, false, false>;
     }
-    hipLaunchKernelGGL(ex0, dim3(g0), dim3(256), 0, stream, b.state[0], b.srank[1], rank, off,
-                       b.ctl, Li, p.cap[0], p.kbits, single ? p.kbits_far : 0);
+    if (recorded) {
+      const auto bin = single ? (o.to_tail ? lr_bin<false, true> : lr_bin<false, false>)
+                              : (o.to_tail ? lr_bin<true, true> : lr_bin<true, false>);
+      const int cus = device_info().cus;
+      hipLaunchKernelGGL(bin, dim3(cus / kXcds * kXcds), dim3(kTileThreads), 0, stream, b.rec,
+                         (const int32_t*)b.srank[1], off, Li, p.cap[0], b.ctl);
+      tm.mark("bin");
+      hipLaunchKernelGGL(lr_place, dim3(std::min(p.rec_bins, cus)), dim3(kTileThreads), 0, stream,
+                         b.rec, rank, b.ctl);
+      tm.mark("place");
+    }
+    if (!recorded || b.rec.if_far)
+      hipLaunchKernelGGL(ex0, dim3(g0), dim3(256), 0, stream, b.state[0], b.srank[1], rank, off,
+                         b.ctl, Li, p.cap[0], p.kbits, single ? p.kbits_far : 0,
+                         recorded ? 1 : 0);
     PJ_HIP(hipGetLastError());
     tm.mark("expand0");
   }
@@ -2130,6 +2682,25 @@ size_t list_rank_workspace(int64_t n0, int64_t L, const pj_opts* user, bool sing
   Plan p = make_plan(n0, L, n0, o, weighted, chosen);
   Buffers b;
   return carve(p, L, single, o.validate != 0, o.validate && !o.d_status, nullptr, &b);
+}
+
+// Workspace with which a batch of these sizes is recorded, if it is; else as
+// list_rank_workspace.
+size_t list_rank_graph_workspace(int64_t n0, int64_t L, int64_t max_size, const pj_opts* user) {
+  pj_opts raw;
+  pj_opts_init(&raw);
+  if (user) raw = *user;
+  apply_tuned(raw, n0, L);
+  const bool spacing_given = raw.spacing > 0;
+  (void)level0_spacing(raw.spacing, n0, false, &raw.spacing);
+  const pj_opts o = resolved_opts(&raw);
+  Plan p = make_plan(n0, L, max_size, o, false, 0), pr;
+  Buffers b;
+  const bool status = o.validate && !o.d_status;
+  size_t bytes = list_rank_workspace(n0, L, user, false);
+  if (recorded_plan(p, n0, L, max_size, false, false, o, spacing_given, &pr))
+    bytes = std::max(bytes, carve(pr, L, false, o.validate != 0, status, nullptr, &b));
+  return bytes;
 }
 
 }  // namespace pj
