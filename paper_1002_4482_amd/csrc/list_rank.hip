@@ -85,7 +85,8 @@ __device__ __forceinline__ bool is_static(int y, int N, int log2B, uint32_t seed
 // What a walk needs to know of a node's successor y (a global id), worked out
 // once by the head-find pass so that a step of the walk is a read and a sign
 // test: y, with the sign bit set if y is a static splitter.  A tail is -1.
-constexpr int kNoCopy = 0, kPlainCopy = 1, kCodedCopy = 2;
+// Weighted calls get {code, weight} pairs.
+constexpr int kNoCopy = 0, kPlainCopy = 1, kCodedCopy = 2, kPairCopy = 3;
 
 __device__ __forceinline__ int step_code(int y, int N, int log2B, uint32_t seed) {
   return is_static(y, N, log2B, seed) ? y | INT32_MIN : y;
@@ -111,6 +112,7 @@ struct RecCtl {
 struct RecArgs {
   RecCtl* ctl;
   int4* strips;         // kStrip node ids (-1: none) per strip
+  int4* before;         // weighted: weight of the sublist before each of them
   int2* head;           // {sublist id, offset of the strip's first node} per strip
   int32_t* slab_of;     // [kXcds][max_slabs]
   int32_t* used;        // strips used of each slab
@@ -152,7 +154,10 @@ __global__ void lr_init(LrCtl* ctl, int n0, unsigned long long* lsum, int32_t* l
 // The same coalesced pass counts tails and flags out-of-range successors.
 template <int kCopy>
 __global__ void __launch_bounds__(256) lr_headfind_single(const int32_t* succ, int n,
-                                                          int32_t* copy, int log2B, uint32_t seed,
+                                                          int32_t* copy,
+                                                          const int32_t* __restrict__ weight,
+                                                          int2* __restrict__ pair, int log2B,
+                                                          uint32_t seed,
                                                           unsigned long long* lsum,
                                                           int32_t* ltails, int32_t* lerr,
                                                           unsigned long long* lnear) {
@@ -160,7 +165,8 @@ __global__ void __launch_bounds__(256) lr_headfind_single(const int32_t* succ, i
   int tails = 0, bad = 0, near = 0;
   const int tid = blockIdx.x * blockDim.x + threadIdx.x;
   const int stride = gridDim.x * blockDim.x;
-  const bool vec = ((reinterpret_cast<uintptr_t>(succ) | reinterpret_cast<uintptr_t>(copy)) & 15) == 0;
+  const bool vec = ((reinterpret_cast<uintptr_t>(succ) | reinterpret_cast<uintptr_t>(copy) |
+                     reinterpret_cast<uintptr_t>(weight)) & 15) == 0;
   const int n4 = vec ? (n >> 2) : 0;
   const int4* s4 = reinterpret_cast<const int4*>(succ);
   const auto one = [&](int s, int i) {  // counts node i, returns its code
@@ -170,7 +176,7 @@ __global__ void __launch_bounds__(256) lr_headfind_single(const int32_t* succ, i
     bad |= (!tail & !range);
     acc += (!tail & range) ? (unsigned long long)s : 0ull;
     near += (!tail & range) & ((unsigned)(s - i + kNear) <= 2u * kNear);
-    return kCopy != kCodedCopy ? s : (tail | !range) ? -1 : step_code(s, n, log2B, seed);
+    return kCopy < kCodedCopy ? s : (tail | !range) ? -1 : step_code(s, n, log2B, seed);
   };
   for (int q = tid; q < n4; q += stride) {
     int4 v = s4[q];
@@ -179,11 +185,18 @@ __global__ void __launch_bounds__(256) lr_headfind_single(const int32_t* succ, i
     v.y = one(v.y, i + 1);
     v.z = one(v.z, i + 2);
     v.w = one(v.w, i + 3);
-    if (kCopy != kNoCopy) reinterpret_cast<int4*>(copy)[q] = v;
+    if (kCopy == kPairCopy) {
+      const int4 u = reinterpret_cast<const int4*>(weight)[q];
+      reinterpret_cast<int4*>(pair)[2 * q] = make_int4(v.x, u.x, v.y, u.y);
+      reinterpret_cast<int4*>(pair)[2 * q + 1] = make_int4(v.z, u.z, v.w, u.w);
+    } else if (kCopy != kNoCopy) {
+      reinterpret_cast<int4*>(copy)[q] = v;
+    }
   }
   for (int i = (n4 << 2) + tid; i < n; i += stride) {
     const int v = one(succ[i], i);
-    if (kCopy != kNoCopy) copy[i] = v;
+    if (kCopy == kPairCopy) pair[i] = make_int2(v, weight[i]);
+    else if (kCopy != kNoCopy) copy[i] = v;
   }
   acc = wave_sum(acc);
   tails = wave_sum(tails);
@@ -223,7 +236,9 @@ constexpr int kHfChunk = 16;
 template <int kCopy>
 __global__ void __launch_bounds__(256) lr_headfind_batched(const int32_t* succ,
                                                            const int64_t* __restrict__ off, int L,
-                                                           int n, int32_t* copy, int log2B,
+                                                           int n, int32_t* copy,
+                                                           const int32_t* __restrict__ weight,
+                                                           int2* __restrict__ pair, int log2B,
                                                            uint32_t seed,
                                                            unsigned long long* lsum,
                                                            int32_t* ltails, int32_t* lerr) {
@@ -279,8 +294,11 @@ __global__ void __launch_bounds__(256) lr_headfind_batched(const int32_t* succ,
       tails += tail;
       if (!tail & !range) atomicOr(&lerr[l], kErrRange);
       acc += (!tail & range) ? (unsigned long long)s : 0ull;
-      if (kCopy == kCodedCopy)
-        copy[g] = (tail | !range) ? -1 : step_code((int)lbase + s, n, log2B, seed);
+      if (kCopy >= kCodedCopy) {
+        const int code = (tail | !range) ? -1 : step_code((int)lbase + s, n, log2B, seed);
+        if (kCopy == kPairCopy) pair[g] = make_int2(code, weight[g]);
+        else copy[g] = code;
+      }
     }
   }
   // wave-combine when the whole wave ended in one list
@@ -334,7 +352,14 @@ struct WalkArgs {
 constexpr int kWalkBurst = 16;
 constexpr int kWalkChunk = 64;  // items a wave takes at a time
 
-template <bool kLevel0, bool kBatched, bool kPacked>
+//
+// kPaired (level 0, weighted calls): the state array holds {step code, weight}
+// pairs, made by the head-find pass, and a visited one {-2 - sublist id, weight
+// before the node}: one random line per node instead of three for successor,
+// weight and state (walk of 2^26 random nodes 5.66 -> 2.58 ms in place, 1.59
+// recorded).  A visited state is told from a code by its sign and size, which
+// the host makes sure of.
+template <bool kLevel0, bool kBatched, bool kPacked, bool kPaired = false>
 __global__ void __launch_bounds__(1024) lr_walk(WalkArgs a) {
   LrCtl* ctl = a.ctl;
   const int N = level_nodes(ctl, a.level, a.L, a.cap_prev);
@@ -353,7 +378,7 @@ __global__ void __launch_bounds__(1024) lr_walk(WalkArgs a) {
   const int max_walk = far ? a.max_walk_far : a.max_walk;
   // One list, packed: the work array holds step codes, made for the far spacing
   // when there is one.
-  constexpr bool kCoded = kLevel0 && !kBatched && kPacked;
+  constexpr bool kCoded = kPaired || (kLevel0 && !kBatched && kPacked);
   const bool coded = a.log2B_far == 0 || far;
   const int r = (int)(((int64_t)N + (1 << log2B) - 1) >> log2B);
   const int head_base = kLevel0 ? 0 : ctl->lv[a.level - 1].r;
@@ -436,7 +461,7 @@ __global__ void __launch_bounds__(1024) lr_walk(WalkArgs a) {
           const int start = item << log2B;
           const int bsize = min(1 << log2B, N - start);
           x = start + (int)splitter_offset((uint32_t)item, seed, (uint32_t)bsize);
-          if (kLevel0 && kBatched) {
+          if (kLevel0 && kBatched && !kCoded) {
             lid = find_instance(a.off, a.L, x);
             base = a.off[lid];
             size = (int)(a.off[lid + 1] - base);
@@ -497,7 +522,16 @@ __global__ void __launch_bounds__(1024) lr_walk(WalkArgs a) {
       int y, w;
       bool tail;
       bool stop = false;  // y is a static splitter
-      if (kCoded) {
+      bool seen = false;  // (paired) a walk has been here: a malformed input
+      if (kPaired) {
+        const int2 in = a.state[x];
+        seen = in.x < -1 && in.x >= INT32_MIN + N;
+        tail = in.x == -1 || seen;
+        y = in.x & INT32_MAX;
+        w = seen ? 0 : in.y;
+        if (seen) errbits |= kErrBase;
+        stop = coded ? in.x < 0 : is_static(y, N, log2B, seed);
+      } else if (kCoded) {
         const int s = a.work[x];
         tail = s == -1;
         y = s & INT32_MAX;
@@ -529,7 +563,7 @@ __global__ void __launch_bounds__(1024) lr_walk(WalkArgs a) {
       }
       if (!kCoded) stop = is_static(y, N, log2B, seed);
       if (kLevel0 && kPacked) a.work[x] = (sid << kbits) | k;
-      else store_pair(&a.state[x], sid, k);
+      else if (!seen) store_pair(&a.state[x], kPaired ? -2 - sid : sid, k);
       k += w;
       if (tail) {
         store_pair(&a.link_out[sid], -1, k);
@@ -595,7 +629,7 @@ __global__ void __launch_bounds__(256) lr_rec_chunks(const int64_t* __restrict__
   }
 }
 
-template <bool kBatched>
+template <bool kBatched, bool kPaired>
 __global__ void __launch_bounds__(256) lr_walk_rec(WalkArgs a, RecArgs rec) {
   LrCtl* ctl = a.ctl;
   const int N = ctl->lv[0].n;
@@ -623,7 +657,7 @@ __global__ void __launch_bounds__(256) lr_walk_rec(WalkArgs a, RecArgs rec) {
     ahead_lb = rec.chunk_list[chunk + 1];
   }
 
-  int sid = -1, x = 0, k = 0;
+  int sid = -1, x = 0, k = 0, steps = 0;
   int errbits = 0;
   for (;;) {
     for (;;) {
@@ -656,7 +690,7 @@ __global__ void __launch_bounds__(256) lr_walk_rec(WalkArgs a, RecArgs rec) {
         x = start + (int)splitter_offset((uint32_t)block, seed,
                                          (uint32_t)min(1 << log2B, N - start));
         sid = block;
-        k = 0;
+        k = steps = 0;
       } else if (idle && item < end) {  // the virtual splitter at a list's head
         const int l = la + item - statics;
         const int64_t base = kBatched ? a.off[l] : 0;
@@ -675,7 +709,7 @@ __global__ void __launch_bounds__(256) lr_walk_rec(WalkArgs a, RecArgs rec) {
           } else {
             x = (int)(base + h);
             sid = r + l;
-            k = 0;
+            k = steps = 0;
           }
         }
       }
@@ -686,13 +720,21 @@ __global__ void __launch_bounds__(256) lr_walk_rec(WalkArgs a, RecArgs rec) {
     const bool walks = sid >= 0;
     const int k0 = k;
     bool over = !walks;
-    int node[kStrip];
+    int node[kStrip], before[kStrip];
 #pragma unroll
     for (int t = 0; t < kStrip; ++t) {
       node[t] = over ? -1 : x;
+      before[t] = k;
       if (!over) {
-        x = a.work[x];
-        ++k;
+        if (kPaired) {
+          const int2 in = a.state[x];
+          x = in.x;
+          k += in.y;
+        } else {
+          x = a.work[x];
+          ++k;
+        }
+        ++steps;
         over = x < 0;
       }
     }
@@ -723,13 +765,18 @@ __global__ void __launch_bounds__(256) lr_walk_rec(WalkArgs a, RecArgs rec) {
         for (int t = 0; t < kStrip / 4; ++t)
           rec.strips[(int64_t)strip * (kStrip / 4) + t] =
               make_int4(node[4 * t], node[4 * t + 1], node[4 * t + 2], node[4 * t + 3]);
+        if (kPaired)
+#pragma unroll
+          for (int t = 0; t < kStrip / 4; ++t)
+            rec.before[(int64_t)strip * (kStrip / 4) + t] =
+                make_int4(before[4 * t], before[4 * t + 1], before[4 * t + 2], before[4 * t + 3]);
         rec.head[strip] = make_int2(sid, k0);
       } else {
         errbits |= kErrOverflow;
         if (!over) store_pair(&a.link_out[sid], -1, k);
         over = true;
       }
-      if (!over && k >= a.max_walk) {  // cut: the node reached becomes a splitter
+      if (!over && steps >= a.max_walk) {  // cut: the node reached becomes a splitter
         const int t = atomicAdd(dyn, 1);
         if (t >= a.cap) {
           errbits |= kErrOverflow;
@@ -740,6 +787,7 @@ __global__ void __launch_bounds__(256) lr_walk_rec(WalkArgs a, RecArgs rec) {
           store_pair(&a.link_out[sid], nid, k);
           sid = nid;
           k = 0;
+          steps = 0;
         }
       }
       if (over) sid = -1;
@@ -756,7 +804,7 @@ __global__ void __launch_bounds__(256) lr_walk_rec(WalkArgs a, RecArgs rec) {
 // its entries reach a bin as one run.  kTileBins bins from the tile's lowest on
 // are sorted; entries past them (slabs of distant lists in one tile) go to
 // their bins one by one.
-template <bool kBatched, bool kToTail>
+template <bool kBatched, bool kToTail, bool kPaired>
 __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
                                                        const int32_t* __restrict__ srank,
                                                        const int64_t* __restrict__ off, int L,
@@ -773,7 +821,7 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
   const int listed = rec.ctl->listed[home];
   bool bad = false;
   // the thread's strip of the tile at i0, read one tile ahead
-  int ahead[kStrip];
+  int ahead[kStrip], ahead_before[kStrip];
   int2 ahead_head = make_int2(-1, 0);
   const auto fetch = [&](int i0) {
     ahead_head = make_int2(-1, 0);
@@ -791,6 +839,15 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
           ahead[4 * t + 2] = v.z;
           ahead[4 * t + 3] = v.w;
         }
+        if (kPaired)
+#pragma unroll
+          for (int t = 0; t < kStrip / 4; ++t) {
+            const int4 v = rec.before[strip * (kStrip / 4) + t];
+            ahead_before[4 * t] = v.x;
+            ahead_before[4 * t + 1] = v.y;
+            ahead_before[4 * t + 2] = v.z;
+            ahead_before[4 * t + 3] = v.w;
+          }
       }
     }
   };
@@ -798,14 +855,17 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
   const int begin = blockIdx.x / kXcds * kTileSlabs;
   if (begin < listed) fetch(begin);
   for (int i0 = begin; i0 < listed; i0 += step) {
-    int node[kStrip], pos[kStrip];
+    int node[kStrip], pos[kStrip], place[kStrip];  // place: in the sublist
     const int2 h = ahead_head;
     const bool have = h.x >= 0;
     const bool known = (unsigned)h.x < (unsigned)Nup;
     bad |= have && !known;
 #pragma unroll
-    for (int t = 0; t < kStrip; ++t) node[t] = known ? ahead[t] : -1;
-    int value = known ? srank[h.x] + h.y : 0;
+    for (int t = 0; t < kStrip; ++t) {
+      node[t] = known ? ahead[t] : -1;
+      place[t] = kPaired ? ahead_before[t] : kToTail ? -t : t;
+    }
+    int value = known ? srank[h.x] + (kPaired ? 0 : h.y) : 0;
     if (kToTail && known) {
       int size = N;
       if (kBatched) {
@@ -837,7 +897,7 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
           const int at = atomicAdd(&rec.cursor[b + lo], 1);
           if (at < kBinNodes)
             rec.ent[((int64_t)(b + lo) << kBinShift) + at] =
-                make_uint2((unsigned)node[t], (unsigned)(kToTail ? value - t : value + t));
+                make_uint2((unsigned)node[t], (unsigned)(value + place[t]));
         }
       }
     }
@@ -877,7 +937,7 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
     for (int t = 0; t < kStrip; ++t)
       if (pos[t] >= 0)
         ent[start[(node[t] >> kBinShift) - lo] + pos[t]] =
-            make_uint2((unsigned)node[t], (unsigned)(kToTail ? value - t : value + t));
+            make_uint2((unsigned)node[t], (unsigned)(value + place[t]));
     __syncthreads();
     for (int e = tid; e < total; e += kTileThreads) {
       const uint2 v = ent[e];
@@ -1554,6 +1614,38 @@ __global__ void __launch_bounds__(256) lr_expand0(const int2* __restrict__ state
   if (bad) atomicOr(&ctl->err, kErrTotal);
 }
 
+// Level 0 of a paired walk: rank = rank of the sublist + weight before the node.
+// A pair no walk came by (a cycle beside the list) is reported.
+__global__ void __launch_bounds__(256) lr_expand0_paired(const int2* __restrict__ state,
+                                                         const int32_t* __restrict__ srank_up,
+                                                         int32_t* __restrict__ rank, LrCtl* ctl,
+                                                         int L, int cap_here, int if_near) {
+  const int N = ctl->lv[0].n;
+  if (if_near && far_chosen(ctl, N)) return;
+  const int Nup = level_nodes(ctl, 1, L, cap_here);
+  int bad = 0;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t j0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j0 < N;
+       j0 += kExpandPer * stride) {
+    int2 s[kExpandPer];
+#pragma unroll
+    for (int u = 0; u < kExpandPer; ++u) {
+      const int64_t j = j0 + u * stride;
+      s[u] = j < N ? state[j] : make_int2(-1, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < kExpandPer; ++u) {
+      const int64_t j = j0 + u * stride;
+      if (j >= N) break;
+      const int sid = -2 - s[u].x;
+      const bool ok = s[u].x < -1 && s[u].x >= INT32_MIN + N && sid < Nup;
+      rank[j] = ok ? srank_up[sid] + s[u].y : 0;
+      bad |= !ok;
+    }
+  }
+  if (bad) atomicOr(&ctl->err, kErrTotal);
+}
+
 // ------------------------------------------------ per-node batched passes
 // Calls f(g, l, base, size) for every node g of a batch, with l its list.
 // Each wave owns a contiguous run of chunks of kWave * kListedPer nodes: one
@@ -1990,6 +2082,7 @@ struct Plan {
   int cap[PJ_MAX_LEVELS + 1] = {};
   int wide_rounds = 0;
   int wy_rounds = 0;
+  bool paired = false;     // weighted: {step code, weight} pairs at level 0
   bool packed = false;     // level 0 state packed into the output buffer
   int kbits = 0;           // offset bits of the packed state
   int max_walk0 = 0;       // cut length at level 0
@@ -2084,6 +2177,8 @@ Plan make_plan(int64_t n0, int64_t L, int64_t max_size, const pj_opts& o, bool w
     ++lv;
   }
   p.levels = lv;
+  // (a visited state -2 - sublist id must not reach down to a splitter's code)
+  p.paired = weighted && p.bound[1] + n0 + 2 < (int64_t(1) << 31);
   return p;
 }
 
@@ -2131,10 +2226,10 @@ constexpr int kRecordSpacing = 32;
 bool recorded_plan(const Plan& in_place, int64_t n0, int64_t L, int64_t max_size, bool single,
                    bool weighted, const pj_opts& o, bool spacing_given, Plan* out) {
   const Plan& q = in_place;
-  if (weighted || q.algo != PJ_ALGO_RULING_SET || q.small || q.chosen > 0 ||
-      o.level0_state == PJ_STATE_SEPARATE || o.max_walk % kStrip != 0)
+  if (weighted != q.paired || q.algo != PJ_ALGO_RULING_SET || q.small || q.chosen > 0 ||
+      (o.level0_state == PJ_STATE_SEPARATE && !weighted) || o.max_walk % kStrip != 0)
     return false;
-  if (single ? !q.packed || n0 < kRecordList || n0 > (int64_t)kTileBins * kBinNodes
+  if (single ? !(q.packed || q.paired) || n0 < kRecordList || n0 > (int64_t)kTileBins * kBinNodes
              : n0 < kRecordBatch || max_size > kRecordLongest)
     return false;
   Plan p = in_place;
@@ -2208,13 +2303,17 @@ size_t carve(const Plan& p, int64_t L, bool single, bool validate, bool want_sta
     if (!single) take(b->rec.chunk_list, (size_t)p.rec_chunks + 1);
     take(b->rec.cursor, (size_t)p.rec_bins);
     take(b->rec.ent, (size_t)p.rec_bins * kBinNodes);
+    if (p.paired) {
+      take(b->rec.before, slabs * kSlab * kStrip / 4);
+      b->state[0] = reinterpret_cast<int2*>(b->rec.ent);  // read before the bins are filled
+    }
     b->rec.max_slabs = p.max_slabs;
     b->rec.log2B = p.rec_log2B;
     b->rec.if_far = p.log2B_far > 0 ? 1 : 0;
   }
   if (p.chosen > 0) take(b->ssucc, (size_t)p.chosen);
   for (int l = 0; l < p.levels; ++l) {
-    if (l > 0 || !(p.packed || (p.max_slabs > 0 && p.log2B_far == 0))) take(b->state[l], (size_t)p.bound[l]);
+    if (l > 0 || !(p.packed || (p.max_slabs > 0 && (p.paired || p.log2B_far == 0)))) take(b->state[l], (size_t)p.bound[l]);
     take(b->link[l + 1], (size_t)p.bound[l + 1]);
     take(b->srank[l + 1], (size_t)p.bound[l + 1]);
   }
@@ -2366,12 +2465,13 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
     if (o.validate || o.d_status) {
       if (single)
         hipLaunchKernelGGL(lr_headfind_single<kNoCopy>, dim3(grid_for(n / 4 + 1, 256, 1024)),
-                           dim3(256), 0, stream, succ, n, nullptr, 0, 0u, b.lsum, b.ltails, b.lerr,
-                           nullptr);
+                           dim3(256), 0, stream, succ, n, nullptr, nullptr, nullptr, 0, 0u, b.lsum,
+                           b.ltails, b.lerr, nullptr);
       else
         hipLaunchKernelGGL(lr_headfind_batched<kNoCopy>,
                            dim3(headfind_grid(n, gcap)), dim3(256), 0,
-                           stream, succ, off, Li, n, nullptr, 0, 0u, b.lsum, b.ltails, b.lerr);
+                           stream, succ, off, Li, n, nullptr, nullptr, nullptr, 0, 0u, b.lsum, b.ltails,
+                           b.lerr);
       check_tails = true;
       tm.mark("headfind");
     }
@@ -2414,24 +2514,28 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
   } else if (n0 > 0) {
     // level 0 head find (and, in the packed form, the successor copy, which
     // in place is already there)
-    int32_t* copy = p.packed || recorded ? rank : nullptr;
+    int32_t* copy = !weight && (p.packed || recorded) ? rank : nullptr;
+    // weighted: successor and weight side by side where the state goes
+    int2* pair = weight && p.paired ? b.state[0] : nullptr;
     const bool copy_succ = copy && (const void*)succ != (const void*)rank;
     if (single) {
-      auto k = copy && p.chosen == 0 ? lr_headfind_single<kCodedCopy>
+      auto k = pair ? lr_headfind_single<kPairCopy>
+               : copy && p.chosen == 0 ? lr_headfind_single<kCodedCopy>
                : copy_succ ? lr_headfind_single<kPlainCopy> : lr_headfind_single<kNoCopy>;
       // (a workgroup ends in up to four atomics on the same words: 2^20 nodes
       // take 18.9 us with 1024 workgroups and 11.5 us with 256)
       hipLaunchKernelGGL(k, dim3(grid_for(n / 4 + 1, 256, n <= 1 << 22 ? 256 : 1024)), dim3(256),
-                         0, stream, succ, n, copy,
+                         0, stream, succ, n, copy, weight, pair,
                          p.log2B_far > 0 ? p.log2B_far : p.log2B[0], level_seed(o.seed, 0),
                          b.lsum, b.ltails, b.lerr, &b.ctl->near);
     } else {
-      auto k = recorded ? lr_headfind_batched<kCodedCopy>
+      auto k = pair ? lr_headfind_batched<kPairCopy>
+                        : recorded ? lr_headfind_batched<kCodedCopy>
                         : copy_succ ? lr_headfind_batched<kPlainCopy>
                                     : lr_headfind_batched<kNoCopy>;
       hipLaunchKernelGGL(k, dim3(headfind_grid(n, gcap)), dim3(256), 0,
-                         stream, succ, off, Li, n, copy, p.log2B[0], level_seed(o.seed, 0), b.lsum,
-                         b.ltails, b.lerr);
+                         stream, succ, off, Li, n, copy, weight, pair, p.log2B[0],
+                         level_seed(o.seed, 0), b.lsum, b.ltails, b.lerr);
     }
     PJ_HIP(hipGetLastError());
     if (p.chosen > 0) {
@@ -2442,7 +2546,7 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
     tm.mark("headfind");
     check_total = weight == nullptr;
     if (weight && status)
-      for (int lv = 0; lv < p.levels; ++lv)
+      for (int lv = pair ? 1 : 0; lv < p.levels; ++lv)
         hipLaunchKernelGGL(lr_state_clear, dim3(grid_for(p.bound[lv], 256, gcap)), dim3(256), 0,
                            stream, b.state[lv], p.bound[lv]);
     check_tails = true;
@@ -2473,6 +2577,7 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
       a.seed = level_seed(o.seed, lv);
       void (*kfn)(WalkArgs);
       if (lv > 0) kfn = lr_walk<false, false, false>;
+      else if (pair) kfn = single ? lr_walk<true, false, false, true> : lr_walk<true, true, false, true>;
       else if (single) kfn = p.packed ? lr_walk<true, false, true> : lr_walk<true, false, false>;
       else kfn = p.packed ? lr_walk<true, true, true> : lr_walk<true, true, false>;
       if (lv == 0 && recorded) {
@@ -2481,8 +2586,9 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
         if (!single)
           hipLaunchKernelGGL(lr_rec_chunks, dim3(grid_for(p.rec_chunks + 1, 256, gcap)), dim3(256),
                              0, stream, off, Li, p.rec_chunks, p.rec_log2B + 6, b.rec.chunk_list);
-        hipLaunchKernelGGL(single ? lr_walk_rec<false> : lr_walk_rec<true>, dim3(p.rec_grid),
-                           dim3(256), 0, stream, ra, b.rec);
+        const auto walk = pair ? (single ? lr_walk_rec<false, true> : lr_walk_rec<true, true>)
+                               : (single ? lr_walk_rec<false, false> : lr_walk_rec<true, false>);
+        hipLaunchKernelGGL(walk, dim3(p.rec_grid), dim3(256), 0, stream, ra, b.rec);
         PJ_HIP(hipGetLastError());
         if (!b.rec.if_far) {
           tm.mark("walk0");
@@ -2548,8 +2654,10 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
       else ex0 = p.packed ? lr_expand0<true, false, true> : lr_expand0<true, false, false>;
     }
     if (recorded) {
-      const auto bin = single ? (o.to_tail ? lr_bin<false, true> : lr_bin<false, false>)
-                              : (o.to_tail ? lr_bin<true, true> : lr_bin<true, false>);
+      const auto bin =
+          pair ? (single ? lr_bin<false, false, true> : lr_bin<true, false, true>)
+          : single ? (o.to_tail ? lr_bin<false, true, false> : lr_bin<false, false, false>)
+                   : (o.to_tail ? lr_bin<true, true, false> : lr_bin<true, false, false>);
       const int cus = device_info().cus;
       hipLaunchKernelGGL(bin, dim3(cus / kXcds * kXcds), dim3(kTileThreads), 0, stream, b.rec,
                          (const int32_t*)b.srank[1], off, Li, p.cap[0], b.ctl);
@@ -2558,7 +2666,10 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
                          b.rec, rank, b.ctl);
       tm.mark("place");
     }
-    if (!recorded || b.rec.if_far)
+    if (pair && (!recorded || b.rec.if_far))
+      hipLaunchKernelGGL(lr_expand0_paired, dim3(g0), dim3(256), 0, stream, (const int2*)pair,
+                         (const int32_t*)b.srank[1], rank, b.ctl, Li, p.cap[0], recorded ? 1 : 0);
+    else if (!recorded || b.rec.if_far)
       hipLaunchKernelGGL(ex0, dim3(g0), dim3(256), 0, stream, b.state[0], b.srank[1], rank, off,
                          b.ctl, Li, p.cap[0], p.kbits, single ? p.kbits_far : 0,
                          recorded ? 1 : 0);
