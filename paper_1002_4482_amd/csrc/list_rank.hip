@@ -105,8 +105,7 @@ constexpr int kTileThreads = kTileSlabs * kSlab;
 constexpr int kTileBins = 2048;
 
 struct RecCtl {
-  int32_t slabs;             // slabs taken
-  int32_t listed[kXcds];     // entries of slab_of
+  int32_t taken[kXcds];      // slabs taken of each group's
 };
 
 struct RecArgs {
@@ -114,12 +113,11 @@ struct RecArgs {
   int4* strips;         // kStrip node ids (-1: none) per strip
   int4* before;         // weighted: weight of the sublist before each of them
   int2* head;           // {sublist id, offset of the strip's first node} per strip
-  int32_t* slab_of;     // [kXcds][max_slabs]
   int32_t* used;        // strips used of each slab
   int32_t* chunk_list;  // a batch: first list of each chunk
   int32_t* cursor;      // entries of each bin
   uint2* ent;           // {node, rank}, kBinNodes per bin
-  int max_slabs;
+  int group_slabs;      // slabs of a group (an XCD of a batch; all of one list)
   int log2B;            // splitter spacing
   int if_far;           // only if the head-find pass found the list not local
 };
@@ -611,8 +609,10 @@ __global__ void __launch_bounds__(1024) lr_walk(WalkArgs a) {
 // mapping.  256 lists of 2^18 nodes, following successors: 69 G nodes/s over
 // all XCDs, 220 G/s list by list.
 //
-// Strips are handed out in slabs of kSlab per wave, from one counter; slab_of
-// lists the slabs of each XCD in the order they were taken.
+// Strips are handed out in slabs of kSlab per wave, in order from one counter
+// per group: the XCD of a batch, so that lr_bin finds slabs of neighbouring
+// lists together, or all waves of one list.  A wave holds one slab ahead, so
+// it never waits for the counter.
 // First list of every chunk of kWalkChunk splitter blocks (a batch).
 __global__ void __launch_bounds__(256) lr_rec_chunks(const int64_t* __restrict__ off, int L,
                                                      int nchunks, int log2_chunk,
@@ -651,6 +651,9 @@ __global__ void __launch_bounds__(256) lr_walk_rec(WalkArgs a, RecArgs rec) {
   // heads of the lists la .. la + heads - 1; next of them to be taken
   int first = 0, statics = 0, la = 0, heads = 0, next = 0;
   int slab = -1, cursor = kSlab;    // the wave's slab and the strips used of it
+  const int group = kBatched ? home : 0;
+  int ahead_slab = 0;               // in lane 0: the group's slab taken ahead
+  if (lane_id() == 0) ahead_slab = atomicAdd(&rec.ctl->taken[group], 1);
   int ahead_la = 0, ahead_lb = 0;   // lists of the next chunk, read early
   if (kBatched && chunk < range_hi) {
     ahead_la = rec.chunk_list[chunk];
@@ -745,15 +748,12 @@ __global__ void __launch_bounds__(256) lr_walk_rec(WalkArgs a, RecArgs rec) {
     const int mine = cursor + lanes_below(walking);
     int strip = mine < kSlab ? slab * kSlab + mine : -1;
     if (cursor + count > kSlab) {
-      int fresh = 0;
+      const int fresh = __builtin_amdgcn_readfirstlane(ahead_slab);
       if (lane_id() == 0) {
         if (slab >= 0) rec.used[slab] = kSlab;
-        fresh = atomicAdd(&rec.ctl->slabs, 1);
-        if (fresh < rec.max_slabs)
-          rec.slab_of[home * rec.max_slabs + atomicAdd(&rec.ctl->listed[home], 1)] = fresh;
+        ahead_slab = atomicAdd(&rec.ctl->taken[group], 1);
       }
-      fresh = __builtin_amdgcn_readfirstlane(fresh);
-      slab = fresh < rec.max_slabs ? fresh : -1;
+      slab = fresh < rec.group_slabs ? group * rec.group_slabs + fresh : -1;
       if (strip < 0 && slab >= 0) strip = slab * kSlab + (mine - kSlab);
       cursor -= kSlab;
       if (slab < 0) cursor = kSlab - count;  // no slab: only a malformed input gets here
@@ -793,7 +793,10 @@ __global__ void __launch_bounds__(256) lr_walk_rec(WalkArgs a, RecArgs rec) {
       if (over) sid = -1;
     }
   }
-  if (lane_id() == 0 && slab >= 0) rec.used[slab] = cursor;
+  if (lane_id() == 0) {
+    if (slab >= 0) rec.used[slab] = cursor;
+    if (ahead_slab < rec.group_slabs) rec.used[group * rec.group_slabs + ahead_slab] = 0;
+  }
   if (errbits) atomicOr(&ctl->err, errbits);
 }
 
@@ -817,8 +820,9 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
   if (!kBatched && rec.if_far && !far_chosen(ctl, N)) return;
   const int Nup = level_nodes(ctl, 1, L, cap_here);
   const int tid = threadIdx.x;
-  const int home = blockIdx.x % kXcds;
-  const int listed = rec.ctl->listed[home];
+  const int groups = kBatched ? kXcds : 1;
+  const int group = blockIdx.x % groups;
+  const int taken = min(rec.ctl->taken[group], rec.group_slabs);
   bool bad = false;
   // the thread's strip of the tile at i0, read one tile ahead
   int ahead[kStrip], ahead_before[kStrip];
@@ -826,8 +830,8 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
   const auto fetch = [&](int i0) {
     ahead_head = make_int2(-1, 0);
     const int i = i0 + tid / kSlab;
-    if (i < listed) {
-      const int slab = rec.slab_of[home * rec.max_slabs + i];
+    if (i < taken) {
+      const int slab = group * rec.group_slabs + i;
       if (tid % kSlab < rec.used[slab]) {
         const int64_t strip = (int64_t)slab * kSlab + tid % kSlab;
         ahead_head = rec.head[strip];
@@ -851,10 +855,10 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
       }
     }
   };
-  const int step = gridDim.x / kXcds * kTileSlabs;
-  const int begin = blockIdx.x / kXcds * kTileSlabs;
-  if (begin < listed) fetch(begin);
-  for (int i0 = begin; i0 < listed; i0 += step) {
+  const int step = gridDim.x / groups * kTileSlabs;
+  const int begin = blockIdx.x / groups * kTileSlabs;
+  if (begin < taken) fetch(begin);
+  for (int i0 = begin; i0 < taken; i0 += step) {
     int node[kStrip], pos[kStrip], place[kStrip];  // place: in the sublist
     const int2 h = ahead_head;
     const bool have = h.x >= 0;
@@ -874,7 +878,7 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
       }
       value = size - 1 - value;
     }
-    if (i0 + step < listed) fetch(i0 + step);
+    if (i0 + step < taken) fetch(i0 + step);
     if (tid == 0) low = INT32_MAX;
     for (int b = tid; b < kTileBins; b += kTileThreads) hist[b] = 0;
     __syncthreads();
@@ -2089,7 +2093,7 @@ struct Plan {
   int log2B_far = 0;       // > 0: level 0 may pick this on the device (see lr_walk),
   int kbits_far = 0;       // with these offset bits (packed form)
   int max_walk_far = 0;    // and this cut length
-  int rec_grid = 0, rec_log2B = 0, rec_chunks = 0, rec_bins = 0;
+  int rec_grid = 0, rec_log2B = 0, rec_chunks = 0, rec_bins = 0, group_slabs = 0;
   int max_slabs = 0;       // > 0: level 0 records its walks (see lr_walk_rec)
   int64_t chosen = 0;      // > 0: level 0 uses this many caller-chosen splitters
 };
@@ -2241,11 +2245,19 @@ bool recorded_plan(const Plan& in_place, int64_t n0, int64_t L, int64_t max_size
   if (p.log2B_far > 0) p.log2B_far = std::max(p.log2B_far, ilog2(kRecordSpacing));
   p.rec_grid = device_info().cus * (single ? 2 : 1) / kXcds * kXcds;
   p.rec_log2B = p.log2B_far > 0 ? p.log2B_far : p.log2B[0];
-  // every sublist piece ends in one partly filled strip at most, and every
-  // wave in one partly filled slab
+  // Every sublist piece ends in one partly filled strip at most, and every wave
+  // in one partly filled and one unused slab.  The sublists that start in an
+  // XCD's eighth of a batch stay in the lists that do, so they hold an eighth
+  // of the nodes and two lists at most -- of the longest size that a captured
+  // call may be replayed with, the next power of two.
   const int64_t r = (n0 + (1ll << p.rec_log2B) - 1) >> p.rec_log2B;
-  const int64_t strips = n0 / kStrip + r + L + n0 / o.max_walk + 64;
-  p.max_slabs = (int)(strips / kSlab + 1 + p.rec_grid * (256 / kWave));
+  const int64_t groups = single ? 1 : kXcds;
+  const int64_t longest = 1ll << bits_for(max_size);
+  const int64_t nodes = n0 / groups + (single ? 0 : 2 * longest + (kWalkChunk << p.rec_log2B));
+  const int64_t pieces = r / groups + kWalkChunk + L + nodes / o.max_walk + 64;
+  p.group_slabs =
+      (int)((nodes / kStrip + pieces) / kSlab + 1 + 2 * (p.rec_grid / groups) * (256 / kWave));
+  p.max_slabs = (int)(groups * p.group_slabs);
   p.rec_chunks = (int)((r + kWalkChunk - 1) / kWalkChunk);
   p.rec_bins = (int)((n0 + kBinNodes - 1) >> kBinShift);
   *out = p;
@@ -2298,7 +2310,6 @@ size_t carve(const Plan& p, int64_t L, bool single, bool validate, bool want_sta
     take(b->rec.ctl, 1);
     take(b->rec.strips, slabs * kSlab * kStrip / 4);
     take(b->rec.head, slabs * kSlab);
-    take(b->rec.slab_of, slabs * kXcds);
     take(b->rec.used, slabs);
     if (!single) take(b->rec.chunk_list, (size_t)p.rec_chunks + 1);
     take(b->rec.cursor, (size_t)p.rec_bins);
@@ -2307,7 +2318,7 @@ size_t carve(const Plan& p, int64_t L, bool single, bool validate, bool want_sta
       take(b->rec.before, slabs * kSlab * kStrip / 4);
       b->state[0] = reinterpret_cast<int2*>(b->rec.ent);  // read before the bins are filled
     }
-    b->rec.max_slabs = p.max_slabs;
+    b->rec.group_slabs = p.group_slabs;
     b->rec.log2B = p.rec_log2B;
     b->rec.if_far = p.log2B_far > 0 ? 1 : 0;
   }
