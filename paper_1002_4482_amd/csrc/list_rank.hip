@@ -422,6 +422,14 @@ __global__ void __launch_bounds__(1024) lr_walk(WalkArgs a) {
   int lid = 0;        // level 0: list index
   bool retired = false;
   int errbits = 0;
+  // what a node's step needs: {successor or code, weight}
+  const auto fetch = [&](int at) {
+    if (kPaired) return a.state[at];
+    if (kLevel0 && kPacked) return make_int2(a.work[at], 1);
+    if (kLevel0) return make_int2(a.succ0[at], a.weight0 ? a.weight0[at] : 1);
+    return a.link_in[at];
+  };
+  int2 in = make_int2(-1, 0);  // of node x
 
   while (true) {
     const bool need = (sid < 0) & !retired;
@@ -512,35 +520,37 @@ __global__ void __launch_bounds__(1024) lr_walk(WalkArgs a) {
         }
       }
     }
+    if (need && sid >= 0) {
+      in = fetch(x);
+      // waited for here, or the loop below would wait for its stores as well
+      asm volatile("" : "+v"(in.x), "+v"(in.y));
+    }
     if (__ballot(!retired) == 0) break;
     // Up to kWalkBurst steps before looking for new work: when the steps hit
     // in cache (local layouts) the work-distribution code, not memory, would
     // otherwise set the pace; random layouts do not notice either way.
     for (int rep = 0; rep < kWalkBurst && sid >= 0; ++rep) {
-      int y, w;
+      int y = in.x, w = in.y;
       bool tail;
       bool stop = false;  // y is a static splitter
       bool seen = false;  // (paired) a walk has been here: a malformed input
       if (kPaired) {
-        const int2 in = a.state[x];
         seen = in.x < -1 && in.x >= INT32_MIN + N;
         tail = in.x == -1 || seen;
         y = in.x & INT32_MAX;
-        w = seen ? 0 : in.y;
+        if (seen) w = 0;
         if (seen) errbits |= kErrBase;
         stop = coded ? in.x < 0 : is_static(y, N, log2B, seed);
       } else if (kCoded) {
-        const int s = a.work[x];
-        tail = s == -1;
-        y = s & INT32_MAX;
+        tail = in.x == -1;
+        y = in.x & INT32_MAX;
         if (!tail && y >= N) {  // a state: a malformed input led here twice
           errbits |= kErrRange;
           tail = true;
         }
-        w = 1;
-        stop = coded ? s < 0 : is_static(y, N, log2B, seed);
+        stop = coded ? in.x < 0 : is_static(y, N, log2B, seed);
       } else if (kLevel0) {
-        const int s = kPacked ? a.work[x] : a.succ0[x];
+        const int s = in.x;
         const int xl = (int)(x - base);
         tail = (s == -1) | (s == xl);
         if (!tail && (unsigned)s >= (unsigned)size) {
@@ -548,21 +558,23 @@ __global__ void __launch_bounds__(1024) lr_walk(WalkArgs a) {
           tail = true;
         }
         y = (int)(base + s);
-        w = (!kPacked && a.weight0) ? a.weight0[x] : 1;
       } else {
-        const int2 in = a.link_in[x];
         tail = in.x == -1;
         if (!tail && (unsigned)in.x >= (unsigned)N) {
           errbits |= kErrBase;
           tail = true;
         }
-        y = in.x;
-        w = in.y;
       }
       if (!kCoded) stop = is_static(y, N, log2B, seed);
+      // The next load before this node's store: a load is only waited for
+      // together with the stores issued before it, which doubles the latency
+      // of a step (2^20 random nodes: walks of 54 + 29 us, 61 + 35 the other
+      // way round, and that is what a sublist of 90 steps waits for).
+      if (!tail && !stop) in = fetch(y);
       if (kLevel0 && kPacked) a.work[x] = (sid << kbits) | k;
       else if (!seen) store_pair(&a.state[x], kPaired ? -2 - sid : sid, k);
       k += w;
+      x = y;
       if (tail) {
         store_pair(&a.link_out[sid], -1, k);
         sid = -1;
@@ -581,10 +593,7 @@ __global__ void __launch_bounds__(1024) lr_walk(WalkArgs a) {
           sid = nid;
           k = 0;
           steps = 0;
-          x = y;
         }
-      } else {
-        x = y;
       }
     }
   }
