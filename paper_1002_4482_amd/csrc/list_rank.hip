@@ -567,9 +567,9 @@ __global__ void __launch_bounds__(1024) lr_walk(WalkArgs a) {
       }
       if (!kCoded) stop = is_static(y, N, log2B, seed);
       // The next load before this node's store: a load is only waited for
-      // together with the stores issued before it, which doubles the latency
-      // of a step (2^20 random nodes: walks of 54 + 29 us, 61 + 35 the other
-      // way round, and that is what a sublist of 90 steps waits for).
+      // together with the stores issued before it (2^20 random nodes, whose
+      // longest sublist of about 90 steps sets the time: walks of 61 + 32 us,
+      // 67 + 36 the other way round).
       if (!tail && !stop) in = fetch(y);
       if (kLevel0 && kPacked) a.work[x] = (sid << kbits) | k;
       else if (!seen) store_pair(&a.state[x], kPaired ? -2 - sid : sid, k);
@@ -1273,204 +1273,224 @@ __global__ void __launch_bounds__(kBaseThreads) lr_base_lds(const int2* __restri
 }
 
 // The same for a few lists (at most kBaseLists), by the ruling set once more,
-// inside LDS: one splitter per kBaseBlock ids and the heads; a thread walks its
-// splitters' sublists, the splitters are ranked by pointer jumping, and a node
-// gets its splitter's rank + its offset.  Jumping over all nodes takes
+// inside LDS: one splitter per block of 4 or 8 ids and the heads; a thread walks
+// its splitters' sublists, the splitters are ranked by pointer jumping, and a
+// node gets its splitter's rank + its offset.  Jumping over all nodes takes
 // ceil(log2 N) rounds of two LDS accesses a node, which set its time (12500
-// nodes: BASEOLD us); here a node costs three accesses, and only a quarter of
-// the nodes jump (BASENEW us).
+// nodes: 52 us, 35 with one splitter per 4 ids); here a node costs three
+// accesses, and only a quarter or an eighth of the nodes jump.
+//
+// One workgroup runs it, so latency and its instruction count bound it: every
+// phase issues its reads before it uses one, a walk reads its next node before
+// it marks the last, each wave has its own share of the walks instead of a
+// counter, and a wave skips the rows it has no part in (12500 nodes: 35 -> 21.7
+// us, 8194: 29 -> 20).  A second workgroup of the same XCD reads the level into
+// their L2 meanwhile, as one CU alone reads 9 bytes a clock from beyond it (2 us
+// of 12500 nodes).  Blocks of 8 take more steps a walk and half the jumps:
+// lists of 100003 and 2^20 and 2^22 nodes, whose bases have 12502, 8194 and 8194
+// nodes, take 59.3, 131.1 and 263.7 us with them, 61.9, 131.2 and 262.4 with
+// blocks of 4.
 //
 // word[x]: {weight, next (| kStop)} at first; {offset, splitter | kSeen} once a walk has
-// passed x; of a splitter {weight of the sublists before it, ancestor} while
-// jumping.
-constexpr int kBaseBlock = 4;
+// passed x; of a splitter {weight of its sublist, next splitter} after its walk
+// and {weight of the sublists before it, ancestor} while jumping.
+constexpr int kBaseBlock4 = 10240;  // blocks of 4 up to this many nodes
 constexpr int kBaseLists = 1024;
+constexpr int kEarlyRows = 2;
 constexpr int kSeen = 1 << 30;
 constexpr int kStop = 1 << 29;  // the next node is a splitter
+constexpr int kEnd = kStop - 1;  // no next node (with kStop in a node's word)
 constexpr unsigned long long kNoPred = ~0ull;
 
 __device__ __forceinline__ unsigned long long pack_w(int hi, uint32_t lo) {
   return (unsigned long long)(unsigned)hi << 32 | lo;
 }
 
+// `bound` nodes may be read of link, whatever the level's node count.
 __global__ void __launch_bounds__(kBaseThreads) lr_base_walk(const int2* __restrict__ link,
                                                              int32_t* __restrict__ srank,
                                                              LrCtl* ctl, int level, int L,
-                                                             int cap_prev) {
-  __shared__ unsigned long long word[kMaxCutoff];
-  __shared__ unsigned long long total;
-  __shared__ int taken;
-  const int N = level_nodes(ctl, level, L, cap_prev);
-  const int head_base = ctl->lv[level - 1].r;
-  const int tid = threadIdx.x;
-  if (tid == 0) {
-    total = 0ull;
-    taken = 0;
+                                                             int cap_prev, int bound) {
+  if (blockIdx.x > 0) {
+    if (blockIdx.x % kXcds != 0) return;
+    const int nodes = min(bound, level_nodes(ctl, level, L, cap_prev));
+    int any = 0;  // one node per 128-byte line
+    for (int j = threadIdx.x * 16; j < nodes; j += 16 * kBaseThreads) any |= link[j].x;
+    asm volatile("" ::"v"(any));  // that the loads are kept
+    return;
   }
-  if (N > kMaxCutoff || head_base + L > N) {
+  // one word more, which lanes without a splitter take for theirs
+  __shared__ unsigned long long word[kMaxCutoff + 1];
+  __shared__ unsigned long long total;
+  const int tid = threadIdx.x;
+  // the wave's first row entry: rows it has no part in are skipped as a whole
+  const int wave0 = __builtin_amdgcn_readfirstlane(tid & ~(kWave - 1));
+  int2 in[kPerThread];  // the first rows while the node count is on its way
+  const auto read = [&](int t, int limit) {
+    const int j = tid + t * kBaseThreads;
+    in[t] = j < limit ? link[j] : make_int2(-1, 0);
+  };
+#pragma unroll
+  for (int t = 0; t < kEarlyRows; ++t) read(t, bound);
+  const int N = level_nodes(ctl, level, L, cap_prev);
+#pragma unroll
+  for (int t = kEarlyRows; t < kPerThread; ++t) read(t, min(N, bound));
+  const int head_base = ctl->lv[level - 1].r;
+  if (tid == 0) total = 0ull;
+  if (N > min(kMaxCutoff, bound) || head_base + L > N) {
     if (tid == 0) atomicOr(&ctl->err, kErrBase);
     return;
   }
+  const int log2b = N <= kBaseBlock4 ? 2 : 3;
+  // (in the last block it may lie past the nodes: then there is none)
   const auto block_splitter = [&](int b) {
-    const int x = b * kBaseBlock + (int)(mix32((uint32_t)b) >> 16) % kBaseBlock;
-    return x < N ? x : b * kBaseBlock;
+    return (b << log2b) + (int)(((unsigned)b % 65536 * 0x9E3779u >> 20) & ((1u << log2b) - 1));
   };
-  const auto is_head = [&](int x) { return x >= head_base && x < head_base + L; };
-  const auto is_splitter = [&](int x) {
-    return x == block_splitter(x / kBaseBlock) || is_head(x);
-  };
-  bool bad = false;
+  const auto is_head = [&](int x) { return (unsigned)(x - head_base) < (unsigned)L; };
+  int bad = 0;
   unsigned long long mytotal = 0;
-  {
-    int2 in[kPerThread];
 #pragma unroll
-    for (int t = 0; t < kPerThread; ++t) {
+  for (int t = 0; t < kPerThread; ++t)
+    if (t * kBaseThreads + wave0 < N) {
       const int j = tid + t * kBaseThreads;
-      in[t] = j < N ? link[j] : make_int2(-1, 0);
+      const int to = j < N ? in[t].x : -1;
+      const int weight = j < N ? in[t].y : 0;
+      const bool end = (unsigned)to >= (unsigned)N;
+      const bool stop = end | is_head(to) | (block_splitter(to >> log2b) == to);
+      bad |= end & (to != -1);
+      mytotal += (unsigned)weight;
+      word[j] = pack_w(weight, (end ? kEnd : to) | (stop ? kStop : 0));
     }
-#pragma unroll
-    for (int t = 0; t < kPerThread; ++t) {
-      const int j = tid + t * kBaseThreads;
-      if (j >= N) continue;
-      const bool end = in[t].x < 0 || in[t].x >= N;
-      bad |= end && in[t].x != -1;
-      mytotal += (unsigned)in[t].y;
-      const bool stop = !end && is_splitter(in[t].x);
-      word[j] = pack_w(in[t].y, end ? ~0u : (uint32_t)in[t].x | (stop ? kStop : 0));
-    }
-  }
-  // the thread's splitters: one per row of blocks, then one head
-  constexpr int kRows = kMaxCutoff / kBaseBlock / kBaseThreads + 1;
-  const int blocks = (N + kBaseBlock - 1) / kBaseBlock;
-  int mine[kRows], reach[kRows], weight[kRows];
-#pragma unroll
-  for (int t = 0; t < kRows; ++t) {
-    mine[t] = -1;
-    if (t < kRows - 1) {
-      const int b = tid + t * kBaseThreads;
-      if (b < blocks) mine[t] = block_splitter(b);
-    } else if (tid < L) {
-      const int h = head_base + tid;
-      if (block_splitter(h / kBaseBlock) != h) mine[t] = h;
-    }
-  }
   __syncthreads();
+  const int blocks = (N + (1 << log2b) - 1) >> log2b;
   // Walks: a lane takes a splitter, follows its successors to the next one and
-  // leaves {sublist weight, next splitter or -1} in the splitter's word, which
-  // no other walk reads.
+  // leaves {sublist weight, next splitter or kEnd} in the splitter's word,
+  // which no other walk reads.  (A branch leads to a node walked already, and a
+  // cycle without a splitter to its own first node: either ends the walk.)
   {
     const int slots = blocks + L;
-    int own = -1, x = -1, acc = 0, steps = 0;
-    bool retired = false;
+    constexpr int kWaves = kBaseThreads / kWave;
+    const int per = (slots + kWaves - 1) / kWaves;
+    int next = wave0 / kWave * per;
+    const int last = min(slots, next + per);
+    int own = -1, x = 0, acc = 0;
+    unsigned long long w = 0;
     for (;;) {
-      const uint64_t idle = __ballot(own < 0 && !retired);
-      if (idle) {
-        int first = 0;
-        if (lane_id() == __builtin_ctzll(idle)) first = atomicAdd(&taken, (int)__popcll(idle));
-        first = __shfl(first, __builtin_ctzll(idle));
-        if (own < 0 && !retired) {
-          const int slot = first + lanes_below(idle);
-          retired = slot >= slots;
-          if (!retired) {
-            own = slot < blocks ? block_splitter(slot) : head_base + slot - blocks;
-            if (slot >= blocks && block_splitter(own / kBaseBlock) == own) {
-              own = -1;  // a head that is its block's splitter
-            } else {
-              const unsigned long long w = word[own];
-              x = (int)(uint32_t)w;
-              acc = (int)(w >> 32);
-            }
+      const uint64_t idle = __ballot(own < 0);
+      if (idle && next < last) {
+        const int slot = next + lanes_below(idle);
+        next += (int)__popcll(idle);
+        if (own < 0 && slot < last) {
+          const int at = slot < blocks ? block_splitter(slot) : head_base + slot - blocks;
+          // (a head may be its block's splitter)
+          if (slot < blocks ? at < N : block_splitter(at >> log2b) != at) {
+            own = x = at;
+            acc = 0;
+            w = word[x];
           }
         }
+      } else if (idle == ~0ull) {
+        break;
       }
-      if (__ballot(!retired) == 0) break;
 #pragma unroll
       for (int rep = 0; rep < 4; ++rep)
         if (own >= 0) {
-          if (x < 0 || (x & kStop)) {
-            word[own] = pack_w(acc, x < 0 ? ~0u : (uint32_t)(x & ~kStop));
+          const int to = (int)(uint32_t)w;
+          const bool end = to & (kSeen | kStop);
+          const unsigned long long mark = pack_w(acc, (uint32_t)(own | kSeen));
+          const int at = x;
+          acc += (int)(w >> 32);
+          x = end ? own : to;
+          w = word[x];
+          word[at] = mark;
+          if (end) {
+            word[own] = pack_w(acc, (to & kSeen) ? kEnd : to & ~kStop);
+            bad |= to & kSeen;
             own = -1;
-          } else {
-            const unsigned long long w = word[x];
-            const int next = (int)(uint32_t)w;
-            if ((next >= 0 && (next & kSeen)) || ++steps > 2 * kMaxCutoff) {
-              bad = true;  // walked already (a branch), or a cycle without a splitter
-              x = -1;
-            } else {
-              word[x] = pack_w(acc, (uint32_t)(own | kSeen));
-              acc += (int)(w >> 32);
-              x = next;
-            }
           }
         }
     }
   }
   __syncthreads();
-#pragma unroll
-  for (int t = 0; t < kRows; ++t)
-    if (mine[t] >= 0) {
-      const unsigned long long w = word[mine[t]];
-      reach[t] = (int)(uint32_t)w;
-      weight[t] = (int)(w >> 32);
-    }
-  __syncthreads();
-#pragma unroll
-  for (int t = 0; t < kRows; ++t)
-    if (mine[t] >= 0) word[mine[t]] = is_head(mine[t]) ? pack_w(0, (uint32_t)mine[t]) : kNoPred;
-  __syncthreads();
-#pragma unroll
-  for (int t = 0; t < kRows; ++t)
-    if (mine[t] >= 0 && reach[t] >= 0)
-      bad |= atomicExch(&word[reach[t]], pack_w(weight[t], (uint32_t)mine[t])) != kNoPred;
-  __syncthreads();
+  // the thread's splitters: one per row of blocks, then one head
+  constexpr int kRows =
+      (std::max(kBaseBlock4 / 4, kMaxCutoff / 8) + kBaseThreads - 1) / kBaseThreads + 1;
+  constexpr int kNone = kMaxCutoff;
+  int mine[kRows];
   unsigned long long at[kRows];
+  const auto row = [&](int t) {
+    return t < kRows - 1 ? t * kBaseThreads + wave0 < blocks : wave0 < L;
+  };
 #pragma unroll
   for (int t = 0; t < kRows; ++t)
-    if (mine[t] >= 0) {
-      at[t] = word[mine[t]];
-      if (at[t] == kNoPred) bad = true;  // a head that is no list's
+    if (row(t)) {
+      const int b = tid + t * kBaseThreads, h = head_base + tid;
+      const int x = t < kRows - 1 ? block_splitter(b) : h;
+      const bool is = t < kRows - 1 ? b < blocks && x < N
+                                    : tid < L && block_splitter(h >> log2b) != h;
+      mine[t] = is ? x : kNone;
+      at[t] = is ? word[x] : pack_w(0, kEnd);
     }
-  if (bad) atomicOr(&ctl->err, kErrBase);
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < kRows; ++t)
+    if (row(t))
+      word[mine[t]] = is_head(mine[t]) || mine[t] == kNone ? pack_w(0, (uint32_t)mine[t]) : kNoPred;
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < kRows; ++t)
+    if (row(t) && (uint32_t)at[t] != kEnd)
+      bad |= atomicExch(&word[(uint32_t)at[t]],
+                        pack_w((int)(at[t] >> 32), (uint32_t)mine[t])) != kNoPred;
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < kRows; ++t)
+    if (row(t)) at[t] = word[mine[t]];
   // (a malformed forest may leave splitters without predecessor: they jump
   // nowhere)
 #pragma unroll
   for (int t = 0; t < kRows; ++t)
-    if (mine[t] >= 0 && at[t] == kNoPred) word[mine[t]] = at[t] = pack_w(0, (uint32_t)mine[t]);
+    if (row(t) && at[t] == kNoPred) {
+      bad = 1;  // a head that is no list's
+      word[mine[t]] = at[t] = pack_w(0, (uint32_t)mine[t]);
+    }
+  if (bad) atomicOr(&ctl->err, kErrBase);
   __syncthreads();
-  for (int span = 1; span < 2 * (blocks + L); span *= 2) {
-    bool moved = false;
+  for (int span = 1; span < blocks + L; span *= 2) {
+    unsigned long long up[kRows];
 #pragma unroll
     for (int t = 0; t < kRows; ++t)
-      if (mine[t] >= 0) {
-        const unsigned long long w = word[(uint32_t)at[t]];
-        if ((uint32_t)w != (uint32_t)at[t]) {
-          at[t] = pack_w((int)(at[t] >> 32) + (int)(w >> 32), (uint32_t)w);
-          word[mine[t]] = at[t];
-          moved = true;
-        }
+      if (row(t)) up[t] = word[(uint32_t)at[t]];
+#pragma unroll
+    for (int t = 0; t < kRows; ++t)
+      if (row(t) && (uint32_t)up[t] != (uint32_t)at[t]) {
+        at[t] = pack_w((int)(at[t] >> 32) + (int)(up[t] >> 32), (uint32_t)up[t]);
+        word[mine[t]] = at[t];
       }
-    if (!__syncthreads_or(moved)) break;
+    __syncthreads();
   }
   mytotal = wave_sum(mytotal);
   if (lane_id() == 0 && mytotal) atomicAdd(&total, mytotal);
-  bad = false;
+  bad = 0;
+  unsigned long long w[kPerThread], of[kPerThread];
+#pragma unroll
+  for (int t = 0; t < kPerThread; ++t)
+    if (t * kBaseThreads + wave0 < N) w[t] = word[tid + t * kBaseThreads];
+#pragma unroll
+  for (int t = 0; t < kPerThread; ++t)
+    if (t * kBaseThreads + wave0 < N) {
+      of[t] = w[t];
+      if ((uint32_t)w[t] & kSeen) of[t] = word[(uint32_t)w[t] ^ kSeen];
+      else w[t] = 0;
+    }
+  // (the word of a node that no walk came by leads to no head: the next node,
+  // kStop added to a head, or kEnd)
 #pragma unroll
   for (int t = 0; t < kPerThread; ++t) {
     const int j = tid + t * kBaseThreads;
     if (j >= N) continue;
-    unsigned long long w = word[j];
-    int v = (int)(w >> 32);
-    if (!is_splitter(j)) {
-      if (((int)(uint32_t)w & kSeen) == 0 || (uint32_t)w == ~0u) {
-        bad = true;  // no walk came by
-        w = pack_w(0, (uint32_t)head_base);
-      } else {
-        w = word[(int)(uint32_t)w & ~kSeen];
-        v += (int)(w >> 32);
-      }
-    }
-    bad |= !is_head((int)(uint32_t)w);
-    srank[j] = v;
+    bad |= !is_head((int)(uint32_t)of[t]);
+    srank[j] = (int)(of[t] >> 32) + (int)(w[t] >> 32);
   }
   if (bad) atomicOr(&ctl->err, kErrBase);
   __syncthreads();
@@ -2637,9 +2657,12 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
     const int top = p.levels;
     const int cap_prev = p.cap[top - 1];
     if (p.base_kind == 1) {
-      hipLaunchKernelGGL(L <= kBaseLists ? lr_base_walk : lr_base_lds, dim3(1),
-                         dim3(kBaseThreads), 0, stream, b.link[top],
-                         b.srank[top], b.ctl, top, Li, cap_prev);
+      if (L <= kBaseLists)
+        hipLaunchKernelGGL(lr_base_walk, dim3(kXcds + 1), dim3(kBaseThreads), 0, stream, b.link[top],
+                           b.srank[top], b.ctl, top, Li, cap_prev, (int)p.bound[top]);
+      else
+        hipLaunchKernelGGL(lr_base_lds, dim3(1), dim3(kBaseThreads), 0, stream, b.link[top],
+                           b.srank[top], b.ctl, top, Li, cap_prev);
     } else {
       const int g = grid_for(p.bound[top], 256, gcap);
       hipLaunchKernelGGL(wide_clear, dim3(g), dim3(256), 0, stream, b.wide_lnk, b.ctl, top, Li,

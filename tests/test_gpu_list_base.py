@@ -73,3 +73,16 @@ def test_malformed(pj, case):
     for spacing in (2, 8):
         pj.list_rank(dev(succ), spacing=spacing, status=st)
         assert int(st.item()) == pj.PJ_EBADLIST
+
+
+# 10240 nodes: one splitter per 4 ids up to there, per 8 beyond
+@pytest.mark.parametrize("n", [20_475, 20_476, 20_477, 20_478, 20_479, 20_480, 20_481, 20_483])
+def test_block_edges(pj, n):
+    succ = W.random_list(n, n)
+    st = torch.full((1,), 7, dtype=torch.int32, device="cuda")
+    got = pj.list_rank(dev(succ), spacing=2, status=st)
+    assert np.array_equal(got.cpu().numpy(), oracle.list_rank(succ))
+    assert int(st.item()) == pj.PJ_OK
+    succ[np.argsort(oracle.list_rank(succ))[n // 3]] = -1
+    pj.list_rank(dev(succ), spacing=2, status=st)
+    assert int(st.item()) == pj.PJ_EBADLIST
