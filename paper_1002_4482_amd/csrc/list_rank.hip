@@ -100,6 +100,8 @@ constexpr int kSlab = 256;
 constexpr int kXcds = 8;
 constexpr int kBinShift = 15;
 constexpr int kBinNodes = 1 << kBinShift;  // 128 KiB of ranks in LDS
+constexpr int kWordLongest = 1 << 20;      // (see lr_bin)
+constexpr int kBinShiftMin = 12;
 constexpr int kTileSlabs = 4;
 constexpr int kTileThreads = kTileSlabs * kSlab;
 constexpr int kTileBins = 2048;
@@ -116,7 +118,8 @@ struct RecArgs {
   int32_t* used;        // strips used of each slab
   int32_t* chunk_list;  // a batch: first list of each chunk
   int32_t* cursor;      // entries of each bin
-  uint2* ent;           // {node, rank}, kBinNodes per bin
+  void* ent;            // a bin's entries, one per node
+  int bin_shift;        // nodes of a bin, as a shift
   int group_slabs;      // slabs of a group (an XCD of a batch; all of one list)
   int log2B;            // splitter spacing
   int if_far;           // only if the head-find pass found the list not local
@@ -809,19 +812,38 @@ __global__ void __launch_bounds__(256) lr_walk_rec(WalkArgs a, RecArgs rec) {
   if (errbits) atomicOr(&ctl->err, errbits);
 }
 
-// Deals the recorded nodes to bins: entry {node, rank} of every node, where
-// rank = rank of the strip's sublist + place in it.  A bin's region of `ent`
-// holds one entry per node of the bin, which a valid input fills exactly.  A
-// tile of kTileSlabs slabs, a strip a thread, is sorted by bin in LDS, so that
+// Deals the recorded nodes to bins: an entry of node and rank for every node,
+// where rank = rank of the strip's sublist + place in it.  A bin's region of
+// `ent` holds one entry per node of the bin, which a valid input fills exactly.
+// A tile of kTileSlabs slabs, a strip a thread, is sorted by bin in LDS, so that
 // its entries reach a bin as one run.  kTileBins bins from the tile's lowest on
 // are sorted; entries past them (slabs of distant lists in one tile) go to
 // their bins one by one.
-template <bool kBatched, bool kToTail, bool kPaired>
+//
+// kWord: the entry is one word, rank << bin_shift | node's place in the bin.
+// Batches of lists of up to kWordLongest nodes take it, with bins of
+// 2^(32 - bits of the longest list's ranks) nodes.  lr_bin and lr_place move 4
+// bytes a node for the strips, 4 for the ranks and twice the entry, so the word
+// instead of a {node, rank} pair takes them from 1400 + 1264 us to 1310 + 629
+// (4096 lists of 2^6..2^20 nodes).  Beyond kWordLongest the bins are so small
+// that kTileBins of them no longer cover the lists of a tile (100 lists of
+// 2^17..2^20.9 nodes, 21 bits: lr_bin 217 us with pairs, 920 with words); one
+// list's ranks take up to 26 bits, and weights 32.
+template <bool kBatched, bool kToTail, bool kPaired, bool kWord = false>
 __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
                                                        const int32_t* __restrict__ srank,
                                                        const int64_t* __restrict__ off, int L,
                                                        int cap_here, LrCtl* ctl) {
-  __shared__ uint2 ent[kTileThreads * kStrip];
+  using Entry = std::conditional_t<kWord, uint32_t, uint2>;
+  __shared__ Entry ent[kTileThreads * kStrip];
+  __shared__ uint16_t bin_of[kWord ? kTileThreads * kStrip : 1];
+  Entry* const out = static_cast<Entry*>(rec.ent);
+  const int shift = kWord ? rec.bin_shift : kBinShift;
+  const int bin_nodes = 1 << shift;
+  const auto entry = [&](int node, int rank) {
+    if constexpr (kWord) return (uint32_t)rank << shift | (uint32_t)(node & (bin_nodes - 1));
+    else return make_uint2((unsigned)node, (unsigned)rank);
+  };
   __shared__ int hist[kTileBins], start[kTileBins], to[kTileBins];
   __shared__ int wsum[kTileThreads / kWave];
   __shared__ int low, total;
@@ -894,7 +916,7 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
     int least = INT32_MAX;
 #pragma unroll
     for (int t = 0; t < kStrip; ++t)
-      if (node[t] >= 0) least = min(least, node[t] >> kBinShift);
+      if (node[t] >= 0) least = min(least, node[t] >> shift);
     least = wave_min(least);
     if (lane_id() == 0) atomicMin(&low, least);
     __syncthreads();
@@ -903,14 +925,13 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
     for (int t = 0; t < kStrip; ++t) {
       pos[t] = -1;
       if (node[t] >= 0) {
-        const int b = (node[t] >> kBinShift) - lo;
+        const int b = (node[t] >> shift) - lo;
         if (b < kTileBins) {
           pos[t] = atomicAdd(&hist[b], 1);
         } else {
           const int at = atomicAdd(&rec.cursor[b + lo], 1);
-          if (at < kBinNodes)
-            rec.ent[((int64_t)(b + lo) << kBinShift) + at] =
-                make_uint2((unsigned)node[t], (unsigned)(value + place[t]));
+          if (at < bin_nodes)
+            out[((int64_t)(b + lo) << shift) + at] = entry(node[t], value + place[t]);
         }
       }
     }
@@ -948,47 +969,67 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < kStrip; ++t)
-      if (pos[t] >= 0)
-        ent[start[(node[t] >> kBinShift) - lo] + pos[t]] =
-            make_uint2((unsigned)node[t], (unsigned)(value + place[t]));
+      if (pos[t] >= 0) {
+        const int b = (node[t] >> shift) - lo;
+        const int e = start[b] + pos[t];
+        ent[e] = entry(node[t], value + place[t]);
+        if (kWord) bin_of[e] = (uint16_t)b;
+      }
     __syncthreads();
     for (int e = tid; e < total; e += kTileThreads) {
-      const uint2 v = ent[e];
-      const int b = (int)(v.x >> kBinShift) - lo;
+      const Entry v = ent[e];
+      int b;
+      if constexpr (kWord) b = bin_of[e];
+      else b = (int)(v.x >> shift) - lo;
       const int at = to[b] + e - start[b];
-      if (at < kBinNodes) rec.ent[((int64_t)(lo + b) << kBinShift) + at] = v;
+      if (at < bin_nodes) out[((int64_t)(lo + b) << shift) + at] = v;
     }
     __syncthreads();  // hist, start, to and ent are reused by the next tile
   }
   if (__ballot(bad) && lane_id() == 0) atomicOr(&ctl->err, kErrTotal);
 }
 
-// A bin's ranks put in order in LDS and written.
+// Ranks put in order in LDS and written, kBinNodes at a time (one bin or
+// several).
+template <bool kWord>
 __global__ void __launch_bounds__(kTileThreads) lr_place(RecArgs rec, int32_t* __restrict__ rank,
                                                          LrCtl* ctl) {
   __shared__ int32_t out[kBinNodes];
+  __shared__ int filled[kBinNodes >> kBinShiftMin];
+  using Entry = std::conditional_t<kWord, uint32_t, uint2>;
   const int N = ctl->lv[0].n;
   if (rec.if_far && !far_chosen(ctl, N)) return;
-  const int nbins = (int)(((int64_t)N + kBinNodes - 1) >> kBinShift);
-  for (int b = blockIdx.x; b < nbins; b += gridDim.x) {
-    const int64_t v0 = (int64_t)b << kBinShift;
+  const int shift = kWord ? rec.bin_shift : kBinShift;
+  const int nparts = (int)(((int64_t)N + kBinNodes - 1) >> kBinShift);
+  for (int p = blockIdx.x; p < nparts; p += gridDim.x) {
+    const int64_t v0 = (int64_t)p << kBinShift;
     const int size = (int)min<int64_t>(kBinNodes, N - v0);
-    const int filled = rec.cursor[b];
-    if (filled != size && threadIdx.x == 0) atomicOr(&ctl->err, kErrTotal);
-    const uint2* e = rec.ent + v0;
-    const int have = min(filled, kBinNodes);
-    constexpr int kIn = 8;  // entries in flight per thread
-    for (int q0 = threadIdx.x; q0 < have; q0 += kIn * kTileThreads) {
-      uint2 v[kIn];
+    const int bins = (size + (1 << shift) - 1) >> shift;
+    if ((int)threadIdx.x < bins) {
+      const int b = threadIdx.x;
+      const int f = rec.cursor[(v0 >> shift) + b];
+      filled[b] = f;
+      if (f != min(1 << shift, size - (b << shift))) atomicOr(&ctl->err, kErrTotal);
+    }
+    __syncthreads();
+    const Entry* e = static_cast<const Entry*>(rec.ent) + v0;
+    constexpr int kIn = kWord ? 16 : 8;  // entries in flight per thread
+    for (int q0 = threadIdx.x; q0 < size; q0 += kIn * kTileThreads) {
+      Entry v[kIn];
 #pragma unroll
       for (int u = 0; u < kIn; ++u) {
         const int q = q0 + u * kTileThreads;
-        if (q < have) v[u] = e[q];
+        if (q < size) v[u] = e[q];
       }
 #pragma unroll
       for (int u = 0; u < kIn; ++u) {
         const int q = q0 + u * kTileThreads;
-        if (q < have) out[v[u].x & (kBinNodes - 1)] = (int)v[u].y;
+        const int place = q & ((1 << shift) - 1);
+        if (q >= size || place >= filled[q >> shift]) continue;
+        if constexpr (kWord)
+          out[q - place + (v[u] & ((1u << shift) - 1))] = (int)(v[u] >> shift);
+        else
+          out[v[u].x & (kBinNodes - 1)] = (int)v[u].y;
       }
     }
     __syncthreads();
@@ -2123,6 +2164,8 @@ struct Plan {
   int kbits_far = 0;       // with these offset bits (packed form)
   int max_walk_far = 0;    // and this cut length
   int rec_grid = 0, rec_log2B = 0, rec_chunks = 0, rec_bins = 0, group_slabs = 0;
+  int bin_shift = 0;       // and deals them to bins of this size (see lr_bin),
+  bool word = false;       // in entries of one word
   int max_slabs = 0;       // > 0: level 0 records its walks (see lr_walk_rec)
   int64_t chosen = 0;      // > 0: level 0 uses this many caller-chosen splitters
 };
@@ -2288,7 +2331,9 @@ bool recorded_plan(const Plan& in_place, int64_t n0, int64_t L, int64_t max_size
       (int)((nodes / kStrip + pieces) / kSlab + 1 + 2 * (p.rec_grid / groups) * (256 / kWave));
   p.max_slabs = (int)(groups * p.group_slabs);
   p.rec_chunks = (int)((r + kWalkChunk - 1) / kWalkChunk);
-  p.rec_bins = (int)((n0 + kBinNodes - 1) >> kBinShift);
+  p.word = !single && !weighted && max_size <= kWordLongest;
+  p.bin_shift = p.word ? std::min(kBinShift, 32 - bits_for(max_size)) : kBinShift;
+  p.rec_bins = (int)((n0 + (1ll << p.bin_shift) - 1) >> p.bin_shift);
   *out = p;
   return true;
 }
@@ -2342,7 +2387,10 @@ size_t carve(const Plan& p, int64_t L, bool single, bool validate, bool want_sta
     take(b->rec.used, slabs);
     if (!single) take(b->rec.chunk_list, (size_t)p.rec_chunks + 1);
     take(b->rec.cursor, (size_t)p.rec_bins);
-    take(b->rec.ent, (size_t)p.rec_bins * kBinNodes);
+    uint32_t* ent = nullptr;
+    take(ent, ((size_t)p.rec_bins << p.bin_shift) * (p.word ? 1 : 2));
+    b->rec.ent = ent;
+    b->rec.bin_shift = p.bin_shift;
     if (p.paired) {
       take(b->rec.before, slabs * kSlab * kStrip / 4);
       b->state[0] = reinterpret_cast<int2*>(b->rec.ent);  // read before the bins are filled
@@ -2700,13 +2748,15 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
       const auto bin =
           pair ? (single ? lr_bin<false, false, true> : lr_bin<true, false, true>)
           : single ? (o.to_tail ? lr_bin<false, true, false> : lr_bin<false, false, false>)
+          : p.word ? (o.to_tail ? lr_bin<true, true, false, true> : lr_bin<true, false, false, true>)
                    : (o.to_tail ? lr_bin<true, true, false> : lr_bin<true, false, false>);
       const int cus = device_info().cus;
       hipLaunchKernelGGL(bin, dim3(cus / kXcds * kXcds), dim3(kTileThreads), 0, stream, b.rec,
                          (const int32_t*)b.srank[1], off, Li, p.cap[0], b.ctl);
       tm.mark("bin");
-      hipLaunchKernelGGL(lr_place, dim3(std::min(p.rec_bins, cus)), dim3(kTileThreads), 0, stream,
-                         b.rec, rank, b.ctl);
+      hipLaunchKernelGGL(p.word ? lr_place<true> : lr_place<false>,
+                         dim3((unsigned)std::min<int64_t>((n0 + kBinNodes - 1) >> kBinShift, cus)), dim3(kTileThreads),
+                         0, stream, b.rec, rank, b.ctl);
       tm.mark("place");
     }
     if (pair && (!recorded || b.rec.if_far))

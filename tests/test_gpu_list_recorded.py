@@ -130,3 +130,21 @@ def test_malformed(pj, case, batched):
         st = torch.full((1,), 7, dtype=torch.int32, device="cuda")
         pj.list_rank(dev(succ), status=st)
         assert int(st.item()) == pj.PJ_EBADLIST
+
+
+# entries of one word and of two: bins of 2^15 nodes up to lists of 2^17, then
+# smaller ones, pairs beyond 2^20
+@pytest.mark.parametrize("longest", [1 << 12, 1 << 17, (1 << 17) + 1, (1 << 19) + 5, 1 << 20,
+                                     (1 << 20) + 1, 1 << 21])
+@pytest.mark.parametrize("to_tail", [False, True])
+def test_entry_widths(pj, longest, to_tail):
+    sizes = [1, longest, 0, longest - 1, 4095, longest, 2] + [3000] * 400
+    succ, off = W.concat_lists([W.random_list(s, 31 + i) for i, s in enumerate(sizes)])
+    st = torch.full((len(sizes),), 7, dtype=torch.int32, device="cuda")
+    got = pj.list_rank_batched(dev(succ), dev(off), h_offsets=off, to_tail=to_tail, status=st)
+    bad, want = oracle.list_rank_batched(succ, off)
+    if to_tail:
+        want = np.repeat(np.diff(off), np.diff(off)) - 1 - want
+    assert bad.max() == 0
+    assert np.array_equal(got.cpu().numpy(), want)
+    assert (st.cpu().numpy() == pj.PJ_OK).all()
