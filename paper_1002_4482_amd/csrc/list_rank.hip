@@ -125,6 +125,14 @@ struct RecArgs {
   int if_far;           // only if the head-find pass found the list not local
 };
 
+// Where the first four nodes of a strip are, the next four kSlab words on: a
+// slab holds those of its strips side by side, so that the lanes of a wave move
+// whole lines (4096 lists of 2^6..2^20 nodes, strip after strip: walk 4280 us,
+// lr_bin 1300; side by side 4165 and 1240).
+__device__ __forceinline__ int64_t strip_word(int strip) {
+  return (int64_t)(strip / kSlab) * (kSlab * kStrip / 4) + strip % kSlab;
+}
+
 // ------------------------------------------------------------------ init
 __global__ void lr_init(LrCtl* ctl, int n0, unsigned long long* lsum, int32_t* ltails,
                         int32_t* lerr, int L, int64_t* off_single, RecArgs rec, int nbins) {
@@ -773,14 +781,16 @@ __global__ void __launch_bounds__(256) lr_walk_rec(WalkArgs a, RecArgs rec) {
     cursor += count;
     if (walks) {
       if (strip >= 0) {
+        int4* const to = rec.strips + strip_word(strip);
+        int4* const to_before = rec.before + strip_word(strip);
 #pragma unroll
         for (int t = 0; t < kStrip / 4; ++t)
-          rec.strips[(int64_t)strip * (kStrip / 4) + t] =
+          to[t * kSlab] =
               make_int4(node[4 * t], node[4 * t + 1], node[4 * t + 2], node[4 * t + 3]);
         if (kPaired)
 #pragma unroll
           for (int t = 0; t < kStrip / 4; ++t)
-            rec.before[(int64_t)strip * (kStrip / 4) + t] =
+            to_before[t * kSlab] =
                 make_int4(before[4 * t], before[4 * t + 1], before[4 * t + 2], before[4 * t + 3]);
         rec.head[strip] = make_int2(sid, k0);
       } else {
@@ -844,7 +854,7 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
     if constexpr (kWord) return (uint32_t)rank << shift | (uint32_t)(node & (bin_nodes - 1));
     else return make_uint2((unsigned)node, (unsigned)rank);
   };
-  __shared__ int hist[kTileBins], start[kTileBins], to[kTileBins];
+  __shared__ int hist[kTileBins], start[kTileBins];
   __shared__ int wsum[kTileThreads / kWave];
   __shared__ int low, total;
   const int N = ctl->lv[0].n;
@@ -856,7 +866,7 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
   const int taken = min(rec.ctl->taken[group], rec.group_slabs);
   bool bad = false;
   // the thread's strip of the tile at i0, read one tile ahead
-  int ahead[kStrip], ahead_before[kStrip];
+  int ahead[kStrip], ahead_strip = 0;
   int2 ahead_head = make_int2(-1, 0);
   const auto fetch = [&](int i0) {
     ahead_head = make_int2(-1, 0);
@@ -864,25 +874,18 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
     if (i < taken) {
       const int slab = group * rec.group_slabs + i;
       if (tid % kSlab < rec.used[slab]) {
-        const int64_t strip = (int64_t)slab * kSlab + tid % kSlab;
+        const int strip = slab * kSlab + tid % kSlab;
         ahead_head = rec.head[strip];
+        const int4* const from = rec.strips + strip_word(strip);
+        ahead_strip = strip;
 #pragma unroll
         for (int t = 0; t < kStrip / 4; ++t) {
-          const int4 v = rec.strips[strip * (kStrip / 4) + t];
+          const int4 v = from[t * kSlab];
           ahead[4 * t] = v.x;
           ahead[4 * t + 1] = v.y;
           ahead[4 * t + 2] = v.z;
           ahead[4 * t + 3] = v.w;
         }
-        if (kPaired)
-#pragma unroll
-          for (int t = 0; t < kStrip / 4; ++t) {
-            const int4 v = rec.before[strip * (kStrip / 4) + t];
-            ahead_before[4 * t] = v.x;
-            ahead_before[4 * t + 1] = v.y;
-            ahead_before[4 * t + 2] = v.z;
-            ahead_before[4 * t + 3] = v.w;
-          }
       }
     }
   };
@@ -898,7 +901,18 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
 #pragma unroll
     for (int t = 0; t < kStrip; ++t) {
       node[t] = known ? ahead[t] : -1;
-      place[t] = kPaired ? ahead_before[t] : kToTail ? -t : t;
+      if (!kPaired) place[t] = kToTail ? -t : t;
+    }
+    if (kPaired) {  // (not read a tile ahead: the registers do not last)
+      const int4* const from = rec.before + strip_word(ahead_strip);
+#pragma unroll
+      for (int t = 0; t < kStrip / 4; ++t) {
+        const int4 v = have ? from[t * kSlab] : make_int4(0, 0, 0, 0);
+        place[4 * t] = v.x;
+        place[4 * t + 1] = v.y;
+        place[4 * t + 2] = v.z;
+        place[4 * t + 3] = v.w;
+      }
     }
     int value = known ? srank[h.x] + (kPaired ? 0 : h.y) : 0;
     if (kToTail && known) {
@@ -913,14 +927,17 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
     if (tid == 0) low = INT32_MAX;
     for (int b = tid; b < kTileBins; b += kTileThreads) hist[b] = 0;
     __syncthreads();
-    int least = INT32_MAX;
+    int lo = 0;  // (one list has kTileBins bins at most)
+    if (kBatched) {
+      int least = INT32_MAX;
 #pragma unroll
-    for (int t = 0; t < kStrip; ++t)
-      if (node[t] >= 0) least = min(least, node[t] >> shift);
-    least = wave_min(least);
-    if (lane_id() == 0) atomicMin(&low, least);
-    __syncthreads();
-    const int lo = low;
+      for (int t = 0; t < kStrip; ++t)
+        if (node[t] >= 0) least = min(least, node[t] >> shift);
+      least = wave_min(least);
+      if (lane_id() == 0) atomicMin(&low, least);
+      __syncthreads();
+      lo = low;
+    }
 #pragma unroll
     for (int t = 0; t < kStrip; ++t) {
       pos[t] = -1;
@@ -936,8 +953,17 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
       }
     }
     __syncthreads();
-    // exclusive prefix of the counts, kTileBins / kTileThreads bins a thread
+    // The bins' regions are asked for here and needed after the sort (lanes on
+    // consecutive cursors).
     constexpr int kPer = kTileBins / kTileThreads;
+    int to[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int b = tid + q * kTileThreads, c = hist[b];
+      to[q] = 0;
+      if (c) to[q] = atomicAdd(&rec.cursor[lo + b], c);
+    }
+    // exclusive prefix of the counts, kPer bins a thread
     int cnt[kPer], sum = 0;
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
@@ -961,11 +987,6 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
       start[b] = excl;
       excl += cnt[q];
     }
-    // (lanes on consecutive cursors)
-    for (int b = tid; b < kTileBins; b += kTileThreads) {
-      const int c = hist[b];
-      if (c) to[b] = atomicAdd(&rec.cursor[lo + b], c);
-    }
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < kStrip; ++t)
@@ -975,16 +996,21 @@ __global__ void __launch_bounds__(kTileThreads) lr_bin(RecArgs rec,
         ent[e] = entry(node[t], value + place[t]);
         if (kWord) bin_of[e] = (uint16_t)b;
       }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {  // hist: from place in the tile to place in the bin
+      const int b = tid + q * kTileThreads;
+      hist[b] = to[q] - start[b];
+    }
     __syncthreads();
     for (int e = tid; e < total; e += kTileThreads) {
       const Entry v = ent[e];
       int b;
       if constexpr (kWord) b = bin_of[e];
       else b = (int)(v.x >> shift) - lo;
-      const int at = to[b] + e - start[b];
+      const int at = e + hist[b];
       if (at < bin_nodes) out[((int64_t)(lo + b) << shift) + at] = v;
     }
-    __syncthreads();  // hist, start, to and ent are reused by the next tile
+    __syncthreads();  // hist, start and ent are reused by the next tile
   }
   if (__ballot(bad) && lane_id() == 0) atomicOr(&ctl->err, kErrTotal);
 }
