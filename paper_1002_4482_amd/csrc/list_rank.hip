@@ -1373,61 +1373,32 @@ __device__ __forceinline__ unsigned long long pack_w(int hi, uint32_t lo) {
   return (unsigned long long)(unsigned)hi << 32 | lo;
 }
 
-// `bound` nodes may be read of link, whatever the level's node count.
-__global__ void __launch_bounds__(kBaseThreads) lr_base_walk(const int2* __restrict__ link,
-                                                             int32_t* __restrict__ srank,
-                                                             LrCtl* ctl, int level, int L,
-                                                             int cap_prev, int bound) {
-  if (blockIdx.x > 0) {
-    if (blockIdx.x % kXcds != 0) return;
-    const int nodes = min(bound, level_nodes(ctl, level, L, cap_prev));
-    int any = 0;  // one node per 128-byte line
-    for (int j = threadIdx.x * 16; j < nodes; j += 16 * kBaseThreads) any |= link[j].x;
-    asm volatile("" ::"v"(any));  // that the loads are kept
-    return;
-  }
-  // one word more, which lanes without a splitter take for theirs
-  __shared__ unsigned long long word[kMaxCutoff + 1];
-  __shared__ unsigned long long total;
+// The splitter of block b (in the last block it may lie past the nodes: then
+// there is none).
+__device__ __forceinline__ int base_splitter(int b, int log2b) {
+  return (b << log2b) + (int)(((unsigned)b % 65536 * 0x9E3779u >> 20) & ((1u << log2b) - 1));
+}
+
+// A node's first word; heads are ids head_base .. head_base + L - 1.
+__device__ __forceinline__ unsigned long long base_word(int to, bool end, int weight, int log2b,
+                                                        int head_base, int L) {
+  const bool stop = end | ((unsigned)(to - head_base) < (unsigned)L) |
+                    (base_splitter(to >> log2b, log2b) == to);
+  return pack_w(weight, (end ? kEnd : to) | (stop ? kStop : 0));
+}
+
+// Ranks the N nodes whose first words lie in word[] (before a barrier) and
+// hands each to emit(node, rank).  word[kMaxCutoff] is taken for their splitter
+// by lanes without one.  Returns whether this thread saw that they are no L
+// lists from those heads.
+template <class Emit>
+__device__ __forceinline__ int base_rank(unsigned long long* word, int N, int log2b, int head_base,
+                                         int L, Emit emit) {
   const int tid = threadIdx.x;
   // the wave's first row entry: rows it has no part in are skipped as a whole
   const int wave0 = __builtin_amdgcn_readfirstlane(tid & ~(kWave - 1));
-  int2 in[kPerThread];  // the first rows while the node count is on its way
-  const auto read = [&](int t, int limit) {
-    const int j = tid + t * kBaseThreads;
-    in[t] = j < limit ? link[j] : make_int2(-1, 0);
-  };
-#pragma unroll
-  for (int t = 0; t < kEarlyRows; ++t) read(t, bound);
-  const int N = level_nodes(ctl, level, L, cap_prev);
-#pragma unroll
-  for (int t = kEarlyRows; t < kPerThread; ++t) read(t, min(N, bound));
-  const int head_base = ctl->lv[level - 1].r;
-  if (tid == 0) total = 0ull;
-  if (N > min(kMaxCutoff, bound) || head_base + L > N) {
-    if (tid == 0) atomicOr(&ctl->err, kErrBase);
-    return;
-  }
-  const int log2b = N <= kBaseBlock4 ? 2 : 3;
-  // (in the last block it may lie past the nodes: then there is none)
-  const auto block_splitter = [&](int b) {
-    return (b << log2b) + (int)(((unsigned)b % 65536 * 0x9E3779u >> 20) & ((1u << log2b) - 1));
-  };
   const auto is_head = [&](int x) { return (unsigned)(x - head_base) < (unsigned)L; };
   int bad = 0;
-  unsigned long long mytotal = 0;
-#pragma unroll
-  for (int t = 0; t < kPerThread; ++t)
-    if (t * kBaseThreads + wave0 < N) {
-      const int j = tid + t * kBaseThreads;
-      const int to = j < N ? in[t].x : -1;
-      const int weight = j < N ? in[t].y : 0;
-      const bool end = (unsigned)to >= (unsigned)N;
-      const bool stop = end | is_head(to) | (block_splitter(to >> log2b) == to);
-      bad |= end & (to != -1);
-      mytotal += (unsigned)weight;
-      word[j] = pack_w(weight, (end ? kEnd : to) | (stop ? kStop : 0));
-    }
   __syncthreads();
   const int blocks = (N + (1 << log2b) - 1) >> log2b;
   // Walks: a lane takes a splitter, follows its successors to the next one and
@@ -1448,9 +1419,9 @@ __global__ void __launch_bounds__(kBaseThreads) lr_base_walk(const int2* __restr
         const int slot = next + lanes_below(idle);
         next += (int)__popcll(idle);
         if (own < 0 && slot < last) {
-          const int at = slot < blocks ? block_splitter(slot) : head_base + slot - blocks;
+          const int at = slot < blocks ? base_splitter(slot, log2b) : head_base + slot - blocks;
           // (a head may be its block's splitter)
-          if (slot < blocks ? at < N : block_splitter(at >> log2b) != at) {
+          if (slot < blocks ? at < N : base_splitter(at >> log2b, log2b) != at) {
             own = x = at;
             acc = 0;
             w = word[x];
@@ -1492,9 +1463,9 @@ __global__ void __launch_bounds__(kBaseThreads) lr_base_walk(const int2* __restr
   for (int t = 0; t < kRows; ++t)
     if (row(t)) {
       const int b = tid + t * kBaseThreads, h = head_base + tid;
-      const int x = t < kRows - 1 ? block_splitter(b) : h;
+      const int x = t < kRows - 1 ? base_splitter(b, log2b) : h;
       const bool is = t < kRows - 1 ? b < blocks && x < N
-                                    : tid < L && block_splitter(h >> log2b) != h;
+                                    : tid < L && base_splitter(h >> log2b, log2b) != h;
       mine[t] = is ? x : kNone;
       at[t] = is ? word[x] : pack_w(0, kEnd);
     }
@@ -1521,7 +1492,6 @@ __global__ void __launch_bounds__(kBaseThreads) lr_base_walk(const int2* __restr
       bad = 1;  // a head that is no list's
       word[mine[t]] = at[t] = pack_w(0, (uint32_t)mine[t]);
     }
-  if (bad) atomicOr(&ctl->err, kErrBase);
   __syncthreads();
   for (int span = 1; span < blocks + L; span *= 2) {
     unsigned long long up[kRows];
@@ -1536,9 +1506,6 @@ __global__ void __launch_bounds__(kBaseThreads) lr_base_walk(const int2* __restr
       }
     __syncthreads();
   }
-  mytotal = wave_sum(mytotal);
-  if (lane_id() == 0 && mytotal) atomicAdd(&total, mytotal);
-  bad = 0;
   unsigned long long w[kPerThread], of[kPerThread];
 #pragma unroll
   for (int t = 0; t < kPerThread; ++t)
@@ -1557,11 +1524,151 @@ __global__ void __launch_bounds__(kBaseThreads) lr_base_walk(const int2* __restr
     const int j = tid + t * kBaseThreads;
     if (j >= N) continue;
     bad |= !is_head((int)(uint32_t)of[t]);
-    srank[j] = (int)(of[t] >> 32) + (int)(w[t] >> 32);
+    emit(j, (int)(of[t] >> 32) + (int)(w[t] >> 32));
   }
+  return bad;
+}
+
+// Reads one node per 128-byte line, to have them in this XCD's L2.
+template <class T>
+__device__ __forceinline__ void read_ahead(const T* p, int n) {
+  constexpr int kPerLine = 128 / sizeof(T);
+  int any = 0;
+  for (int j = threadIdx.x * kPerLine; j < n; j += kPerLine * kBaseThreads)
+    any |= *reinterpret_cast<const int*>(p + j);
+  asm volatile("" ::"v"(any));  // that the loads are kept
+}
+
+// `bound` nodes may be read of link, whatever the level's node count.
+__global__ void __launch_bounds__(kBaseThreads) lr_base_walk(const int2* __restrict__ link,
+                                                             int32_t* __restrict__ srank,
+                                                             LrCtl* ctl, int level, int L,
+                                                             int cap_prev, int bound) {
+  if (blockIdx.x > 0) {
+    if (blockIdx.x % kXcds == 0)
+      read_ahead(link, min(bound, level_nodes(ctl, level, L, cap_prev)));
+    return;
+  }
+  __shared__ unsigned long long word[kMaxCutoff + 1];
+  __shared__ unsigned long long total;
+  const int tid = threadIdx.x;
+  const int wave0 = __builtin_amdgcn_readfirstlane(tid & ~(kWave - 1));
+  int2 in[kPerThread];  // the first rows while the node count is on its way
+  const auto read = [&](int t, int limit) {
+    const int j = tid + t * kBaseThreads;
+    in[t] = j < limit ? link[j] : make_int2(-1, 0);
+  };
+#pragma unroll
+  for (int t = 0; t < kEarlyRows; ++t) read(t, bound);
+  const int N = level_nodes(ctl, level, L, cap_prev);
+#pragma unroll
+  for (int t = kEarlyRows; t < kPerThread; ++t) read(t, min(N, bound));
+  const int head_base = ctl->lv[level - 1].r;
+  if (tid == 0) total = 0ull;
+  if (N > min(kMaxCutoff, bound) || head_base + L > N) {
+    if (tid == 0) atomicOr(&ctl->err, kErrBase);
+    return;
+  }
+  const int log2b = N <= kBaseBlock4 ? 2 : 3;
+  int bad = 0;
+  unsigned long long mytotal = 0;
+#pragma unroll
+  for (int t = 0; t < kPerThread; ++t)
+    if (t * kBaseThreads + wave0 < N) {
+      const int j = tid + t * kBaseThreads;
+      const int to = j < N ? in[t].x : -1;
+      const int weight = j < N ? in[t].y : 0;
+      const bool end = (unsigned)to >= (unsigned)N;
+      bad |= end & (to != -1);
+      mytotal += (unsigned)weight;
+      word[j] = base_word(to, end, weight, log2b, head_base, L);
+    }
+  bad |= base_rank(word, N, log2b, head_base, L, [&](int j, int rank) { srank[j] = rank; });
+  mytotal = wave_sum(mytotal);
+  if (lane_id() == 0 && mytotal) atomicAdd(&total, mytotal);
   if (bad) atomicOr(&ctl->err, kErrBase);
   __syncthreads();
   if (tid == 0) ctl->base_total = total;
+}
+
+// One whole list of at most kMaxCutoff nodes, weighted or not, in the same way
+// and in one kernel: the head is what the sum of the successors leaves out.
+// succ is read before any rank is written (in place allowed).  Bound as
+// lr_base_walk is, and by the call itself below 2000 nodes.  Unweighted lists of
+// up to kOneList nodes are left to lr_lds, whose jumps need no head and no walks
+// (a call of 2000 nodes 11.9 us here, 10.4 there; 4096: 12.8 both; 6000: 14.3
+// and 15.5; 16384: 21.1 and 28.1).  Weighted lists took a kernel to clear two
+// words and one that jumped over every node with weights and links apart: 28 us
+// for 100 to 2000 nodes, 71.5 for 16383, and here 10.8 to 11.8, and 21.2.
+constexpr int kOneList = 4096;
+
+__global__ void __launch_bounds__(kBaseThreads) lr_one_lds(const int32_t* succ,
+                                                           const int32_t* __restrict__ weight,
+                                                           int n, int to_tail, int32_t* rank,
+                                                           int32_t* lerr, int32_t* status) {
+  if (blockIdx.x > 0) {
+    if (blockIdx.x % kXcds == 0) {
+      read_ahead(succ, n);
+      if (weight) read_ahead(weight, n);
+    }
+    return;
+  }
+  __shared__ unsigned long long word[kMaxCutoff + 1];
+  __shared__ unsigned long long sum;
+  __shared__ int tails, wrong;
+  const int tid = threadIdx.x;
+  const int wave0 = __builtin_amdgcn_readfirstlane(tid & ~(kWave - 1));
+  int to[kPerThread], w[kPerThread];
+#pragma unroll
+  for (int t = 0; t < kPerThread; ++t) {
+    const int j = tid + t * kBaseThreads;
+    to[t] = j < n ? succ[j] : -1;
+    w[t] = j < n ? weight ? weight[j] : 1 : 0;
+  }
+  if (tid == 0) {
+    sum = 0;
+    tails = wrong = 0;
+  }
+  __syncthreads();
+  {
+    unsigned long long mine = 0;
+    int ends = 0, bad = 0;
+#pragma unroll
+    for (int t = 0; t < kPerThread; ++t) {
+      const int j = tid + t * kBaseThreads;
+      if (to[t] == j) to[t] = -1;
+      ends += j < n && to[t] == -1;
+      bad |= to[t] < -1 || to[t] >= n;
+      mine += to[t] > 0 ? to[t] : 0;
+    }
+    mine = wave_sum(mine);
+    ends = wave_sum(ends);
+    if (lane_id() == 0) {
+      atomicAdd(&sum, mine);
+      atomicAdd(&tails, ends);
+    }
+    if (bad) wrong = 1;
+  }
+  __syncthreads();
+  const long long head = (long long)n * (n - 1) / 2 - (long long)sum;
+  int bad = tails != 1 || wrong || head < 0 || head >= n;
+  if (!bad) {
+    const int log2b = n <= kBaseBlock4 ? 2 : 3;
+#pragma unroll
+    for (int t = 0; t < kPerThread; ++t)
+      if (t * kBaseThreads + wave0 < n)
+        word[tid + t * kBaseThreads] =
+            base_word(to[t], to[t] == -1, w[t], log2b, (int)head, 1);
+    bad = base_rank(word, n, log2b, (int)head, 1,
+                    [&](int j, int r) { rank[j] = to_tail ? n - 1 - r : r; });
+    if (bad) wrong = 1;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    const bool ok = tails == 1 && !wrong && head >= 0 && head < n;
+    if (status) status[0] = ok ? PJ_OK : PJ_EBADLIST;
+    if (lerr) lerr[0] = ok ? 0 : kErrBase;
+  }
 }
 
 // ---------------------------------------------------- base: device-wide
@@ -1968,7 +2075,7 @@ __global__ void __launch_bounds__(kThreads) lr_lds(const int32_t* succ, int n,
   }
 }
 
-// Weighted: a whole batch of at most kMaxCutoff nodes in one workgroup,
+// Weighted batches: a whole batch of at most kMaxCutoff nodes in one workgroup,
 // predecessor links in LDS and pointer jumping along them, a node's own term
 // being its predecessor's weight.  succ is read before any rank is written (in
 // place allowed).
@@ -2441,8 +2548,16 @@ size_t carve(const Plan& p, int64_t L, bool single, bool validate, bool want_sta
 // Lists ranked in LDS (see lr_lds).  The smaller instance lets eight workgroups
 // share a CU.  A workgroup's block of nodes leaves room for the longest list to
 // run over its end, or, for lists over half the capacity, is half the capacity.
-int launch_lds(const int32_t* succ, int64_t n, int64_t max_size, const int64_t* d_off, int64_t L,
-               int32_t* rank, int to_tail, int32_t* lerr, int32_t* status, hipStream_t stream) {
+// One list of more than kOneList nodes, or weighted, goes to lr_one_lds.
+int launch_lds(const int32_t* succ, const int32_t* weight, int64_t n, int64_t max_size,
+               const int64_t* d_off, int64_t L, int32_t* rank, int to_tail, int32_t* lerr,
+               int32_t* status, hipStream_t stream) {
+  if (!d_off && (weight || n > kOneList)) {
+    hipLaunchKernelGGL(lr_one_lds, dim3(kXcds + 1), dim3(kBaseThreads), 0, stream, succ, weight,
+                       (int)n, to_tail, rank, lerr, status);
+    PJ_HIP(hipGetLastError());
+    return PJ_OK;
+  }
   constexpr int kSmallCap = 4096;
   const bool small = d_off && max_size <= kSmallCap;
   const int cap = small ? kSmallCap : kMaxCutoff;
@@ -2536,10 +2651,11 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
   add_far_spacing(p, n0, L, far_spacing, o.max_walk);
   Buffers b;
   size_t need = carve(p, L, single, o.validate != 0, want_status, nullptr, &b);
-  if (p.small && !weight && n0 > 0 && !o.validate && !(user && user->stats)) {
+  if (p.small && (!weight || single) && n0 > 0 && !o.validate && !(user && user->stats)) {
     // one kernel, which also writes the statuses: no workspace, no init
     if (o.workspace && o.workspace_bytes < need) return PJ_EINVAL;
-    return launch_lds(succ, n0, max_size, d_off, L, rank, o.to_tail, nullptr, o.d_status, stream);
+    return launch_lds(succ, weight, n0, max_size, d_off, L, rank, o.to_tail, nullptr, o.d_status,
+                      stream);
   }
   Workspace ws;
   // the recorded walk where its strips fit the caller's workspace or the pool
@@ -2617,12 +2733,13 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
     }
     tm.mark("wyllie_final");
   } else if (n0 > 0 && p.small) {
-    if (weight) {
+    if (weight && !single) {
       hipLaunchKernelGGL(lr_small_weighted, dim3(1), dim3(kBaseThreads), 0, stream, succ, weight,
                          off, Li, n, rank, b.ltails, b.lerr);
       check_tails = true;
     } else {
-      PJ_TRY(launch_lds(succ, n0, max_size, d_off, L, rank, o.to_tail, b.lerr, nullptr, stream));
+      PJ_TRY(launch_lds(succ, weight, n0, max_size, d_off, L, rank, o.to_tail, b.lerr, nullptr,
+                        stream));
     }
     tm.mark("small");
   } else if (n0 > 0) {
