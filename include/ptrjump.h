@@ -31,7 +31,9 @@
  *    hold fewer than 2^31 nodes or vertices.
  *  - Temporary device memory is taken stream-ordered from the device's memory
  *    pool (hipMallocAsync / hipFreeAsync) unless the caller passes a workspace
- *    of at least *_workspace_bytes() bytes in opts->workspace.
+ *    of at least *_workspace_bytes() bytes in opts->workspace.  Calls that need
+ *    at most 1 MiB share up to 16 blocks of that size, kept between calls and
+ *    given back by pj_graph_cache_clear().
  */
 #ifndef PTRJUMP_H
 #define PTRJUMP_H
@@ -249,7 +251,7 @@ size_t pj_list_rank_weighted_workspace_bytes(int64_t total_nodes, int64_t L,
  * largest) leaves the captured plan valid.  Not used together with
  * opts->stats or with validate and no d_status.  The cache holds up to 8
  * graphs; pj_graph_cache_clear() frees them all (it synchronises the
- * device).
+ * device), and the small workspaces kept between calls.
  */
 void pj_graph_cache_clear(void);
 

@@ -335,6 +335,7 @@ void pj_graph_cache_clear(void) {
     pj::g_graphs.clear();
   }
   pj::cc_graph_cache_clear();
+  pj::drop_kept_workspaces();
 }
 
 }  // extern "C"

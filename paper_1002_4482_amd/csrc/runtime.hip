@@ -62,6 +62,126 @@ int persistent_grid(const void* kernel, int block, size_t lds_bytes) {
   return grid;
 }
 
+// ------------------------------------------------------- kept workspaces
+// Small workspaces are kept between calls: allocating and freeing one from the
+// stream-ordered pool takes the host 25 us, and a call on 17000 to 70000 nodes
+// keeps the device busy for as long (one list of 17000 nodes: 50 us a call, 25 us
+// with the block kept).  Larger ones belong to calls that the device bounds, and
+// go back to the pool.
+//
+// A call takes a block out of the list, so that no other call has it, and puts
+// it back with an event recorded behind its last kernel; the next one has its
+// stream wait for that event, whichever stream that is.  It looks for the block
+// its own stream used last, so that streams do not wait for each other, then
+// takes a new one, and the one longest unused when the list is full.  At most
+// kKeptBlocks are held, from a pool of their own per device;
+// pj_graph_cache_clear gives them back.  A stream that is being captured takes
+// none: its kernels run later.
+namespace {
+
+constexpr size_t kKeptBytes = size_t(1) << 20;
+constexpr size_t kKeptBlocks = 16;
+
+struct KeptBlock {
+  int device;
+  char* base;
+  hipEvent_t done;
+  hipStream_t stream;  // of its last call (to choose by; `done` orders)
+};
+
+std::mutex g_kept_mu;
+std::vector<KeptBlock> g_kept;
+
+hipMemPool_t kept_pool(int device) {  // (g_kept_mu held)
+  static std::unordered_map<int, hipMemPool_t> pools;
+  auto it = pools.find(device);
+  if (it != pools.end()) return it->second;
+  hipMemPoolProps props = {};
+  props.allocType = hipMemAllocationTypePinned;
+  props.location.type = hipMemLocationTypeDevice;
+  props.location.id = device;
+  hipMemPool_t pool = nullptr;
+  if (hipMemPoolCreate(&pool, &props) != hipSuccess) {
+    (void)hipGetLastError();
+    pool = nullptr;
+  }
+  return pools[device] = pool;
+}
+
+// Frees a block behind the kernels that still use it.
+void drop_kept(const KeptBlock& k, hipStream_t stream) {
+  (void)hipFreeAsync(k.base, stream);
+  (void)hipEventDestroy(k.done);
+}
+
+bool take_kept(Workspace& ws, hipStream_t stream) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return false;
+  }
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess) return false;
+  KeptBlock k = {device, nullptr, nullptr, stream};
+  hipMemPool_t pool = nullptr;
+  {
+    std::lock_guard<std::mutex> lk(g_kept_mu);
+    auto at = g_kept.end();
+    for (auto i = g_kept.begin(); i != g_kept.end(); ++i)
+      if (i->device == device && (i->stream == stream || (g_kept.size() >= kKeptBlocks &&
+                                                          at == g_kept.end())))
+        at = i;
+    if (at != g_kept.end()) {
+      k = *at;
+      g_kept.erase(at);
+    } else {
+      pool = kept_pool(device);
+    }
+  }
+  if (k.base) {
+    if (hipStreamWaitEvent(stream, k.done, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      (void)hipEventSynchronize(k.done);
+    }
+  } else {
+    void* p = nullptr;
+    if (!pool || hipEventCreateWithFlags(&k.done, hipEventDisableTiming) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    if (hipMallocFromPoolAsync(&p, kKeptBytes, pool, stream) != hipSuccess) {
+      (void)hipGetLastError();
+      (void)hipEventDestroy(k.done);
+      return false;
+    }
+    k.base = static_cast<char*>(p);
+  }
+  ws.base = k.base;
+  ws.size = kKeptBytes;
+  ws.owned = true;
+  ws.kept = k.done;
+  ws.device = device;
+  return true;
+}
+
+}  // namespace
+
+void drop_kept_workspaces() {
+  std::vector<KeptBlock> all;
+  {
+    std::lock_guard<std::mutex> lk(g_kept_mu);
+    all.swap(g_kept);
+  }
+  int device = 0;
+  if (all.empty() || hipGetDevice(&device) != hipSuccess) return;
+  for (const KeptBlock& k : all) {
+    (void)hipSetDevice(k.device);
+    (void)hipEventSynchronize(k.done);
+    drop_kept(k, nullptr);
+  }
+  (void)hipSetDevice(device);
+}
+
 int workspace_acquire(Workspace& ws, size_t bytes, const pj_opts* opts, hipStream_t stream) {
   ws.used = 0;
   ws.stream = stream;
@@ -72,6 +192,7 @@ int workspace_acquire(Workspace& ws, size_t bytes, const pj_opts* opts, hipStrea
     ws.owned = false;
     return PJ_OK;
   }
+  if (bytes <= kKeptBytes && take_kept(ws, stream)) return PJ_OK;
   static std::once_flag pool_once;
   std::call_once(pool_once, [] {
     int ndev = 0;
@@ -97,12 +218,30 @@ int workspace_acquire(Workspace& ws, size_t bytes, const pj_opts* opts, hipStrea
   return PJ_OK;
 }
 
+Workspace::~Workspace() { (void)workspace_release(*this); }
+
 int workspace_release(Workspace& ws) {
-  if (ws.owned && ws.base) {
-    PJ_HIP(hipFreeAsync(ws.base, ws.stream));
-  }
+  const bool owned = ws.owned && ws.base;
+  char* const base = ws.base;
+  const KeptBlock k = {ws.device, base, ws.kept, ws.stream};
   ws.base = nullptr;
   ws.owned = false;
+  ws.kept = nullptr;
+  if (!owned) return PJ_OK;
+  if (!k.done) {
+    PJ_HIP(hipFreeAsync(base, ws.stream));
+    return PJ_OK;
+  }
+  if (hipEventRecord(k.done, ws.stream) == hipSuccess) {
+    std::lock_guard<std::mutex> lk(g_kept_mu);
+    if (g_kept.size() < kKeptBlocks) {
+      g_kept.push_back(k);
+      return PJ_OK;
+    }
+  } else {
+    (void)hipGetLastError();
+  }
+  drop_kept(k, ws.stream);
   return PJ_OK;
 }
 
