@@ -18,10 +18,14 @@
 //   * the splitter lists (one per input list, head = its virtual splitter)
 //     form level l+1, weighted by sublist length, and are ranked the same way
 //     (the recursion replacing the paper's single-block RS4) until a level is
-//     small enough for one workgroup, which ranks it in LDS by pointer
-//     jumping (the paper's single-kernel Wyllie);
+//     small enough for one workgroup, which ranks it in LDS (lr_base_walk, or
+//     the paper's single-kernel Wyllie for many lists, lr_base_lds);
 //   * expand (the paper's RS5): rank[x] = rank of its splitter + its weight
 //     offset, a coalesced pass per level.
+// Long lists that are not local, and large batches of shorter ones, record
+// level 0's walks instead of writing over the nodes, and deal the records to
+// the ranks (lr_walk_rec, lr_bin, lr_place).  Lists that fit LDS are ranked
+// there by one kernel (lr_lds, lr_one_lds).
 // The rank counted here is the distance from the head; the paper's RS5
 // subtracts from the splitter rank because it counts toward the tail.
 #include <algorithm>
