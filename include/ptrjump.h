@@ -54,7 +54,7 @@ typedef struct ihipStream_t *pj_stream_t;
 #define PJ_ENOMEM (-2)    /* device memory could not be obtained */
 #define PJ_EHIP (-3)      /* a HIP runtime call failed (see pj_last_hip_error) */
 #define PJ_EBADLIST (-4)  /* the successor array is not exactly one list over the instance */
-#define PJ_ENOCONV (-5)   /* components did not converge within the round guard */
+#define PJ_ENOCONV (-5)   /* components did not converge (not returned: there are no rounds) */
 #define PJ_EBUDGET (-6)   /* serving: request larger than the whole HBM budget */
 #define PJ_ENOTFOUND (-7) /* serving: unknown request id */
 #define PJ_EBUSY (-8)     /* serving: request not finished yet (poll again) */
@@ -65,7 +65,7 @@ typedef struct ihipStream_t *pj_stream_t;
 #define PJ_ALGO_AUTO 0        /* tuned choice (ruling set for lists, SV for components) */
 #define PJ_ALGO_WYLLIE 1      /* list ranking by pointer jumping, ceil(log2 n) device-wide rounds */
 #define PJ_ALGO_RULING_SET 2  /* list ranking by random splitters with recursive splitter ranking */
-#define PJ_ALGO_SV 3          /* components: Shiloach-Vishkin hook and shortcut */
+#define PJ_ALGO_SV 3          /* components: hook and shortcut (Shiloach-Vishkin's family) */
 
 /* Level-0 state layout of the ruling set (pj_opts.level0_state). */
 #define PJ_STATE_AUTO 0      /* packed into the output array when the id space allows */
@@ -84,7 +84,8 @@ typedef struct pj_opts {
                                  consecutive node ids (power of two, 2..65536);
                                  zero: n / 2^20 rounded down to a power of
                                  two, within 8..256 for one list and 8..64
-                                 for a batch (a single list of >= 2^24 nodes
+                                 for a batch, 32 at least for a batch of 2^20
+                                 nodes or more (a single list of >= 2^24 nodes
                                  keeps 8 when most successors are local) */
     int32_t spacing_up;       /* ruling set, recursion levels: same meaning
                                  (zero: 4) */
@@ -186,7 +187,10 @@ int pj_list_rank_batched_ex(const int32_t *succ, const int64_t *offsets, int64_t
                             int32_t *rank, const pj_opts *opts, pj_stream_t stream);
 
 /* Bytes of workspace a call with these sizes needs (L = 1: enough for both the
- * plain call and a batched call holding one list). */
+ * plain call and a batched call holding one list).  One list of 11 * 2^20 to
+ * 2^26 nodes, and a batch of 2^20 nodes or more whose lists have at most 2^21,
+ * use 12 to 20 bytes per node beyond that, and run faster, where the library
+ * allocates or opts->workspace is that much larger. */
 size_t pj_list_rank_workspace_bytes(int64_t total_nodes, int64_t L, const pj_opts *opts);
 
 /*
