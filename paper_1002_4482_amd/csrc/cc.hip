@@ -30,15 +30,14 @@
 namespace pj {
 namespace {
 
-constexpr int kFlatHops = 24;   // parent steps of one vertex in one shortcut pass
-constexpr int kMaxFlat = 3 * 7; // shortcut passes: three times, and 25^7 > 2^31
+constexpr int kFlatHops = 24;   // parent steps of a vertex in cc_flatten between its stores
+constexpr int kFlatPer = 4;     // vertices of a thread in cc_flatten
 
 constexpr int kClasses = 255;
 
 struct CcCtl {
   int32_t err;
-  int32_t steps;                // longest chain of parent steps of a shortcut pass
-  int32_t more[kMaxFlat];       // shortcut pass i left vertices short of their root
+  int32_t steps;                // longest chain of parent steps of a shortcut, up to kFlatHops
   int32_t classes;              // numbered parents (cc_class_pick), 0: not used
   int32_t parents[kClasses];
 };
@@ -305,32 +304,69 @@ __global__ void __launch_bounds__(256) cc_hook_rest(const int32_t* __restrict__ 
     hook_rest<false>(src, dst, m, n, D, cls, stride, units, ctl, queue, &queued);
 }
 
-// Shortcut: D[v] <- its root, or the ancestor kFlatHops + 1 steps up.  A pass
-// divides the depth of every tree by kFlatHops + 1 at least (the reads return
-// values no older than the kernel's start), so ceil(log25 n) passes flatten any
-// forest; hooks leave depths far below 24, and a pass that leaves nothing over
-// makes the later ones return at once.
-__global__ void __launch_bounds__(256) cc_flatten(int32_t* D, int n, CcCtl* ctl, int pass,
-                                                  int if_more) {
-  if (if_more && ctl->more[pass - 1] == 0) return;
-  const int stride = gridDim.x * blockDim.x;
+// Shortcut: D[v] <- its root, in one pass whatever the depth.  Hooks leave trees
+// far less than kFlatHops deep, and then a vertex climbs to its root.  From a
+// deeper one it publishes, every kFlatHops steps, how far it has come, so that
+// the vertices under it skip those steps: a parent's id is smaller than its
+// child's and vertices are taken in ascending order, so what is above a vertex
+// is flat already or climbs at the same time, and the depth left is divided by
+// kFlatHops + 1 while one vertex takes kFlatHops steps.  The order is the
+// workgroups', each with a run of vertices: with a stride over the grid the
+// first ones would reach vertices of workgroups that wait for them to end, and
+// climb link by link (a path of 2^22 ids in order: 347 ms).  (Climbing stops at
+// the root even if none of those stores is seen.)  Bound by the reads of parents;
+// in passes of kFlatHops steps, most of which found nothing left, a launch each,
+// three shortcuts of a solve took 68 us of 300000 vertices and 112 of 10^6, and
+// take 36 and 46 here (whole solves 165 -> 130 and 296 -> 230 us).  Four vertices a
+// thread, one by one: with two there is less above that is flat already (10^6
+// 252 us), with six too few lanes in small graphs; only deep ones climb side by
+// side (a path of 2^20 ids in order, doubled: 554 us, one by one 792).
+__global__ void __launch_bounds__(256) cc_flatten(int32_t* D, int n, CcCtl* ctl) {
+  const int64_t v0 = (int64_t)blockIdx.x * (256 * kFlatPer) + threadIdx.x;
+  int up[kFlatPer];  // of the deep vertices: the ancestor reached
   int most = 0;
-  bool more = false;
-  for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
+  bool deep = false;
+#pragma unroll
+  for (int t = 0; t < kFlatPer; ++t) {  // one by one: the later find flat trees above
+    const int64_t v = v0 + t * 256;
+    up[t] = -1;
+    if (v >= n) continue;
     const int p0 = D[v];
     int p = p0, h = 0;
-    for (; h < kFlatHops; ++h) {
+    for (; h < kFlatHops; ++h) {  // (plain reads: most lanes end at the same few roots)
       const int g = D[p];
       if (g == p) break;
       p = g;
     }
-    if (p != p0) D[v] = p;
-    more |= h == kFlatHops;
     most = max(most, h);
+    if (h == kFlatHops) {
+      publish(&D[v], p);
+      up[t] = p;
+      deep = true;
+    } else if (p != p0) {
+      D[v] = p;
+    }
+  }
+  while (deep) {  // side by side
+    bool left = true;
+    for (int h = 0; h < kFlatHops && left; ++h) {
+      int g[kFlatPer];
+#pragma unroll
+      for (int t = 0; t < kFlatPer; ++t) g[t] = up[t] >= 0 ? load_coherent(&D[up[t]]) : -1;
+      left = false;
+#pragma unroll
+      for (int t = 0; t < kFlatPer; ++t) {
+        left |= g[t] != up[t];
+        up[t] = g[t];
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < kFlatPer; ++t)
+      if (up[t] >= 0) publish(&D[v0 + t * 256], up[t]);
+    deep = left;
   }
   most = -wave_min(-most);
   if (lane_id() == 0 && most > 1 && load_coherent(&ctl->steps) < most) atomicMax(&ctl->steps, most);
-  raise_flag(&ctl->more[pass], more);
 }
 
 // ------------------------------------------------- one workgroup's graphs
@@ -875,14 +911,9 @@ int cc_enqueue(CcRun& r) {
                      b.ctl);
   PJ_HIP(hipGetLastError());
   mark(r, "init");
-  int pass = 0;
-  int passes = 1;
-  for (int64_t reach = kFlatHops + 1; reach < z.n; reach *= kFlatHops + 1) ++passes;
-  // later passes mostly have nothing to do: a small grid returns sooner
   const auto flatten = [&] {
-    for (int i = 0; i < passes; ++i, ++pass)
-      hipLaunchKernelGGL(cc_flatten, dim3(i > 0 ? std::min(gv, cap / 4) : gv), dim3(256), 0,
-                         stream, r.D, n, b.ctl, pass, i > 0 ? 1 : 0);
+    hipLaunchKernelGGL(cc_flatten, dim3(grid_for(z.n, 256 * kFlatPer, INT32_MAX)), dim3(256), 0,
+                       stream, r.D, n, b.ctl);
     mark(r, "shortcut");
   };
   if (z.m > 0) {

@@ -139,3 +139,25 @@ def test_batch_of_one_workgroup_graphs(pj, case, tables):
             keep[voff[bad]:voff[bad + 1]] = False
         assert np.array_equal(got[keep], want[keep])
     pj.graph_cache_clear()
+
+
+# deep trees for the shortcut: chains in id order, up and down, beside pairs that
+# hook blind, at sizes around a workgroup's 1024 vertices
+@pytest.mark.parametrize("n", [65_537, 66_560, 66_561, 100_000, (1 << 20) + 1023, 1 << 22])
+@pytest.mark.parametrize("shape", ["up", "down", "doubled", "x4", "comb"])
+def test_deep_trees(pj, n, shape):
+    a = np.arange(n - 1, dtype=np.int32)
+    src, dst = a, a + 1
+    if shape == "down":
+        src, dst = dst[::-1], src[::-1]
+    elif shape == "doubled":
+        src, dst = np.concatenate([src, dst]), np.concatenate([dst, src])
+    elif shape == "x4":
+        perm = np.random.default_rng(n).permutation(n - 1)
+        src, dst = np.tile(src[perm], 4), np.tile(dst[perm], 4)
+    elif shape == "comb":               # a chain of the even ids, a tooth at each
+        a = np.arange(0, n - 2, 2, dtype=np.int32)
+        t = np.arange(0, n - 1, 2, dtype=np.int32)
+        src, dst = np.concatenate([a, t]), np.concatenate([a + 2, t + 1])
+    want = oracle.connected_components(src, dst, n)
+    assert np.array_equal(solve(pj, src, dst, n), want)
