@@ -833,22 +833,25 @@ struct CcRun {
   PhaseTimer* tm = nullptr;
 };
 
-// LDS or the whole device: a workgroup joins about kLdsPairsPerUs pairs a
-// microsecond and one per CU runs at once; the device-wide kernels cost about
-// kDeviceUs of launches and dependent passes, and then join kDevicePairsPerUs.
-// Measured: 20000 vertices and 40000 pairs 48 us in LDS, 86 us device-wide;
-// 60000 and 120000 119 and 98 us; 1024 graphs of 2^8..2^16 vertices, 5.9 * 10^7
-// pairs, 341 us and 2.07 ms.
-constexpr double kLdsPairsPerUs = 1200.0;
-constexpr double kDevicePairsPerUs = 30000.0;
-constexpr double kDeviceUs = 70.0;
-
+// LDS or the whole device: microseconds of a workgroup with the largest graph or
+// with a CU's share of all, and of the device-wide kernels' launches and
+// dependent passes (few for forests, long climbs in sparse graphs with cycles,
+// three parts otherwise), which then join 30000 pairs a microsecond.  Measured,
+// LDS and device-wide, vertices / pairs: uniform 10000 / 20000 29 and 63, 20000 /
+// 40000 48 and 71, 40000 / 80000 83 and 87, 60000 / 120000 119 and 85, 60000 /
+// 80000 99 and 113, 60000 / 40000 70 and 49; planted 10000 / 80000 46 and 57,
+// 20000 / 100000 65 and 57; paths of 30000 48 and 47, of 60000 87 and 51; 1024
+// graphs of 2^8..2^16 vertices, 5.9 * 10^7 pairs, 341 us and 2.07 ms.
 void cc_plan(CcRun& r) {
   const CcSizes& z = r.z;
   const int cus = device_info().cus;
-  const double lds_us = std::max((double)z.max_m, (double)z.m / cus) / kLdsPairsPerUs;
-  r.lds = z.n > 0 && z.max_n <= kLdsVertices && z.max_m <= kLdsPairs &&
-          lds_us <= kDeviceUs + (double)z.m / kDevicePairsPerUs;
+  const double lds_us = 12 + 0.75e-3 * std::max((double)z.max_n, (double)z.n / cus) +
+                        0.5e-3 * std::max((double)z.max_m, (double)z.m / cus);
+  const double device_us = (z.m <= z.n           ? 45
+                            : 2 * z.m < 3 * z.n ? 110
+                                                : 60 + 0.6e-3 * std::min<double>(z.n, kLdsVertices)) +
+                           z.m / 30000.0;
+  r.lds = z.n > 0 && z.max_n <= kLdsVertices && z.max_m <= kLdsPairs && lds_us <= device_us;
   r.bin = (int)std::min<int64_t>(32768, std::max<int64_t>(2048, z.n / (2 * cus)));
 }
 
@@ -921,9 +924,9 @@ int cc_enqueue(CcRun& r) {
     const int halve = z.n < kHalveSmallBelow ? kHalveSmall : kHalveLarge;
     const auto hook = [&](int64_t stride, int64_t chunks) {
       // two pairs a thread where eight would leave CUs without work (200000
-      // vertices in paths 105 us instead of 125); no more of them at once than
+      // vertices in paths 73 us instead of 91); no more of them at once than
       // that in a graph with many pairs, whose joins meet at few roots (300000
-      // vertices, 450000 pairs: 155 us with eight, 240 with two)
+      // vertices, 450000 pairs: 127 us with eight, 212 with two)
       const bool few = chunks < device_info().cus / (stride > 1 ? 4 : 2);
       const int64_t units = few ? chunks * (kHookPer / 2) : chunks;
       hipLaunchKernelGGL(few ? cc_hook<2> : cc_hook<kHookPer>, dim3(grid_for(units, 1, cap)),
@@ -939,7 +942,7 @@ int cc_enqueue(CcRun& r) {
       // Blind hooks of about two pairs a vertex, swaps of half a pair a vertex,
       // each on a flat forest, and the rest, most of which is settled by then.
       // Swapping all pairs at once climbs unfinished trees: 2^22 vertices and
-      // 2^25 pairs 1780 us, in parts 980 us; 10^6 and 2.2 * 10^6 530 and 280.
+      // 2^25 pairs 2480 us, in parts 950 us; 10^6 and 2.2 * 10^6 473 and 215.
       const int64_t blind_stride = std::max<int64_t>(1, z.m / z.n / 2);
       const int64_t blind = (nchunks + blind_stride - 1) / blind_stride;
       hipLaunchKernelGGL(cc_hook_blind, dim3(grid_for(blind, 1, cap)), dim3(256), 0, stream, es,

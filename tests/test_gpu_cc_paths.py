@@ -161,3 +161,21 @@ def test_deep_trees(pj, n, shape):
         src, dst = np.concatenate([a, t]), np.concatenate([a + 2, t + 1])
     want = oracle.connected_components(src, dst, n)
     assert np.array_equal(solve(pj, src, dst, n), want)
+
+
+def test_one_workgroup_chain_and_more_pairs(pj):
+    n = 65_536                          # one chain of the whole LDS, and pairs beside it
+    i = np.arange(n - 1, dtype=np.int32)
+    far = np.random.default_rng(4).integers(0, n, (2, 6000)).astype(np.int32)
+    for a, b in ((i, i + 1), (i[::-1] + 1, i[::-1])):
+        src, dst = np.concatenate([a, far[0]]), np.concatenate([b, far[1]])
+        assert (solve(pj, src, dst, n) == 0).all()
+
+
+# both sides of the choice between one workgroup and the device
+@pytest.mark.parametrize("n,m", [(27_000, 27_000), (29_000, 28_900), (40_000, 39_000),
+                                 (40_000, 41_000), (60_000, 76_000), (60_000, 89_990),
+                                 (60_000, 90_000), (30_000, 80_000), (30_000, 99_000)])
+def test_either_path(pj, n, m):
+    src, dst = W.random_graph(n, m, n + m)
+    assert np.array_equal(solve(pj, src, dst, n), oracle.connected_components(src, dst, n))
