@@ -83,7 +83,8 @@ typedef struct pj_opts {
     int32_t spacing;          /* ruling set, first level: one splitter per `spacing`
                                  consecutive node ids (power of two, 2..65536);
                                  zero: n / 2^20 rounded down to a power of
-                                 two, within 8..256 for one list and 8..64
+                                 two, within 8..256 for one list (2 up to
+                                 25600 nodes, 4 up to 60000) and 8..64
                                  for a batch, 32 at least for a batch of 2^20
                                  nodes or more (a single list of >= 2^24 nodes
                                  keeps 8 when most successors are local) */
@@ -262,7 +263,7 @@ void pj_graph_cache_clear(void);
 /* ------------------------------------------------------------- autotuner */
 /*
  * Times ruling-set parameters on this input by coordinate descent from the
- * defaults (first-level spacing 8..256, recursion spacing 4..16, LDS cutoff
+ * defaults (first-level spacing 8..256 and the default, recursion spacing 4..16, LDS cutoff
  * 2048..16384, workgroup size of the sublist walks 128..1024, each swept with
  * the others at their best so far) and records the fastest in the tune
  * cache, keyed by (gfx arch, ceil(log2 nodes), ceil(log2 lists)).  Later

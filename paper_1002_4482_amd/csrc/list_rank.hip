@@ -2990,8 +2990,14 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
 // lists) up to 256 for one list (2^28 nodes: 14.5 ms at 256 against 15.9 at
 // 64, measured; longer walks cost imbalance, a larger table costs L2
 // misses) and up to 64 for a batch, whose many short lists end most walks
-// early anyway.
+// early anyway.  One list of up to 25600 nodes takes 2 and of up to 60000 takes
+// 4: its splitters still fit the base, whose time grows less than that of the
+// longest walk falls (random lists at 8, 4 and 2: 17000 nodes 50, 41 and 37.5
+// us, 25000 46, 41 and 40, 32000 46, 42 and 43, 55000 52 and 46; 85000, with one
+// more level, 57.8 and 59.5; local lists of 32000 and 60000, whose walks share
+// their lines, 30 and 34 at 8, 32 and 36 at 4).
 int list_rank_default_spacing(int64_t n, bool single) {
+  if (single && n <= 60000) return n <= 25600 ? 2 : 4;
   const int cap = single ? 256 : 64;
   int sp = 8;
   while (sp < cap && (n >> 20) > sp) sp *= 2;
