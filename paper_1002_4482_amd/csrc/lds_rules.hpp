@@ -1,0 +1,42 @@
+// Rules of the LDS solvers in a form that a build for the CPU can include: the
+// tests model the kernels with them.
+#pragma once
+
+#include <stdint.h>
+
+#ifdef __HIP__
+#include <hip/hip_runtime.h>
+#define PJ_RULE __host__ __device__ __forceinline__
+#else
+#define PJ_RULE inline
+#endif
+
+namespace pj {
+
+// ------------------------------------------------ pointer jumping (lr_lds)
+// A node's word holds (distance << 16 | tail mark | node) of the node it has
+// jumped to.  A tail points to itself at distance 0 and carries the mark; a
+// jump copies the mark with the node, so a marked word has reached a tail of the
+// input, and one that has not (its path ends in a cycle, whatever its distance
+// has grown or wrapped to) never gets it.  The path to a tail passes no node
+// twice, so a marked distance is exact and below kListNodes; it is size - 1 for
+// some node exactly if that node's path is the whole list.
+constexpr int kListNodes = 1 << 14;
+constexpr uint32_t kListTail = kListNodes;
+
+PJ_RULE uint32_t list_tail_word(int node) { return kListTail | (uint32_t)node; }
+PJ_RULE uint32_t list_word(int next) { return 1u << 16 | (uint32_t)next; }
+PJ_RULE int list_target(uint32_t word) { return (int)(word & (kListNodes - 1)); }
+PJ_RULE int list_distance(uint32_t word) { return (int)(word >> 16); }
+
+// The word after a jump to the target of `mine`, whose word is `there`.  After k
+// jumps a node up to 2^k - 1 steps from its tail has the mark.
+PJ_RULE uint32_t list_jump(uint32_t mine, uint32_t there) {
+  return ((mine >> 16) + (there >> 16)) << 16 | (there & 0xffff);
+}
+
+PJ_RULE bool list_whole(uint32_t word, int size) {
+  return (word & kListTail) != 0 && list_distance(word) == size - 1;
+}
+
+}  // namespace pj

@@ -32,6 +32,7 @@
 #include <cmath>
 #include <vector>
 
+#include "lds_rules.hpp"
 #include "pj_internal.hpp"
 
 namespace pj {
@@ -1956,12 +1957,13 @@ __global__ void __launch_bounds__(1024) wy_final(const unsigned long long* __res
 // ------------------------------------------------- one workgroup's lists
 // Lists short enough for LDS: a workgroup reads its lists' successors once,
 // ranks them by pointer jumping in LDS and writes the ranks, one kernel in all.
-// A node's word holds (distance << 16 | node) to the node it has jumped to, so a
-// jump is one LDS read and one write; a tail points to itself at distance 0.
-// Jumping in place is safe: whatever version of a word a jump reads is a true
-// distance.  A list is one list exactly if no successor is out of range and
-// some node is size - 1 jumps away from a tail (with two tails, a branch or a
-// cycle no node is).
+// A node's word (lds_rules.hpp) holds the distance to the node it has jumped to
+// and that node, so a jump is one LDS read and one write.  Jumping in place is
+// safe: whatever version of a word a jump reads is a true distance (modulo 2^16
+// on the way round a cycle).  A list is one list exactly if no successor is out of
+// range and some node is size - 1 steps away from a tail; the words tell that
+// by a mark that only a tail hands out, as distances round a cycle may take any
+// value.
 //
 // A workgroup takes the lists that start in its block of `bin` consecutive
 // nodes, up to kSubLists lists and kCap nodes at a time.  Bound by LDS accesses
@@ -1976,6 +1978,7 @@ __global__ void __launch_bounds__(kThreads) lr_lds(const int32_t* succ, int n,
                                                    const int64_t* __restrict__ off, int L,
                                                    int bin, int to_tail, int32_t* rank,
                                                    int32_t* lerr, int32_t* status) {
+  static_assert(kCap <= kListNodes, "a node fits its word");
   constexpr int kRows = kCap / kThreads;
   __shared__ uint32_t word[kCap];
   __shared__ int so[kSubLists + 1];
@@ -2038,7 +2041,7 @@ __global__ void __launch_bounds__(kThreads) lr_lds(const int32_t* succ, int n,
         const bool tail = (s == -1) | (s == j - base);
         const bool range = s >= 0 && s < size;
         if (!tail && !range) atomicOr(&bad[l >> 5], 1u << (l & 31));
-        mine[t] = tail || !range ? (uint32_t)j : 1u << 16 | (uint32_t)(base + s);
+        mine[t] = tail || !range ? list_tail_word(j) : list_word(base + s);
         word[j] = mine[t];
       }
     }
@@ -2048,8 +2051,7 @@ __global__ void __launch_bounds__(kThreads) lr_lds(const int32_t* succ, int n,
       for (int t = 0; t < kRows; ++t) {
         const int j = j0 + t * kWave;
         if (t < rows && j < nv) {
-          const uint32_t w = word[mine[t] & 0xffff];
-          const uint32_t next = (((mine[t] >> 16) + (w >> 16)) << 16) | (w & 0xffff);
+          const uint32_t next = list_jump(mine[t], word[list_target(mine[t])]);
           if (next != mine[t]) word[j] = mine[t] = next;
         }
       }
@@ -2061,9 +2063,8 @@ __global__ void __launch_bounds__(kThreads) lr_lds(const int32_t* succ, int n,
       const int j = j0 + t * kWave;
       if (t < rows && j < nv) {
         while (l < k - 1 && so[l + 1] <= j) ++l;
-        const int size = so[l + 1] - so[l], d = (int)(mine[t] >> 16), end = mine[t] & 0xffff;
-        if (d == size - 1 && (int)(word[end] & 0xffff) == end)
-          atomicOr(&whole[l >> 5], 1u << (l & 31));
+        const int size = so[l + 1] - so[l], d = list_distance(mine[t]);
+        if (list_whole(mine[t], size)) atomicOr(&whole[l >> 5], 1u << (l & 31));
         rank[v0 + j] = to_tail ? d : size - 1 - d;
       }
     }
