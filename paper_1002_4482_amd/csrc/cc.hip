@@ -25,6 +25,7 @@
 #include <mutex>
 #include <vector>
 
+#include "lds_rules.hpp"
 #include "pj_internal.hpp"
 
 namespace pj {
@@ -475,7 +476,7 @@ __global__ void __launch_bounds__(kLdsThreads) cc_lds(
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int lane = lane_id();
-  __shared__ int first_heavy;
+  __shared__ int first_heavy, past;  // first graph that is heavy, that does not fit
   // with a second set of `bins` workgroups, the first takes the heavy graphs
   const bool take_heavy = (int)gridDim.x > bins && (int)blockIdx.x < bins;
   const int block = (int)blockIdx.x % bins;
@@ -490,14 +491,15 @@ __global__ void __launch_bounds__(kLdsThreads) cc_lds(
     const int64_t v0 = voff ? voff[ga] : 0, e0 = voff ? eoff[ga] : 0;
     __syncthreads();  // the last graphs' tables and parents are done with
     for (int i = tid; i <= k; i += kLdsThreads) {
-      const int64_t dv = (voff ? voff[ga + i] : i * (int64_t)n) - v0;
-      const int64_t de = (voff ? eoff[ga + i] : i * m) - e0;
-      sv[i] = (int)min<int64_t>(max<int64_t>(dv, 0), INT32_MAX);
-      se[i] = (int)min<int64_t>(max<int64_t>(de, 0), INT32_MAX);
+      sv[i] = table_entry((voff ? voff[ga + i] : i * (int64_t)n) - v0);
+      se[i] = table_entry((voff ? eoff[ga + i] : i * m) - e0);
     }
     if (tid < kSubGraphs / 32) badbits[tid] = 0;
-    if (tid == 0) first_heavy = k;
+    if (tid == 0) first_heavy = past = k;
     __syncthreads();
+    if (tid < k && !(entry_fits(sv[tid], sv[tid + 1], kCap) &&
+                     entry_fits(se[tid], se[tid + 1], kLdsPairs)))
+      atomicMin(&past, tid);
     if ((int)gridDim.x > bins) {
       if (tid < k && se[tid + 1] - se[tid] > heavy) atomicMin(&first_heavy, tid);
       __syncthreads();
@@ -512,10 +514,11 @@ __global__ void __launch_bounds__(kLdsThreads) cc_lds(
       }
       k = take_heavy ? 1 : light;
     }
-    const int fit = __syncthreads_count(tid < k && sv[tid + 1] <= kCap && se[tid + 1] <= kLdsPairs);
+    __syncthreads();
+    const int fit = min(k, past);
     const int take = max(fit, 1);
     const int nv = sv[take], ne = se[take];
-    if (fit == 0 || v0 < 0 || v0 + nv > n || e0 < 0 || e0 + ne > m) {
+    if (fit == 0 || v0 < 0 || v0 > n - nv || e0 < 0 || e0 > m - ne) {
       if (status)
         for (int i = tid; i < take; i += kLdsThreads) status[ga + i] = PJ_EINVAL;
       ga += take;

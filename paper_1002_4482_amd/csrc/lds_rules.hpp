@@ -13,6 +13,15 @@
 
 namespace pj {
 
+// -------------------------------------------- groups of instances in LDS
+// A workgroup takes the instances of a stretch of the offset table that fit LDS
+// together.  The table is the device's: it may hold anything, so only a run
+// of entries that each fit after the one before may be indexed with.
+// An entry relative to the group's first: what no table of this size can hold
+// does not fit.
+PJ_RULE int table_entry(int64_t d) { return d < 0 || d > INT32_MAX ? INT32_MAX : (int)d; }
+PJ_RULE bool entry_fits(int before, int entry, int cap) { return entry >= before && entry <= cap; }
+
 // ------------------------------------------------ pointer jumping (lr_lds)
 // A node's word holds (distance << 16 | tail mark | node) of the node it has
 // jumped to.  A tail points to itself at distance 0 and carries the mark; a

@@ -1983,7 +1983,7 @@ __global__ void __launch_bounds__(kThreads) lr_lds(const int32_t* succ, int n,
   __shared__ uint32_t word[kCap];
   __shared__ int so[kSubLists + 1];
   __shared__ uint32_t whole[kSubLists / 32], bad[kSubLists / 32];
-  __shared__ int longest;
+  __shared__ int longest, past;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int lane = lane_id();
@@ -1998,18 +1998,21 @@ __global__ void __launch_bounds__(kThreads) lr_lds(const int32_t* succ, int n,
     const int64_t v0 = off ? off[la] : 0;
     __syncthreads();  // the last lists' tables and words are done with
     for (int i = tid; i <= k; i += kThreads) {
-      const int64_t d = (off ? off[la + i] : i * (int64_t)n) - v0;
-      so[i] = (int)min<int64_t>(max<int64_t>(d, 0), INT32_MAX);
+      so[i] = table_entry((off ? off[la + i] : i * (int64_t)n) - v0);
     }
     if (tid < kSubLists / 32) whole[tid] = bad[tid] = 0;
-    if (tid == 0) longest = 1;
+    if (tid == 0) {
+      longest = 1;
+      past = k;
+    }
     __syncthreads();
-    int fit = 0;  // lists of the group that fit LDS together
-    for (int i0 = 0; i0 < k; i0 += kThreads)
-      fit += __syncthreads_count(i0 + tid < k && so[i0 + tid + 1] <= kCap);
+    for (int i = tid; i < k; i += kThreads)
+      if (!entry_fits(so[i], so[i + 1], kCap)) atomicMin(&past, i);
+    __syncthreads();
+    const int fit = past;  // lists of the group that fit LDS together
     const int take = max(fit, 1);
     const int nv = so[take];
-    if (fit == 0 || v0 < 0 || v0 + nv > n) {  // not the table the host planned with
+    if (fit == 0 || v0 < 0 || v0 > n - nv) {  // not the table the host planned with
       for (int i = tid; i < take; i += kThreads) {
         if (status) status[la + i] = PJ_EBADLIST;
         if (lerr) lerr[la + i] = kErrRange;
