@@ -497,34 +497,25 @@ __global__ void __launch_bounds__(kLdsThreads) cc_lds(
     if (tid < kSubGraphs / 32) badbits[tid] = 0;
     if (tid == 0) first_heavy = past = k;
     __syncthreads();
-    if (tid < k && !(entry_fits(sv[tid], sv[tid + 1], kCap) &&
-                     entry_fits(se[tid], se[tid + 1], kLdsPairs)))
-      atomicMin(&past, tid);
-    if ((int)gridDim.x > bins) {
-      if (tid < k && se[tid + 1] - se[tid] > heavy) atomicMin(&first_heavy, tid);
-      __syncthreads();
-      const int light = first_heavy;  // graphs before the first heavy one
-      if (take_heavy && light > 0) {
-        ga += light;
-        continue;
-      }
-      if (!take_heavy && light == 0) {
-        ++ga;
-        continue;
-      }
-      k = take_heavy ? 1 : light;
+    if (tid < k) {
+      if (!(entry_fits(sv[tid], sv[tid + 1], kCap) && entry_fits(se[tid], se[tid + 1], kLdsPairs)))
+        atomicMin(&past, tid);
+      if ((int)gridDim.x > bins && se[tid + 1] - se[tid] > heavy) atomicMin(&first_heavy, tid);
     }
     __syncthreads();
-    const int fit = min(k, past);
-    const int take = max(fit, 1);
-    const int nv = sv[take], ne = se[take];
-    if (fit == 0 || v0 < 0 || v0 > n - nv || e0 < 0 || e0 > m - ne) {
-      if (status)
-        for (int i = tid; i < take; i += kLdsThreads) status[ga + i] = PJ_EINVAL;
-      ga += take;
+    const TableStep next = table_step(first_heavy, past, take_heavy);
+    if (!next.ours) {
+      ga += next.count;
       continue;
     }
-    k = take;
+    k = next.count;
+    const int nv = sv[k], ne = se[k];
+    if (past == 0 || v0 < 0 || v0 > n - nv || e0 < 0 || e0 > m - ne) {
+      if (status)
+        for (int i = tid; i < k; i += kLdsThreads) status[ga + i] = PJ_EINVAL;
+      ga += k;
+      continue;
+    }
     for (int i = tid; i < (min(nv, kCap) + 1) / 2; i += kLdsThreads)
       par[i] = (uint32_t)(2 * i) | (uint32_t)(2 * i + 1) << 16;
     __syncthreads();

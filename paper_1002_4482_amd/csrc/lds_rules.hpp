@@ -22,6 +22,23 @@ namespace pj {
 PJ_RULE int table_entry(int64_t d) { return d < 0 || d > INT32_MAX ? INT32_MAX : (int)d; }
 PJ_RULE bool entry_fits(int before, int entry, int cap) { return entry >= before && entry <= cap; }
 
+// Graphs with many pairs (heavy ones) go to workgroups of their own, so two
+// workgroups go over one stretch of the table: each takes or passes over the
+// next instances, the heavy ones one at a time, the others a group at a time.
+// Of k instances `heavy_at` is the first heavy one and `past` the first that does
+// not fit (k: none).  Whether an instance is heavy is only asked of those before
+// `past` and of the first, whose size does not depend on where the group
+// starts; so both workgroups answer alike, and every instance has one taker.
+struct TableStep {
+  int count;  // instances gone over
+  bool ours;
+};
+PJ_RULE TableStep table_step(int heavy_at, int past, bool take_heavy) {
+  const bool heavy = heavy_at == 0;
+  const int group = heavy_at < past ? heavy_at : past;
+  return {heavy || group == 0 ? 1 : group, heavy == take_heavy};
+}
+
 // ------------------------------------------------ pointer jumping (lr_lds)
 // A node's word holds (distance << 16 | tail mark | node) of the node it has
 // jumped to.  A tail points to itself at distance 0 and carries the mark; a

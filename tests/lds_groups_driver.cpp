@@ -1,0 +1,77 @@
+// CPU model of how cc_lds's two workgroups go over one stretch of the offset
+// tables: on every table, whatever it holds, each graph has exactly one taker,
+// and a group's entries can be indexed with.  Prints OK.
+#include <algorithm>
+#include <cstdio>
+#include <random>
+#include <vector>
+
+#include "lds_rules.hpp"
+
+namespace {
+
+constexpr int kCap = 65536, kPairs = 1 << 30, kGroup = 512;
+
+bool check(const std::vector<int64_t>& voff, const std::vector<int64_t>& eoff, int heavy) {
+  const int G = (int)voff.size() - 1;
+  std::vector<int> takers(G, 0);
+  for (const bool take_heavy : {true, false}) {
+    for (int ga = 0; ga < G;) {
+      const int k = std::min(G - ga, kGroup);
+      std::vector<int> sv(k + 1), se(k + 1);
+      for (int i = 0; i <= k; ++i) {
+        sv[i] = pj::table_entry((int64_t)((uint64_t)voff[ga + i] - (uint64_t)voff[ga]));
+        se[i] = pj::table_entry((int64_t)((uint64_t)eoff[ga + i] - (uint64_t)eoff[ga]));
+      }
+      int heavy_at = k, past = k;
+      for (int i = k - 1; i >= 0; --i) {
+        if (!(pj::entry_fits(sv[i], sv[i + 1], kCap) && pj::entry_fits(se[i], se[i + 1], kPairs)))
+          past = i;
+        if (se[i + 1] - se[i] > heavy) heavy_at = i;
+      }
+      const pj::TableStep next = pj::table_step(heavy_at, past, take_heavy);
+      if (next.count < 1 || next.count > k) return false;
+      if (next.ours)
+        for (int i = 0; i < next.count; ++i) {
+          ++takers[ga + i];
+          if (past > 0 && (sv[i + 1] < sv[i] || sv[i + 1] > kCap || se[i + 1] < se[i])) return false;
+        }
+      ga += next.count;
+    }
+  }
+  return std::all_of(takers.begin(), takers.end(), [](int t) { return t == 1; });
+}
+
+}  // namespace
+
+int main() {
+  std::mt19937_64 rng(7);
+  const auto below = [&](int64_t n) { return (int64_t)(rng() % (uint64_t)n); };
+  // 3 * 10^9 pairs: a heavy graph behind more than 2^31 pairs of light ones
+  {
+    std::vector<int64_t> voff{0}, eoff{0};
+    for (int g = 0; g < 520; ++g) {
+      voff.push_back(voff.back() + 100);
+      eoff.push_back(eoff.back() + (g == 450 ? 10'000'000 : 5'500'000));
+    }
+    if (!check(voff, eoff, (int)(eoff.back() / 512))) return printf("many pairs\n"), 1;
+  }
+  for (int run = 0; run < 3000; ++run) {
+    const int G = 1 + (int)below(1500);
+    std::vector<int64_t> voff{0}, eoff{0};
+    const int64_t v = 1 + below(run % 3 ? 300 : 60'000), e = 1 + below(run % 5 ? 500 : 20'000'000);
+    for (int g = 0; g < G; ++g) {
+      voff.push_back(voff.back() + below(v));
+      eoff.push_back(eoff.back() + below(below(9) ? e : 9 * e));
+    }
+    const int heavy = (int)std::min<int64_t>(kPairs, eoff.back() / 512);
+    if (run % 2)  // entries of any value
+      for (int64_t i = below(9); i > 0; --i) {
+        auto& off = below(2) ? voff : eoff;
+        off[(size_t)below(G + 1)] = below(3) ? below(2 * off.back() + 2) : (int64_t)rng();
+      }
+    if (!check(voff, eoff, heavy)) return printf("run %d\n", run), 1;
+  }
+  printf("OK\n");
+  return 0;
+}
