@@ -189,8 +189,9 @@ int pj_list_rank_batched_ex(const int32_t *succ, const int64_t *offsets, int64_t
 
 /* Bytes of workspace a call with these sizes needs (L = 1: enough for both the
  * plain call and a batched call holding one list).  One list of 11 * 2^20 to
- * 2^26 nodes, and a batch of 2^20 nodes or more whose lists have at most 2^21,
- * use 12 to 20 bytes per node beyond that, and run faster, where the library
+ * 2^26 nodes uses 14 to 19 bytes per node beyond that, and a batch of 2^20 nodes
+ * or more whose lists have at most 2^21 about as much (at most 32 and 256 MiB; a
+ * batch that would take more uses none), and they run faster, where the library
  * allocates or opts->workspace is that much larger. */
 size_t pj_list_rank_workspace_bytes(int64_t total_nodes, int64_t L, const pj_opts *opts);
 

@@ -34,6 +34,7 @@
 
 #include "lds_rules.hpp"
 #include "pj_internal.hpp"
+#include "record_plan.hpp"
 
 namespace pj {
 namespace {
@@ -99,10 +100,7 @@ __device__ __forceinline__ int step_code(int y, int N, int log2B, uint32_t seed)
 
 __device__ __forceinline__ void store_pair(int2* p, int a, int b) { *p = make_int2(a, b); }
 
-// Recorded walk (see lr_walk_rec).
-constexpr int kStrip = 16;
-constexpr int kSlab = 256;
-constexpr int kXcds = 8;
+// Recorded walk (see lr_walk_rec; its sizes are in record_plan.hpp).
 constexpr int kBinShift = 15;
 constexpr int kBinNodes = 1 << kBinShift;  // 128 KiB of ranks in LDS
 constexpr int kWordLongest = 1 << 20;      // (see lr_bin)
@@ -364,9 +362,7 @@ struct WalkArgs {
 // state.  The read and the write then touch the same cache line, which costs
 // far less than a write to a second random line.
 constexpr int kWalkBurst = 16;
-constexpr int kWalkChunk = 64;  // items a wave takes at a time
 
-//
 // kPaired (level 0, weighted calls): the state array holds {step code, weight}
 // pairs, made by the head-find pass, and a visited one {-2 - sublist id, weight
 // before the node}: one random line per node instead of three for successor,
@@ -2440,8 +2436,11 @@ constexpr int64_t kRecordBatch = int64_t(1) << 20;
 constexpr int64_t kRecordLongest = int64_t(1) << 21;
 constexpr int kRecordSpacing = 32;
 
-bool recorded_plan(const Plan& in_place, int64_t n0, int64_t L, int64_t max_size, bool single,
-                   bool weighted, const pj_opts& o, bool spacing_given, Plan* out) {
+//
+// h_off: the host's table where the call runs on these very lists, else nullptr.
+bool recorded_plan(const Plan& in_place, int64_t n0, int64_t L, int64_t max_size,
+                   const int64_t* h_off, bool single, bool weighted, const pj_opts& o,
+                   bool spacing_given, Plan* out) {
   const Plan& q = in_place;
   if (weighted != q.paired || q.algo != PJ_ALGO_RULING_SET || q.small || q.chosen > 0 ||
       (o.level0_state == PJ_STATE_SEPARATE && !weighted) || o.max_walk % kStrip != 0)
@@ -2458,23 +2457,25 @@ bool recorded_plan(const Plan& in_place, int64_t n0, int64_t L, int64_t max_size
   if (p.log2B_far > 0) p.log2B_far = std::max(p.log2B_far, ilog2(kRecordSpacing));
   p.rec_grid = device_info().cus * (single ? 2 : 1) / kXcds * kXcds;
   p.rec_log2B = p.log2B_far > 0 ? p.log2B_far : p.log2B[0];
-  // Every sublist piece ends in one partly filled strip at most, and every wave
-  // in one partly filled and one unused slab.  The sublists that start in an
-  // XCD's eighth of a batch stay in the lists that do, so they hold an eighth
-  // of the nodes and two lists at most -- of the longest size that a captured
-  // call may be replayed with, the next power of two.
-  const int64_t r = (n0 + (1ll << p.rec_log2B) - 1) >> p.rec_log2B;
-  const int64_t groups = single ? 1 : kXcds;
-  const int64_t longest = 1ll << bits_for(max_size);
-  const int64_t nodes = n0 / groups + (single ? 0 : 2 * longest + (kWalkChunk << p.rec_log2B));
-  const int64_t pieces = r / groups + kWalkChunk + L + nodes / o.max_walk + 64;
-  p.group_slabs =
-      (int)((nodes / kStrip + pieces) / kSlab + 1 + 2 * (p.rec_grid / groups) * (256 / kWave));
-  p.max_slabs = (int)(groups * p.group_slabs);
-  p.rec_chunks = (int)((r + kWalkChunk - 1) / kWalkChunk);
+  const RecordChunks chunks = record_chunks(n0, p.rec_log2B);
+  const int64_t waves = p.rec_grid / (single ? 1 : kXcds) * (256 / kWave);
+  p.rec_chunks = (int)chunks.chunks;
   p.word = !single && !weighted && max_size <= kWordLongest;
   p.bin_shift = p.word ? std::min(kBinShift, 32 - bits_for(max_size)) : kBinShift;
   p.rec_bins = (int)((n0 + (1ll << p.bin_shift) - 1) >> p.bin_shift);
+  int64_t slabs = 0;
+  if (single) {
+    slabs = record_slabs(n0, chunks.blocks + kWalkChunk + 1 + n0 / o.max_walk + 64, waves);
+  } else {
+    const int64_t longest = h_off ? max_size : 1ll << bits_for(max_size);
+    slabs = record_batch_slabs(n0, record_heads(h_off, L, n0, p.rec_log2B), longest, p.rec_log2B,
+                               o.max_walk, waves);
+    if (!record_fits(kXcds * slabs, 4 * kStrip * (weighted ? 2 : 1) + 8,
+                     ((int64_t)p.rec_bins << p.bin_shift) * (p.word ? 4 : 8), n0))
+      return false;
+  }
+  p.group_slabs = (int)slabs;
+  p.max_slabs = (int)(slabs * (single ? 1 : kXcds));
   *out = p;
   return true;
 }
@@ -2596,12 +2597,12 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
   // total nodes and the largest list, from the host's view of the offsets
   int64_t n0 = 0, max_size = 0;
   std::vector<int64_t> hbuf;
+  const int64_t* ho = single ? nullptr : h_off;
   if (single) {
     n0 = n_single;
     max_size = n0;
   } else {
     if (L == 0) return PJ_OK;
-    const int64_t* ho = h_off;
     if (!ho) {
       hbuf.resize((size_t)L + 1);
       PJ_HIP(hipMemcpyAsync(hbuf.data(), d_off, sizeof(int64_t) * (L + 1),
@@ -2669,7 +2670,8 @@ int list_rank_impl(const int32_t* succ, const int64_t* d_off, int64_t L, const i
   // the recorded walk where its strips fit the caller's workspace or the pool
   bool recorded = false;
   Plan pr;
-  if (recorded_plan(p, n0, L, max_size, single, weight != nullptr, o, spacing_given, &pr)) {
+  if (recorded_plan(p, n0, L, max_size, ho && !capturing(stream) ? ho : nullptr, single,
+                    weight != nullptr, o, spacing_given, &pr)) {
     const size_t more = carve(pr, L, single, o.validate != 0, want_status, nullptr, &b);
     if (!o.workspace || o.workspace_bytes >= more)
       recorded = workspace_acquire(ws, more, &o, stream) == PJ_OK;
@@ -3059,7 +3061,7 @@ size_t list_rank_graph_workspace(int64_t n0, int64_t L, int64_t max_size, const 
   Buffers b;
   const bool status = o.validate && !o.d_status;
   size_t bytes = list_rank_workspace(n0, L, user, false);
-  if (recorded_plan(p, n0, L, max_size, false, false, o, spacing_given, &pr))
+  if (recorded_plan(p, n0, L, max_size, nullptr, false, false, o, spacing_given, &pr))
     bytes = std::max(bytes, carve(pr, L, false, o.validate != 0, status, nullptr, &b));
   return bytes;
 }

@@ -94,6 +94,7 @@ inline size_t ws_bytes(size_t count, size_t elem) { return (count * elem + 255) 
 
 int workspace_acquire(Workspace& ws, size_t bytes, const pj_opts* opts, hipStream_t stream);
 int workspace_release(Workspace& ws);
+bool capturing(hipStream_t stream);  // or not known not to be
 void drop_kept_workspaces();
 
 // One pinned host word for a device-to-host flag copy, from a process-wide

@@ -62,6 +62,13 @@ int persistent_grid(const void* kernel, int block, size_t lds_bytes) {
   return grid;
 }
 
+bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // ------------------------------------------------------- kept workspaces
 // Small workspaces are kept between calls: allocating and freeing one from the
 // stream-ordered pool takes the host 25 us, and a call on 17000 to 70000 nodes
@@ -115,11 +122,7 @@ void drop_kept(const KeptBlock& k, hipStream_t stream) {
 }
 
 bool take_kept(Workspace& ws, hipStream_t stream) {
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return false;
-  }
+  if (capturing(stream)) return false;
   int device = 0;
   if (hipGetDevice(&device) != hipSuccess) return false;
   KeptBlock k = {device, nullptr, nullptr, stream};
