@@ -23,7 +23,7 @@ inline RecordChunks record_chunks(int64_t n0, int log2B) {
   c.chunks = (c.blocks + kWalkChunk - 1) / kWalkChunk;
   return c;
 }
-inline int64_t record_group_chunk(int64_t chunks, int group) { return chunks * group / kXcds; }
+constexpr int64_t record_group_chunk(int64_t chunks, int group) { return chunks * group / kXcds; }
 
 // Most lists with nodes that start in one group: counted in the host's table
 // (non-decreasing, L + 1 entries), or, without one (a captured call may be
