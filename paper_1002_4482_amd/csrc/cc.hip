@@ -482,8 +482,9 @@ __global__ void __launch_bounds__(kLdsThreads) cc_lds(
   const int block = (int)blockIdx.x % bins;
   int64_t g0 = 0, g1 = 1;
   if (voff) {
-    g0 = block == 0 ? 0 : count_below<kLdsThreads>(voff, G, (int64_t)block * bin);
-    g1 = block == bins - 1 ? G : count_below<kLdsThreads>(voff, G, (int64_t)(block + 1) * bin);
+    const auto key = [&](int64_t g) { return voff[g]; };
+    g0 = block == 0 ? 0 : count_below<kLdsThreads>(G, (int64_t)block * bin, key);
+    g1 = block == bins - 1 ? G : count_below<kLdsThreads>(G, (int64_t)(block + 1) * bin, key);
   }
   int deep = 0;
   for (int64_t ga = g0; ga < g1;) {

@@ -14,11 +14,15 @@
 namespace pj {
 
 // -------------------------------------------- groups of instances in LDS
-// A workgroup takes the instances of a stretch of the offset table that fit LDS
-// together.  The table is the device's: it may hold anything, so only a run
-// of entries that each fit after the one before may be indexed with.
-// An entry relative to the group's first: what no table of this size can hold
-// does not fit.
+// Workgroup b takes the lists whose key lies in its block of `bin`: the nodes and
+// the lists before them, so that it has at most `bin` nodes' starts and at most
+// `bin` lists, also where thousands of empty ones lie together.
+PJ_RULE int64_t list_key(int64_t off, int64_t l) { return off + l; }
+
+// Of those it takes the ones that fit LDS together, and again.  The table is the
+// device's: it may hold anything, so only a run of entries that each fit after the
+// one before may be indexed with.  An entry relative to the group's first: what
+// no table of this size can hold does not fit.
 PJ_RULE int table_entry(int64_t d) { return d < 0 || d > INT32_MAX ? INT32_MAX : (int)d; }
 PJ_RULE bool entry_fits(int before, int entry, int cap) { return entry >= before && entry <= cap; }
 

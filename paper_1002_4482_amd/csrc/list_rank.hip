@@ -639,7 +639,7 @@ __global__ void __launch_bounds__(1024) lr_walk(WalkArgs a) {
 // order: about those of the chunk's own nodes where lists are spread evenly, and
 // no more than that where many short or empty ones lie together, which one wave
 // would take 64 at a time (1000 lists of 2^16 nodes and 4 * 10^6 empty ones in one
-// place: 142 ms by place).
+// place: 142 ms by place, 4.0 like this).
 __global__ void __launch_bounds__(256) lr_rec_chunks(const int64_t* __restrict__ off, int L,
                                                      int nchunks, int log2_chunk,
                                                      int32_t* __restrict__ chunk_list) {
@@ -1973,8 +1973,8 @@ __global__ void __launch_bounds__(1024) wy_final(const unsigned long long* __res
 // by a mark that only a tail hands out, as distances round a cycle may take any
 // value.
 //
-// A workgroup takes the lists that start in its block of `bin` consecutive
-// nodes, up to kSubLists lists and kCap nodes at a time.  Bound by LDS accesses
+// A workgroup takes the lists of its block of `bin` keys (nodes and lists, see
+// list_key), up to kSubLists lists and kCap nodes at a time.  Bound by LDS accesses
 // (ceil(log2 of the longest list) jumps a node) and, for one short list, by the
 // launch.  20000 lists of 2^3..2^10 nodes: 341 us on the sublist walks, 49 us
 // here; one list of 4096 nodes took 32 us a call with links and sums apart and a
@@ -1997,9 +1997,10 @@ __global__ void __launch_bounds__(kThreads) lr_lds(const int32_t* succ, int n,
   const int lane = lane_id();
   int64_t l0 = 0, l1 = 1;
   if (off) {
-    l0 = blockIdx.x == 0 ? 0 : count_below<kThreads>(off, L, (int64_t)blockIdx.x * bin);
+    const auto key = [&](int64_t l) { return list_key(off[l], l); };
+    l0 = blockIdx.x == 0 ? 0 : count_below<kThreads>(L, (int64_t)blockIdx.x * bin, key);
     l1 = blockIdx.x == gridDim.x - 1
-             ? L : count_below<kThreads>(off, L, (int64_t)(blockIdx.x + 1) * bin);
+             ? L : count_below<kThreads>(L, (int64_t)(blockIdx.x + 1) * bin, key);
   }
   for (int64_t la = l0; la < l1;) {
     int k = (int)min<int64_t>(l1 - la, kSubLists);
@@ -2584,7 +2585,7 @@ int launch_lds(const int32_t* succ, const int32_t* weight, int64_t n, int64_t ma
   const int cap = small ? kSmallCap : kMaxCutoff;
   const int bin = (int)std::max<int64_t>(cap / 2, cap - max_size);
   const auto k = small ? lr_lds<kSmallCap, 256> : lr_lds<kMaxCutoff, kBaseThreads>;
-  hipLaunchKernelGGL(k, dim3(d_off ? (unsigned)(n / bin + 1) : 1), dim3(small ? 256 : kBaseThreads),
+  hipLaunchKernelGGL(k, dim3(d_off ? (unsigned)((n + L) / bin + 1) : 1), dim3(small ? 256 : kBaseThreads),
                      0, stream, succ, (int)n, d_off, (int)L, bin, to_tail, rank, lerr, status);
   PJ_HIP(hipGetLastError());
   return PJ_OK;

@@ -211,17 +211,15 @@ __device__ __forceinline__ int find_instance(const int64_t* __restrict__ off, in
   return lo;
 }
 
-// Number of entries of the non-decreasing table off[0..count) below `target`,
-// found by all kThreads threads of the workgroup together, kThreads probes a
-// step.
-template <int kThreads>
-__device__ __forceinline__ int64_t count_below(const int64_t* __restrict__ off, int64_t count,
-                                               int64_t target) {
+// Number of the non-decreasing key(0..count) below `target`, found by all kThreads
+// threads of the workgroup together, kThreads probes a step.
+template <int kThreads, class Key>
+__device__ __forceinline__ int64_t count_below(int64_t count, int64_t target, Key key) {
   int64_t lo = 0, hi = count;  // the answer lies in [lo, hi]
   while (lo < hi) {
     const int64_t step = (hi - lo + kThreads - 1) / kThreads;
     const int64_t i = lo + threadIdx.x * step;
-    const int below = __syncthreads_count(i < hi && off[i] < target);
+    const int below = __syncthreads_count(i < hi && key(i) < target);
     if (below == 0) return lo;
     const int64_t last = lo + (below - 1) * step;  // the last probe below the target
     hi = min(hi, last + step);

@@ -54,8 +54,10 @@ def lists_in_place(longs, size, empties, where):
     return succ, off, np.concatenate([want[i % 8] for i in range(longs)])
 
 
-# the recorded walk (2^16 nodes a list end on its chunks' borders)
-@pytest.mark.parametrize("longs,size,empties", [(256, 1 << 16, 1_000_000)])
+# the recorded walk (2^16 nodes a list end on its chunks' borders), and lists in
+# LDS with its two workgroup sizes
+@pytest.mark.parametrize("longs,size,empties", [(256, 1 << 16, 1_000_000), (300, 1000, 1_000_000),
+                                                (60, 9000, 1_000_000)])
 def test_lists(pj, longs, size, empties):
     ms = {}
     for where in ("together", "spread"):
