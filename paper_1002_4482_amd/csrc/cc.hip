@@ -380,10 +380,11 @@ __global__ void __launch_bounds__(256) cc_flatten(int32_t* D, int n, CcCtl* ctl)
 // per CU).  1024 graphs of 2^8..2^16 vertices, 5.9 * 10^7 pairs: 2109 us on the
 // device-wide path, 340 us here; 1000 vertices and 1500 pairs 65 and 14 us.
 //
-// A workgroup takes the graphs whose first vertex lies in its block of
-// `bin` consecutive vertices of the concatenation, up to kSubGraphs graphs of
-// kCap vertices in all at a time, so thousands of tiny graphs share a
-// workgroup and a graph of any size up to kCap has one of its own.
+// A workgroup takes the graphs of its block of `bin` keys (graph_key: vertices,
+// pairs and graphs), up to kSubGraphs graphs of kCap vertices in all at a time, so
+// thousands of tiny graphs share a workgroup and a graph of any size up to kCap, or
+// with many pairs, has one of its own (blocks of vertices alone: 20 graphs of 100
+// vertices and 10^6 pairs in one workgroup, 7.9 ms).
 constexpr int kLdsVertices = 65536;
 constexpr int kLdsSmall = 16384;   // the smaller instance: two workgroups per CU
 constexpr int kLdsThreads = 1024;
@@ -466,8 +467,8 @@ __device__ __forceinline__ int lds_flatten(uint32_t* par, int nv) {
 template <int kCap>
 __global__ void __launch_bounds__(kLdsThreads) cc_lds(
     const int32_t* __restrict__ src, const int32_t* __restrict__ dst, int64_t m, int n,
-    const int64_t* __restrict__ voff, const int64_t* __restrict__ eoff, int G, int bin, int bins,
-    int heavy, int32_t* __restrict__ label, int32_t* __restrict__ status, int32_t* deepest) {
+    const int64_t* __restrict__ voff, const int64_t* __restrict__ eoff, int G, int64_t bin,
+    int bins, int heavy, int32_t* __restrict__ label, int32_t* __restrict__ status, int32_t* deepest) {
   __shared__ uint32_t par[kCap / 2];
   __shared__ int sv[kSubGraphs + 1], se[kSubGraphs + 1];
   __shared__ uint32_t badbits[kSubGraphs / 32];
@@ -482,9 +483,9 @@ __global__ void __launch_bounds__(kLdsThreads) cc_lds(
   const int block = (int)blockIdx.x % bins;
   int64_t g0 = 0, g1 = 1;
   if (voff) {
-    const auto key = [&](int64_t g) { return voff[g]; };
-    g0 = block == 0 ? 0 : count_below<kLdsThreads>(G, (int64_t)block * bin, key);
-    g1 = block == bins - 1 ? G : count_below<kLdsThreads>(G, (int64_t)(block + 1) * bin, key);
+    const auto key = [&](int64_t g) { return graph_key(voff[g], eoff[g], g); };
+    g0 = block == 0 ? 0 : count_below<kLdsThreads>(G, block * bin, key);
+    g1 = block == bins - 1 ? G : count_below<kLdsThreads>(G, (block + 1) * bin, key);
   }
   int deep = 0;
   for (int64_t ga = g0; ga < g1;) {
@@ -599,7 +600,7 @@ __global__ void __launch_bounds__(kLdsThreads) cc_lds(
             const int e = c0 + t * kWave + lane;
             a[t] = b[t] = 0;
             if (e < ne) {
-              while (own < k - 1 && se[own + 1] <= e) ++own;
+              own = find_from(se, k, own, e);
               const int base = sv[own], size = min(sv[own + 1], nv) - base;
               const bool ok = x[t] >= 0 && x[t] < size && y[t] >= 0 && y[t] < size;
               if (!ok) atomicOr(&badbits[own >> 5], 1u << (own & 31));
@@ -644,7 +645,7 @@ __global__ void __launch_bounds__(kLdsThreads) cc_lds(
       for (int t = 0; t < kLdsPer; ++t) {
         const int v = c0 + t * kWave + lane;
         if (v >= nv) break;
-        while (own < k - 1 && sv[own + 1] <= v) ++own;
+        own = find_from(sv, k, own, v);
         label[v0 + v] = half_of(lds_load(par, v), v) - sv[own];
       }
     }
@@ -822,7 +823,7 @@ struct CcRun {
   int32_t* D = nullptr;         // parent array, in the caller's label buffer
   int32_t* status = nullptr;
   bool lds = false;             // every graph in one workgroup's LDS
-  int bin = 1;                  // and the vertices each workgroup answers for
+  int64_t bin = 1;              // and the keys each workgroup answers for (graph_key)
   CcBuffers b;
   hipStream_t stream = nullptr;
   PhaseTimer* tm = nullptr;
@@ -840,21 +841,23 @@ struct CcRun {
 void cc_plan(CcRun& r) {
   const CcSizes& z = r.z;
   const int cus = device_info().cus;
-  const double lds_us = 12 + 0.75e-3 * std::max((double)z.max_n, (double)z.n / cus) +
+  const double lds_us = 12 + 0.75e-3 * std::max((double)z.max_n, (z.n + 8.0 * z.G) / cus) +
                         0.5e-3 * std::max((double)z.max_m, (double)z.m / cus);
   const double device_us = (z.m <= z.n           ? 45
                             : 2 * z.m < 3 * z.n ? 110
                                                 : 60 + 0.6e-3 * std::min<double>(z.n, kLdsVertices)) +
                            z.m / 30000.0;
   r.lds = z.n > 0 && z.max_n <= kLdsVertices && z.max_m <= kLdsPairs && lds_us <= device_us;
-  r.bin = (int)std::min<int64_t>(32768, std::max<int64_t>(2048, z.n / (2 * cus)));
+  r.bin = graph_bin(z.n, z.m, z.G, cus);
 }
 
 // Workgroups of cc_lds per set, the pairs that make a graph heavy (half a CU's
 // share) and the sets: with more workgroups than CUs, a first set takes the
 // heavy graphs, so that none of them starts last (1024 graphs of 2^8..2^16
 // vertices: 410 us with one set, 341 us with two).
-inline int cc_lds_bins(const CcRun& r) { return r.batched ? (int)(r.z.n / r.bin + 1) : 1; }
+inline int cc_lds_bins(const CcRun& r) {
+  return r.batched ? (int)(graph_key(r.z.n, r.z.m, r.z.G) / r.bin + 1) : 1;
+}
 inline int cc_lds_heavy(const CcRun& r) {
   return (int)std::min<int64_t>(kLdsPairs, r.z.m / (2 * device_info().cus));
 }

@@ -19,6 +19,19 @@ namespace pj {
 // `bin` lists, also where thousands of empty ones lie together.
 PJ_RULE int64_t list_key(int64_t off, int64_t l) { return off + l; }
 
+// Graphs likewise, by a key of the work before them: a vertex 1 (0.75 ns of a
+// workgroup's time), a pair 1/2, and a graph 8, as tiny ones cost that much.
+PJ_RULE int64_t graph_key(int64_t voff, int64_t eoff, int64_t g) { return voff + eoff / 2 + 8 * g; }
+
+// Keys of one workgroup: half a compute unit's share of all, but no less than 2048
+// and no more than go with 32768 vertices.
+PJ_RULE int64_t graph_bin(int64_t n, int64_t m, int64_t graphs, int cus) {
+  const int64_t all = graph_key(n, m, graphs);
+  const int64_t share = all / (2 * cus), most = 32768 * (all / (n > 0 ? n : 1));
+  const int64_t bin = share < 2048 ? 2048 : share;
+  return bin < most ? bin : most;
+}
+
 // Of those it takes the ones that fit LDS together, and again.  The table is the
 // device's: it may hold anything, so only a run of entries that each fit after the
 // one before may be indexed with.  An entry relative to the group's first: what

@@ -211,6 +211,24 @@ __device__ __forceinline__ int find_instance(const int64_t* __restrict__ off, in
   return lo;
 }
 
+// Largest i in [at, k) with off[i] <= e, given off[at] <= e, by steps that double:
+// one read where the next entry is past e, and few where thousands follow.
+template <class T, class E>
+__device__ __forceinline__ int find_from(const T* off, int k, int at, E e) {
+  unsigned lo = (unsigned)at, step = 1;
+  while (lo + step < (unsigned)k && off[lo + step] <= e) {
+    lo += step;
+    step *= 2;
+  }
+  unsigned hi = min(lo + step, (unsigned)k) - 1;
+  while (lo < hi) {
+    const unsigned mid = (lo + hi + 1) / 2;
+    if (off[mid] <= e) lo = mid;
+    else hi = mid - 1;
+  }
+  return (int)lo;
+}
+
 // Number of the non-decreasing key(0..count) below `target`, found by all kThreads
 // threads of the workgroup together, kThreads probes a step.
 template <int kThreads, class Key>

@@ -1,6 +1,7 @@
 // CPU model of how cc_lds's two workgroups go over one stretch of the offset
 // tables: on every table, whatever it holds, each graph has exactly one taker,
-// and a group's entries can be indexed with.  Prints OK.
+// and a group's entries can be indexed with; and of the shares of a batch's work
+// that its workgroups get.  Prints OK.
 #include <algorithm>
 #include <cstdio>
 #include <random>
@@ -42,9 +43,52 @@ bool check(const std::vector<int64_t>& voff, const std::vector<int64_t>& eoff, i
   return std::all_of(takers.begin(), takers.end(), [](int t) { return t == 1; });
 }
 
+// The work of every workgroup (0.75 ns a vertex, 0.5 a pair, 6 a graph) is within
+// its share and the largest graph it may end with.
+bool shares(const std::vector<int64_t>& voff, const std::vector<int64_t>& eoff) {
+  const int64_t G = (int64_t)voff.size() - 1, n = voff.back(), m = eoff.back();
+  constexpr int kCus = 256;
+  const int64_t bin = pj::graph_bin(n, m, G, kCus);
+  const auto key = [&](int64_t g) { return pj::graph_key(voff[g], eoff[g], g); };
+  const auto cost = [&](int64_t a, int64_t b) {
+    return 0.75 * (double)(voff[b] - voff[a]) + 0.5 * (double)(eoff[b] - eoff[a]) + 6.0 * (double)(b - a);
+  };
+  double largest = 0;
+  for (int64_t g = 0; g < G; ++g) largest = std::max(largest, cost(g, g + 1));
+  const double share = std::max(cost(0, G) / (2 * kCus), 2048.0);
+  const int64_t bins = key(G) / bin + 1;
+  if (bins > 8 * kCus + n / 2048) return false;
+  int64_t at = 0;
+  for (int64_t b = 0; b < bins; ++b) {
+    int64_t end = at;
+    while (end < G && (b == bins - 1 || key(end) < (b + 1) * bin)) ++end;
+    if (cost(at, end) > 2 * share + largest) return false;
+    at = end;
+  }
+  return at == G;
+}
+
+bool all_shares() {
+  const auto table = [](std::vector<int64_t> sizes) {
+    std::vector<int64_t> off{0};
+    for (const int64_t s : sizes) off.push_back(off.back() + s);
+    return off;
+  };
+  const auto same = [](size_t count, int64_t size) { return std::vector<int64_t>(count, size); };
+  std::vector<int64_t> crowd = same(1000000, 0);  // empty graphs before others
+  crowd.insert(crowd.end(), 1000, 100);
+  return shares(table(same(20, 100)), table(same(20, 1000000))) &&       // small and dense
+         shares(table(same(1000, 20)), table(same(1000, 50000))) &&
+         shares(table(same(500000, 1)), table(same(500000, 1))) &&
+         shares(table(crowd), table(crowd)) && shares(table(same(3, 1000)), table(same(3, 1500))) &&
+         shares(table(same(1024, 11000)), table(same(1024, 50000))) &&
+         shares(table(same(5, 65536)), table(same(5, 0)));
+}
+
 }  // namespace
 
 int main() {
+  if (!all_shares()) return printf("shares\n"), 1;
   std::mt19937_64 rng(7);
   const auto below = [&](int64_t n) { return (int64_t)(rng() % (uint64_t)n); };
   // 3 * 10^9 pairs: a heavy graph behind more than 2^31 pairs of light ones

@@ -69,3 +69,39 @@ def test_lists(pj, longs, size, empties):
         assert np.array_equal(rank.cpu().numpy(), want)
         assert (st.cpu().numpy() == pj.PJ_OK).all()
     assert ms["together"] < 4 * ms["spread"], ms
+
+
+# graphs of few vertices and many pairs, of one vertex, and empty ones in one
+# place: chunks of pairs that hold hundreds of graphs, and thousands that hold one
+@pytest.mark.parametrize("case", ["dense", "one_vertex", "empty", "pairs_behind"])
+@pytest.mark.parametrize("how", ["host", "device", "graph"])
+def test_graphs(pj, case, how):
+    rng = np.random.default_rng(3)
+    if case == "dense":
+        sizes, pairs = np.full(20, 100), np.full(20, 200_000)
+    elif case == "one_vertex":
+        sizes, pairs = np.ones(100_000, np.int64), rng.integers(0, 3, 100_000)
+    elif case == "empty":
+        sizes = np.concatenate([np.full(60, 900), np.zeros(300_000, np.int64), np.full(60, 3000)])
+        pairs = sizes * 3 // 2
+    else:                       # all the pairs in the last of many graphs
+        sizes, pairs = np.full(3000, 50), np.zeros(3000, np.int64)
+        pairs[-5:] = 300_000
+    voff = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    eoff = np.concatenate([[0], np.cumsum(pairs)]).astype(np.int64)
+    bound = np.repeat(sizes, pairs)
+    src = (rng.random(bound.shape[0]) * bound).astype(np.int32)
+    dst = (rng.random(bound.shape[0]) * bound).astype(np.int32)
+    want = oracle.connected_components_batched(src, dst, voff, eoff)
+    kw = {} if how == "device" else {"h_vtx_off": voff, "h_edge_off": eoff}
+    if how == "graph":
+        kw["use_graph"] = True
+    st = torch.full((len(sizes),), 7, dtype=torch.int32, device="cuda")
+    label = torch.full((int(voff[-1]),), -3, dtype=torch.int32, device="cuda")
+    args = [dev(a) for a in (src, dst, voff, eoff)]
+    for _ in range(2):
+        pj.connected_components_batched(*args, label, status=st, **kw)
+        torch.cuda.synchronize()
+        assert np.array_equal(label.cpu().numpy(), want)
+        assert (st.cpu().numpy() == pj.PJ_OK).all()
+    pj.graph_cache_clear()
