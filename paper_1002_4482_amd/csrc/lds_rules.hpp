@@ -32,7 +32,28 @@ PJ_RULE int64_t graph_bin(int64_t n, int64_t m, int64_t graphs, int cus) {
   return bin < most ? bin : most;
 }
 
-// Of those it takes the ones that fit LDS together, and again.  The table is the
+// Size of the largest instance of a host's table (INT64_MAX where it is seen to
+// decrease).  Sizes up to kSmallInstance are not told apart: 64 instances that
+// are no more together are looked at as one, as a pass over a table of 10^6 graphs
+// takes as long as its solve.
+constexpr int64_t kSmallInstance = 2048;
+inline int64_t largest_instance(const int64_t* off, int64_t count) {
+  constexpr int64_t kStep = 64;
+  int64_t most = 0;
+  for (int64_t g = 0; g < count; g += kStep) {
+    const int64_t end = g + kStep < count ? g + kStep : count;
+    const int64_t all = off[end] - off[g];
+    if (all >= 0 && all <= kSmallInstance) continue;
+    for (int64_t i = g; i < end; ++i) {
+      const int64_t size = off[i + 1] - off[i];
+      if (size < 0) return INT64_MAX;
+      if (size > most) most = size;
+    }
+  }
+  return most;
+}
+
+// Of its instances a workgroup takes the ones that fit LDS together, and again.  The table is the
 // device's: it may hold anything, so only a run of entries that each fit after the
 // one before may be indexed with.  An entry relative to the group's first: what
 // no table of this size can hold does not fit.

@@ -85,9 +85,29 @@ bool all_shares() {
          shares(table(same(5, 65536)), table(same(5, 0)));
 }
 
+// The largest size of a table, where it is more than kSmallInstance.
+bool largest() {
+  std::mt19937_64 rng(3);
+  for (int run = 0; run < 2000; ++run) {
+    const int64_t count = 1 + (int64_t)(rng() % 700);
+    const uint64_t size = 1 + rng() % (run % 2 ? 40 : 4000);
+    std::vector<int64_t> off{0};
+    for (int64_t i = 0; i < count; ++i)
+      off.push_back(off.back() + (int64_t)(rng() % 100 ? rng() % size : 50 * size));
+    int64_t most = 0;
+    for (int64_t i = 0; i < count; ++i) most = std::max(most, off[i + 1] - off[i]);
+    const int64_t got = pj::largest_instance(off.data(), count);
+    if (got > most || (got < most && most > pj::kSmallInstance)) return false;
+    off.back() = -5;
+    if (pj::largest_instance(off.data(), count) != INT64_MAX) return false;
+  }
+  return true;
+}
+
 }  // namespace
 
 int main() {
+  if (!largest()) return printf("largest\n"), 1;
   if (!all_shares()) return printf("shares\n"), 1;
   std::mt19937_64 rng(7);
   const auto below = [&](int64_t n) { return (int64_t)(rng() % (uint64_t)n); };
