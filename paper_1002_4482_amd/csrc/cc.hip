@@ -848,7 +848,8 @@ struct CcRun {
 // LDS or the whole device: microseconds of a workgroup with the largest graph or
 // with a CU's share of all, and of the device-wide kernels' launches and
 // dependent passes (few for forests, long climbs in sparse graphs with cycles,
-// three parts otherwise), which then join 30000 pairs a microsecond.  Measured,
+// three parts otherwise), which then join 30000 pairs a microsecond, 75000 in
+// smaller graphs.  Measured,
 // LDS and device-wide, vertices / pairs: uniform 10000 / 20000 29 and 63, 20000 /
 // 40000 48 and 71, 40000 / 80000 83 and 87, 60000 / 120000 119 and 85, 60000 /
 // 80000 99 and 113, 60000 / 40000 70 and 49; planted 10000 / 80000 46 and 57,
@@ -862,7 +863,7 @@ void cc_plan(CcRun& r) {
   const double device_us = (z.m <= z.n           ? 45
                             : 2 * z.m < 3 * z.n ? 110
                                                 : 60 + 0.6e-3 * std::min<double>(z.n, kLdsVertices)) +
-                           z.m / 30000.0;
+                           z.m / (z.n < kHalveSmallBelow ? 75000.0 : 30000.0);
   r.lds = z.n > 0 && z.max_n <= kLdsVertices && z.max_m <= kLdsPairs && lds_us <= device_us;
   r.bin = graph_bin(z.n, z.m, z.G, cus);
 }
@@ -957,13 +958,17 @@ int cc_enqueue(CcRun& r) {
       // each on a flat forest, and the rest, most of which is settled by then.
       // Swapping all pairs at once climbs unfinished trees: 2^22 vertices and
       // 2^25 pairs 2480 us, in parts 950 us; 10^6 and 2.2 * 10^6 473 and 215.
-      const int64_t blind_stride = std::max<int64_t>(1, z.m / z.n / 2);
+      // Four chunks are hooked blind and two swapped, at least, of each graph: without
+      // them the rest would all meet at few roots (1000 vertices and 10^7 pairs
+      // 350 us, with them 80).
+      const int64_t spread = std::max<int64_t>(1, nchunks / (4 * z.G));
+      const int64_t blind_stride = std::max<int64_t>(1, std::min(z.m / z.n / 2, spread));
       const int64_t blind = (nchunks + blind_stride - 1) / blind_stride;
       hipLaunchKernelGGL(cc_hook_blind, dim3(grid_for(blind, 1, cap)), dim3(256), 0, stream, es,
                          ed, z.m, n, r.D, blind_stride, blind, b.ctl);
       mark(r, "hook_blind");
       flatten();
-      const int64_t stride = std::max<int64_t>(2, 2 * (z.m / z.n));
+      const int64_t stride = std::max<int64_t>(2, std::min(2 * (z.m / z.n), 2 * spread));
       const int64_t swapped = nchunks / stride;
       if (swapped > 0) {
         hook(stride, swapped);

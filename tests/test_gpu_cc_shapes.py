@@ -50,3 +50,28 @@ def test_hub(pj, n):
     first = solve_ms(pj, np.zeros(n - 1), i + 1, n)
     last = solve_ms(pj, np.full(n - 1, n - 1), i, n)   # every pair meets at the hub's parent
     assert last < 8 * max(first, 0.04), (first, last)
+
+
+# many pairs on few vertices: one graph, and a batch whose graphs lie one after
+# another in the pairs and have one pair in 65537 vertices beside them
+@pytest.mark.parametrize("n,m", [(2, 300_000), (100, 2048), (100, 2049), (100, 4096), (100, 4097),
+                                 (100, 1_000_000), (1000, 1_000_000)])
+def test_few_vertices(pj, n, m):
+    src, dst = np.random.default_rng(n + m).integers(0, n, (2, m))
+    solve_ms(pj, src, dst, n)
+
+
+@pytest.mark.parametrize("beside", [0, 65_537])
+def test_few_vertices_each(pj, beside):
+    rng = np.random.default_rng(5)
+    sizes = np.array([100] * 20 + [beside])
+    pairs = np.array([200_000] * 20 + [min(beside, 1)])
+    voff = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    eoff = np.concatenate([[0], np.cumsum(pairs)]).astype(np.int64)
+    bound = np.repeat(sizes, pairs)
+    src, dst = ((rng.random(bound.shape[0]) * bound).astype(np.int32) for _ in range(2))
+    got = pj.connected_components_batched(dev(src), dev(dst), torch.from_numpy(voff).cuda(),
+                                          torch.from_numpy(eoff).cuda(), h_vtx_off=voff,
+                                          h_edge_off=eoff)
+    assert np.array_equal(got.cpu().numpy(),
+                          oracle.connected_components_batched(src, dst, voff, eoff))
