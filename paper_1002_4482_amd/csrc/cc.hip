@@ -39,6 +39,9 @@ constexpr int kClasses = 255;
 struct CcCtl {
   int32_t err;
   int32_t steps;                // longest chain of parent steps of a shortcut, up to kFlatHops
+  int32_t ordered;              // the ids follow the graph (sample_order)
+  int32_t again;                // pairs were given up and are still to be joined
+  int32_t redo;                 // joining them joined trees: one more shortcut
   int32_t classes;              // numbered parents (cc_class_pick), 0: not used
   int32_t parents[kClasses];
 };
@@ -58,23 +61,44 @@ struct CcCtl {
 //   * The shortcut's stores are plain: each word has one writer in the kernel.
 
 // Joins the trees of x and y.  Both only ever move to a parent, the larger
-// first, so the loop ends after at most x + y steps even on stale values;
-// after `halve` steps it halves the path, which keeps long chains (paths whose
-// ids follow their order) from being climbed link by link.  In a large forest
-// that starts late: the stores of a giant component's pairs go to the few
-// nodes under its root and serialise there (2^20 pairs of a 2^22-vertex uniform
-// graph on a quarter of the roots: 450 us from the 3rd step on, 240 us from the
-// 16th); a small one is bound by the chain of reads instead (300000 vertices:
-// 70 us against 79 us).
+// first, so the loop ends after at most x + y steps even on stale values.
+//
+// After `halve` steps it halves the path.  In a large forest that starts late:
+// the stores of a giant component's pairs go to the few nodes under its root and
+// serialise there (2^20 pairs of a 2^22-vertex uniform graph on a quarter of the
+// roots: 450 us from the 3rd step on, 240 us from the 16th); a small one is bound
+// by the chain of reads instead (300000 vertices: 70 us against 79 us).
+//
+// Hooks may chain every vertex to the one before, and then a pair that meets the
+// chain climbs as far as the graph is long, with nobody else on the way (a ring of
+// 4 * 10^6 vertices in id order: 1.03 s, nearly all for the pair that closes it).
+// So a pair is given up after `most` steps, and its chunk of pairs is marked and
+// read again once a shortcut has flattened the chains (that ring: 0.37 ms).
 //
 // The lanes of a wave that hook the same root send one swap: the pairs of a hub
 // with the largest id all meet at the hub's parent, and swaps on one word run at
 // 88 M/s (a star of 4 * 10^6 vertices 3.26 ms, with one swap a wave 0.18).
 constexpr int kHalveSmall = 3, kHalveLarge = 16;
 constexpr int64_t kHalveSmallBelow = 1 << 20;
+constexpr int kNever = INT32_MAX;
 
-__device__ __forceinline__ void join(int32_t* D, int x, int y, int halve) {
+// Steps before the path is halved, before a pair is given up, and before the
+// others of its thread are after that.  With random ids a few pairs of many
+// millions take more than 24 (8 M in paths 720 us with 24, 697 with 32 and 48).
+// Where ids follow the graph thousands may climb at once, and those that halve
+// their paths meet at the same few nodes (a path of 2 * 10^6 vertices and as many
+// between them, a grid of width 300: swaps of 1.6 ms, 41 us without halving).
+struct Climb {
+  int halve, most, after;
+};
+constexpr Climb kClimbSmall{kHalveSmall, 48, 8}, kClimbLarge{kHalveLarge, 48, 8};
+constexpr Climb kClimbOrdered{kNever, 24, 4};
+
+enum Joined { kSame, kHooked, kLeft };
+
+__device__ __forceinline__ Joined join(int32_t* D, int x, int y, int halve, int most) {
   for (int step = 1; x != y; ++step) {
+    if (step > most) return kLeft;
     const int hi = max(x, y);
     y = min(x, y);
     x = hi;
@@ -86,7 +110,7 @@ __device__ __forceinline__ void join(int32_t* D, int x, int y, int halve) {
       const int got = __builtin_amdgcn_readfirstlane(p);
       const int to = __builtin_amdgcn_readfirstlane(y);
       if (!swaps) p = got == x ? to : got;
-      else if (p == x) return;
+      else if (p == x) return kHooked;
     } else if (step > halve) {
       const int g = load_coherent(&D[p]);
       if (g != p) publish(&D[x], g);
@@ -94,16 +118,69 @@ __device__ __forceinline__ void join(int32_t* D, int x, int y, int halve) {
     }
     x = p;
   }
+  return kSame;
 }
 
-__global__ void __launch_bounds__(256) cc_init(int32_t* __restrict__ D, int n, CcCtl* ctl) {
+// Marks a chunk that holds pairs given up: for cc_hook_rest, which reads the
+// others anyway, or for the last kernels.
+constexpr int32_t kForRest = 1, kForLast = 2;
+
+__device__ __forceinline__ void mark_left(int32_t* left, int64_t chunk, bool any, int32_t how,
+                                          CcCtl* ctl) {
+  if (__ballot(any) && lane_id() == 0) {
+    publish(&left[chunk], how);
+    if (how == kForLast) publish(&ctl->again, 1);
+  }
+}
+
+// Whether the ids follow the graph: one workgroup counts, of 1024 sampled pairs,
+// how many distances of ids differ (in steps of n / 2^14).  With random ids nearly
+// all do; where paths, rings, grids or layers are numbered in order few do.
+constexpr int kSamples = 1024;
+
+__device__ __forceinline__ void sample_order(const int32_t* __restrict__ src,
+                                             const int32_t* __restrict__ dst, int64_t m, int n,
+                                             CcCtl* ctl) {
+  constexpr int kSlots = 4 * kSamples;
+  __shared__ int slot[kSlots], distinct;
+  const int tid = threadIdx.x;
+  unsigned away[kSamples / 256];
+#pragma unroll
+  for (int t = 0; t < kSamples / 256; ++t) {
+    const uint32_t i = t * 256 + tid + 1;
+    const int64_t e = (int64_t)(((uint64_t)mix32(i) << 20 ^ mix32(i + kSamples)) % (uint64_t)m);
+    const unsigned d = (unsigned)src[e] - (unsigned)dst[e];
+    away[t] = min(d, 0u - d) / (unsigned)max(1, n >> 14);  // (2^31 at most)
+  }
+  for (int i = tid; i < kSlots; i += 256) slot[i] = -1;
+  if (tid == 0) distinct = 0;
+  __syncthreads();
+  int mine = 0;
+#pragma unroll
+  for (int t = 0; t < kSamples / 256; ++t)
+    for (uint32_t h = mix32(away[t]);; ++h) {  // a quarter of the slots is taken at most
+      const int old = atomicCAS(&slot[h % kSlots], -1, (int)away[t]);
+      mine += old == -1;
+      if (old == -1 || old == (int)away[t]) break;
+    }
+  atomicAdd(&distinct, mine);
+  __syncthreads();
+  if (tid == 0) ctl->ordered = distinct < kSamples * 7 / 8;
+}
+
+__global__ void __launch_bounds__(256) cc_init(int32_t* __restrict__ D, int n, CcCtl* ctl,
+                                               int32_t* __restrict__ left, int64_t nchunks,
+                                               const int32_t* __restrict__ src,
+                                               const int32_t* __restrict__ dst, int64_t sampled) {
   const int tid = blockIdx.x * blockDim.x + threadIdx.x;
   const int stride = gridDim.x * blockDim.x;
+  if (tid < (int)(offsetof(CcCtl, parents) / 4)) reinterpret_cast<int32_t*>(ctl)[tid] = 0;
+  if (blockIdx.x == 0 && sampled > 0) sample_order(src, dst, sampled, n, ctl);
   const int n4 = (reinterpret_cast<uintptr_t>(D) & 15) == 0 ? n >> 2 : 0;
   for (int q = tid; q < n4; q += stride)
     reinterpret_cast<int4*>(D)[q] = make_int4(4 * q, 4 * q + 1, 4 * q + 2, 4 * q + 3);
   for (int v = 4 * n4 + tid; v < n; v += stride) D[v] = v;
-  if (tid < (int)(offsetof(CcCtl, parents) / 4)) reinterpret_cast<int32_t*>(ctl)[tid] = 0;
+  for (int64_t c = tid; c < nchunks; c += stride) left[c] = 0;
 }
 
 // kPer rows of 256 pairs from row `row` on, loaded and range-checked: an id out
@@ -132,18 +209,25 @@ __device__ __forceinline__ void report(CcCtl* ctl, bool bad) {
   if (__ballot(bad) && lane_id() == 0) atomicOr(&ctl->err, kErrRange);
 }
 
-// First hooks of a graph with many pairs, blind: every stride-th chunk's pairs
-// store their smaller end as the larger end's parent, no read and no swap (85
-// G stores/s against 27 G swaps/s).  One of the pairs of a vertex wins; the
-// others join nothing yet, and cc_hook_rest reads all of them again.
+// First hooks, blind: every stride-th chunk's pairs store their smaller end as the
+// larger end's parent, no read and no swap (85 G stores/s against 27 G swaps/s).
+// One of the pairs of a vertex wins; the others join nothing yet, and all of them
+// are read again.  A workgroup more than those samples the order of the ids.
 constexpr int kHookPer = 8;
 
 __global__ void __launch_bounds__(256) cc_hook_blind(const int32_t* __restrict__ src,
                                                      const int32_t* __restrict__ dst, int64_t m,
                                                      int n, int32_t* __restrict__ D,
-                                                     int64_t stride, int64_t units, CcCtl* ctl) {
+                                                     int64_t stride, int64_t units,
+                                                     const int32_t* only_if, CcCtl* ctl) {
+  if (only_if && *only_if == 0) return;
+  if (!only_if && blockIdx.x == gridDim.x - 1) {  // (cc_init has sampled otherwise)
+    sample_order(src, dst, m, n, ctl);
+    return;
+  }
+  const int64_t groups = gridDim.x - (only_if ? 0 : 1);
   bool bad = false;
-  for (int64_t i = blockIdx.x; i < units; i += gridDim.x) {
+  for (int64_t i = blockIdx.x; i < units; i += groups) {
     int x[kHookPer], y[kHookPer];
     bad |= load_pairs(src, dst, m, n, i * stride * kHookPer, x, y);
 #pragma unroll
@@ -153,20 +237,26 @@ __global__ void __launch_bounds__(256) cc_hook_blind(const int32_t* __restrict__
   report(ctl, bad);
 }
 
-// Hooks the pairs of the chunks stride - 1, 2 * stride - 1, ...
+// Hooks the pairs of the chunks stride - 1, 2 * stride - 1, ..., and leaves those
+// given up to the kernels that `how` says.
 template <int kPer>
 __global__ void __launch_bounds__(256) cc_hook(const int32_t* __restrict__ src,
                                                const int32_t* __restrict__ dst, int64_t m, int n,
                                                int32_t* D, int64_t stride, int64_t units,
-                                               int halve, CcCtl* ctl) {
+                                               Climb climb, int32_t* left, int32_t how,
+                                               CcCtl* ctl) {
+  if (ctl->ordered) climb = kClimbOrdered;
   bool bad = false;
   for (int64_t i = blockIdx.x; i < units; i += gridDim.x) {
     int x[kPer], y[kPer];
     constexpr int kParts = kHookPer / kPer;
     const int64_t c = (i / kParts + 1) * stride - 1;
     bad |= load_pairs(src, dst, m, n, c * kHookPer + i % kParts * kPer, x, y);
+    bool any = false;
 #pragma unroll
-    for (int t = 0; t < kPer; ++t) join(D, x[t], y[t], halve);
+    for (int t = 0; t < kPer; ++t)
+      any |= join(D, x[t], y[t], climb.halve, any ? climb.after : climb.most) == kLeft;
+    mark_left(left, c, any, how, ctl);
   }
   report(ctl, bad);
 }
@@ -262,19 +352,25 @@ __global__ void __launch_bounds__(256) cc_class_fill(const int32_t* __restrict__
   }
 }
 
-// Hooks the pairs of all the other chunks, most of which lie in one tree by
-// now: two reads (of classes, or of D) settle those, the rest is gathered in
+// Hooks the pairs of all the other chunks, and of the `swapped` ones where pairs
+// were given up, most of which lie in one tree by now: two reads (of classes, or of D) settle those, the rest is gathered in
 // LDS first so that the lanes of a wave climb together.
 template <bool kClassed>
 __device__ __forceinline__ void hook_rest(const int32_t* __restrict__ src,
                                           const int32_t* __restrict__ dst, int64_t m, int n,
                                           int32_t* D, const uint8_t* __restrict__ cls,
-                                          int64_t stride, int64_t units, CcCtl* ctl, int2* queue,
-                                          int* queued) {
+                                          int64_t stride, int64_t units, int64_t swapped,
+                                          int32_t* left, CcCtl* ctl, int2* queue, int* queued) {
+  const Climb climb = ctl->ordered ? kClimbOrdered : kClimbLarge;
   bool bad = false;
-  for (int64_t i = blockIdx.x; i < units; i += gridDim.x) {
+  for (int64_t i = blockIdx.x; i < units + swapped; i += gridDim.x) {
+    int64_t c = i / (stride - 1) * stride + i % (stride - 1);
+    if (i >= units) {
+      c = (i - units + 1) * stride - 1;
+      if (left[c] == 0) continue;
+    }
     int x[kHookPer], y[kHookPer];
-    bad |= load_pairs(src, dst, m, n, (i / (stride - 1) * stride + i % (stride - 1)) * kHookPer, x, y);
+    bad |= load_pairs(src, dst, m, n, c * kHookPer, x, y);
     if (threadIdx.x == 0) *queued = 0;
     int cx[kHookPer], cy[kHookPer];
 #pragma unroll
@@ -295,7 +391,10 @@ __device__ __forceinline__ void hook_rest(const int32_t* __restrict__ src,
     }
     __syncthreads();
     const int total = *queued;
-    for (int q = threadIdx.x; q < total; q += 256) join(D, queue[q].x, queue[q].y, kHalveLarge);
+    bool any = false;
+    for (int q = threadIdx.x; q < total; q += 256)
+      any |= join(D, queue[q].x, queue[q].y, climb.halve, any ? climb.after : climb.most) == kLeft;
+    mark_left(left, c, any, kForLast, ctl);
     __syncthreads();  // the queue is reused by the next chunk
   }
   report(ctl, bad);
@@ -305,13 +404,33 @@ __global__ void __launch_bounds__(256) cc_hook_rest(const int32_t* __restrict__ 
                                                     const int32_t* __restrict__ dst, int64_t m,
                                                     int n, int32_t* D,
                                                     const uint8_t* __restrict__ cls,
-                                                    int64_t stride, int64_t units, CcCtl* ctl) {
+                                                    int64_t stride, int64_t units, int64_t swapped,
+                                                    int32_t* left, CcCtl* ctl) {
   __shared__ int2 queue[256 * kHookPer];
   __shared__ int queued;
   if (cls && ctl->classes > 0)
-    hook_rest<true>(src, dst, m, n, D, cls, stride, units, ctl, queue, &queued);
+    hook_rest<true>(src, dst, m, n, D, cls, stride, units, swapped, left, ctl, queue, &queued);
   else
-    hook_rest<false>(src, dst, m, n, D, cls, stride, units, ctl, queue, &queued);
+    hook_rest<false>(src, dst, m, n, D, cls, stride, units, swapped, left, ctl, queue, &queued);
+}
+
+// The pairs still given up, on a flat forest, to the end.  Nearly always there are
+// none.
+__global__ void __launch_bounds__(256) cc_join_left(const int32_t* __restrict__ src,
+                                                    const int32_t* __restrict__ dst, int64_t m,
+                                                    int n, int32_t* D, int64_t nchunks,
+                                                    const int32_t* __restrict__ left, CcCtl* ctl) {
+  if (ctl->again == 0) return;
+  bool hooked = false;
+  for (int64_t c = blockIdx.x; c < nchunks; c += gridDim.x) {
+    if (left[c] != kForLast) continue;
+    int x[kHookPer], y[kHookPer];
+    (void)load_pairs(src, dst, m, n, c * kHookPer, x, y);
+#pragma unroll
+    for (int t = 0; t < kHookPer; ++t)
+      hooked |= join(D, x[t], y[t], kHalveSmall, kNever) == kHooked;
+  }
+  if (__ballot(hooked) && lane_id() == 0) publish(&ctl->redo, 1);
 }
 
 // Shortcut: D[v] <- its root, in one pass whatever the depth.  Hooks leave trees
@@ -331,14 +450,23 @@ __global__ void __launch_bounds__(256) cc_hook_rest(const int32_t* __restrict__ 
 // thread, one by one: with two there is less above that is flat already (10^6
 // 252 us), with six too few lanes in small graphs; only deep ones climb side by
 // side (a path of 2^20 ids in order, doubled: 554 us, one by one 792).
-__global__ void __launch_bounds__(256) cc_flatten(int32_t* D, int n, CcCtl* ctl) {
-  const int64_t v0 = (int64_t)blockIdx.x * (256 * kFlatPer) + threadIdx.x;
-  int up[kFlatPer];  // of the deep vertices: the ancestor reached
+//
+// only_if: only if that word is not 0.  Nearly always it is, so the workgroups are
+// larger: 8000 of 256 threads that end at once take 17 us.  (Fewer that take runs
+// from a counter either wait for it, 2^22 vertices 160 us instead of 60, or take
+// the next run ahead, and others then climb through the vertices of runs that are
+// held and not begun: a path of 2^22 ids in order 137 ms.)
+template <int kThreads>
+__global__ void __launch_bounds__(kThreads) cc_flatten(int32_t* D, int n, const int32_t* only_if,
+                                                       CcCtl* ctl) {
+  if (only_if && *only_if == 0) return;
+  const int64_t v0 = (int64_t)blockIdx.x * (kThreads * kFlatPer) + threadIdx.x;
   int most = 0;
+  int up[kFlatPer];  // of the deep vertices: the ancestor reached
   bool deep = false;
 #pragma unroll
   for (int t = 0; t < kFlatPer; ++t) {  // one by one: the later find flat trees above
-    const int64_t v = v0 + t * 256;
+    const int64_t v = v0 + t * kThreads;
     up[t] = -1;
     if (v >= n) continue;
     const int p0 = D[v];
@@ -372,7 +500,7 @@ __global__ void __launch_bounds__(256) cc_flatten(int32_t* D, int n, CcCtl* ctl)
     }
 #pragma unroll
     for (int t = 0; t < kFlatPer; ++t)
-      if (up[t] >= 0) publish(&D[v0 + t * 256], up[t]);
+      if (up[t] >= 0) publish(&D[v0 + t * kThreads], up[t]);
     deep = left;
   }
   most = -wave_min(-most);
@@ -793,9 +921,15 @@ inline int grid_for(int64_t n, int block, int cap) {
 // 515 us with them (planted components; 33 us to make them).
 inline bool use_classes(int64_t n, int64_t m) { return n >= (3 << 19) && m >= 3 * n; }
 
+// Sparse graphs from this size on are hooked blind first only if ids follow them.
+constexpr int64_t kGatedFrom = 1 << 21;
+
+inline int64_t hook_chunks(int64_t m) { return (m + 256 * kHookPer - 1) / (256 * kHookPer); }
+
 struct CcBuffers {
   CcCtl* ctl = nullptr;
   uint32_t* cls = nullptr;               // class bytes, four to a word
+  int32_t* left = nullptr;               // a mark per chunk of pairs (mark_left)
   int32_t* gsrc = nullptr;
   int32_t* gdst = nullptr;
   int32_t* gerr = nullptr;               // batched: per-graph out-of-range flag
@@ -812,6 +946,7 @@ size_t cc_carve(int64_t n, int64_t m, int64_t G, bool globalise, bool want_statu
   };
   take(b->ctl, 1);
   if (use_classes(n, m)) take(b->cls, (size_t)((n + 3) / 4));
+  take(b->left, (size_t)std::max<int64_t>(hook_chunks(m), 1));
   if (globalise) {
     take(b->gsrc, (size_t)std::max<int64_t>(m, 1));
     take(b->gdst, (size_t)std::max<int64_t>(m, 1));
@@ -860,9 +995,9 @@ void cc_plan(CcRun& r) {
   const int cus = device_info().cus;
   const double lds_us = 12 + 0.75e-3 * std::max((double)z.max_n, (z.n + 8.0 * z.G) / cus) +
                         0.5e-3 * std::max((double)z.max_m, (double)z.m / cus);
-  const double device_us = (z.m <= z.n           ? 45
+  const double device_us = (z.m <= z.n           ? 57
                             : 2 * z.m < 3 * z.n ? 110
-                                                : 60 + 0.6e-3 * std::min<double>(z.n, kLdsVertices)) +
+                                                : 65 + 0.6e-3 * std::min<double>(z.n, kLdsVertices)) +
                            z.m / (z.n < kHalveSmallBelow ? 75000.0 : 30000.0);
   r.lds = z.n > 0 && z.max_n <= kLdsVertices && z.max_m <= kLdsPairs && lds_us <= device_us;
   r.bin = graph_bin(z.n, z.m, z.G, cus);
@@ -896,12 +1031,14 @@ int cc_enqueue(CcRun& r) {
   CcBuffers& b = r.b;
   hipStream_t stream = r.stream;
   const int n = (int)z.n;
-  const int cap = device_info().cus * 16;
+  const int cus = device_info().cus;
+  const int cap = cus * 16;
   const int gv = grid_for(z.n, 256, cap);
   if (r.lds) {
     int32_t* deepest = nullptr;
     if (r.tm && r.tm->on) {
-      hipLaunchKernelGGL(cc_init, dim3(1), dim3(256), 0, stream, r.D, 0, b.ctl);
+      hipLaunchKernelGGL(cc_init, dim3(1), dim3(256), 0, stream, r.D, 0, b.ctl, nullptr,
+                         0, nullptr, nullptr, 0);
       deepest = &b.ctl->steps;
     }
     const auto k = z.max_n <= kLdsSmall ? cc_lds<kLdsSmall> : cc_lds<kLdsVertices>;
@@ -925,33 +1062,50 @@ int cc_enqueue(CcRun& r) {
       ed = b.gdst;
     }
   }
+  const int64_t nchunks = hook_chunks(z.m);
+  const bool sparse = 2 * z.m < 3 * z.n, gated = sparse && z.n >= kGatedFrom;
   hipLaunchKernelGGL(cc_init, dim3(grid_for(z.n / 4, 256, cap)), dim3(256), 0, stream, r.D, n,
-                     b.ctl);
+                     b.ctl, b.left, nchunks, es, ed, gated ? z.m : 0);
   PJ_HIP(hipGetLastError());
   mark(r, "init");
-  const auto flatten = [&] {
-    hipLaunchKernelGGL(cc_flatten, dim3(grid_for(z.n, 256 * kFlatPer, INT32_MAX)), dim3(256), 0,
-                       stream, r.D, n, b.ctl);
+  const auto flatten = [&](const int32_t* only_if = nullptr) {
+    const int threads = only_if ? 1024 : 256;
+    hipLaunchKernelGGL(only_if ? cc_flatten<1024> : cc_flatten<256>,
+                       dim3(grid_for(z.n, threads * kFlatPer, INT32_MAX)), dim3(threads), 0, stream,
+                       r.D, n, only_if, b.ctl);
     mark(r, "shortcut");
   };
+  const auto hook_blind = [&](int64_t stride, const int32_t* only_if) {
+    const int64_t units = (nchunks + stride - 1) / stride;
+    const int groups = only_if ? grid_for(units, 1, 8 * cus) : grid_for(units, 1, cap) + 1;
+    hipLaunchKernelGGL(cc_hook_blind, dim3(groups), dim3(256), 0, stream, es, ed, z.m, n, r.D,
+                       stride, units, only_if, b.ctl);
+    mark(r, "hook_blind");
+  };
   if (z.m > 0) {
-    const int64_t nchunks = (z.m + 256 * kHookPer - 1) / (256 * kHookPer);
-    const int halve = z.n < kHalveSmallBelow ? kHalveSmall : kHalveLarge;
+    const Climb climb = z.n < kHalveSmallBelow ? kClimbSmall : kClimbLarge;
     const auto hook = [&](int64_t stride, int64_t chunks) {
       // two pairs a thread where eight would leave CUs without work (200000
       // vertices in paths 73 us instead of 91); no more of them at once than
       // that in a graph with many pairs, whose joins meet at few roots (300000
       // vertices, 450000 pairs: 127 us with eight, 212 with two)
-      const bool few = chunks < device_info().cus / (stride > 1 ? 4 : 2);
+      const bool few = chunks < cus / (stride > 1 ? 4 : 2);
       const int64_t units = few ? chunks * (kHookPer / 2) : chunks;
       hipLaunchKernelGGL(few ? cc_hook<2> : cc_hook<kHookPer>, dim3(grid_for(units, 1, cap)),
-                         dim3(256), 0, stream, es, ed, z.m, n, r.D, stride, units, halve, b.ctl);
+                         dim3(256), 0, stream, es, ed, z.m, n, r.D, stride, units, climb, b.left,
+                         stride > 1 ? kForRest : kForLast, b.ctl);
       mark(r, "hook");
     };
-    if (2 * z.m < 3 * z.n) {
-      // Paths, trees and sparser: almost every pair joins two trees, so nothing
-      // is spared by parts (64 paths, 8 M pairs: 530 us for the swaps and the
-      // reads of both ends, which run at 27 and 63 G/s).
+    if (sparse) {
+      // Paths, trees and sparser: all pairs blind, a shortcut, and swaps.  Where the
+      // ids follow the graph the first settles nearly all (10^6 vertices in rings
+      // of 100 in order: 58 us, 364 with swaps alone).  With random ids almost
+      // every pair joins two trees, so a large graph spares nothing by it: 64
+      // paths, 8 M pairs, 700 us with swaps alone, 530 of them for the swaps and
+      // the reads of both ends, which run at 27 and 63 G/s, and 790 with all three;
+      // 10^6 vertices 179 and 176.
+      hook_blind(1, gated ? &b.ctl->ordered : nullptr);
+      flatten(gated ? &b.ctl->ordered : nullptr);
       hook(1, nchunks);
     } else {
       // Blind hooks of about two pairs a vertex, swaps of half a pair a vertex,
@@ -962,11 +1116,7 @@ int cc_enqueue(CcRun& r) {
       // them the rest would all meet at few roots (1000 vertices and 10^7 pairs
       // 350 us, with them 80).
       const int64_t spread = std::max<int64_t>(1, nchunks / (4 * z.G));
-      const int64_t blind_stride = std::max<int64_t>(1, std::min(z.m / z.n / 2, spread));
-      const int64_t blind = (nchunks + blind_stride - 1) / blind_stride;
-      hipLaunchKernelGGL(cc_hook_blind, dim3(grid_for(blind, 1, cap)), dim3(256), 0, stream, es,
-                         ed, z.m, n, r.D, blind_stride, blind, b.ctl);
-      mark(r, "hook_blind");
+      hook_blind(std::max<int64_t>(1, std::min(z.m / z.n / 2, spread)), nullptr);
       flatten();
       const int64_t stride = std::max<int64_t>(2, std::min(2 * (z.m / z.n), 2 * spread));
       const int64_t swapped = nchunks / stride;
@@ -983,10 +1133,15 @@ int cc_enqueue(CcRun& r) {
       }
       hipLaunchKernelGGL(cc_hook_rest, dim3(grid_for(nchunks - swapped, 1, cap)), dim3(256), 0,
                          stream, es, ed, z.m, n, r.D, (const uint8_t*)b.cls, stride,
-                         nchunks - swapped, b.ctl);
+                         nchunks - swapped, swapped, b.left, b.ctl);
       mark(r, "hook_rest");
     }
     flatten();
+    const int gl = grid_for(nchunks, 1, 4 * cus);
+    hipLaunchKernelGGL(cc_join_left, dim3(gl), dim3(256), 0, stream, es, ed, z.m, n, r.D, nchunks,
+                       (const int32_t*)b.left, b.ctl);
+    mark(r, "hook_left");
+    flatten(&b.ctl->redo);
   }
   if (r.batched && z.n > 0) {
     hipLaunchKernelGGL(cc_localise, dim3(gv), dim3(256), 0, stream, r.D, n, r.d_voff, (int)z.G);

@@ -75,3 +75,56 @@ def test_few_vertices_each(pj, beside):
                                           h_edge_off=eoff)
     assert np.array_equal(got.cpu().numpy(),
                           oracle.connected_components_batched(src, dst, voff, eoff))
+
+
+# graphs whose hooks chain vertices one after another, and pairs that meet the
+# chains: ids in order, in order through two halves of the ids, and in order a
+# hundredth of the ids apart
+def ordered_graph(shape, n, seed):
+    rng = np.random.default_rng(seed)
+    i = np.arange(n)
+    h = n // 2
+    k = np.arange(h)
+    if shape == "ring":
+        return i, (i + 1) % n
+    if shape == "ring_shuffled":
+        p = rng.permutation(n)
+        return p, (p + 1) % n
+    if shape == "ring_x4":
+        return np.tile(i, 4), (np.tile(i, 4) + 1) % n
+    if shape == "rings_of_100":
+        return i, np.where(i % 100 == 99, i - 99, np.minimum(i + 1, n - 1))
+    if shape == "two_paths":
+        return (np.concatenate([k[:-1], h + k[:-1], [0, h - 1]]),
+                np.concatenate([k[:-1] + 1, h + k[:-1] + 1, [h, 2 * h - 1]]))
+    if shape == "closers":
+        return (np.concatenate([i[:-1], np.zeros(64, np.int64)]),
+                np.concatenate([i[:-1] + 1, n - 1 - np.arange(64)]))
+    if shape == "ladder":               # 0 - h+k - k, k+1
+        return (np.concatenate([k[:-1], k[:-1] + 1, k, np.zeros(h, np.int64)]),
+                np.concatenate([h + k[:-1], h + k[:-1], h + k, h + k]))
+    if shape == "rows_of_2":
+        return np.concatenate([i[:-2], i[::2]]), np.concatenate([i[:-2] + 2, np.minimum(i[::2] + 1, n - 1)])
+    if shape == "grid":
+        return np.concatenate([i[:-1], i[:-300]]), np.concatenate([i[:-1] + 1, i[:-300] + 300])
+    c = rng.integers(0, n, (2, int(0.4 * n)))
+    return np.concatenate([i[:-1], c[0]]), np.concatenate([i[:-1] + 1, c[1]])   # chords
+
+
+@pytest.mark.parametrize("n", [70_000, 300_000, (1 << 21) + 100])
+@pytest.mark.parametrize("ids", ["in_order", "halves", "hundredths"])
+@pytest.mark.parametrize("shape", ["ring", "ring_shuffled", "ring_x4", "rings_of_100", "two_paths",
+                                   "closers", "ladder", "rows_of_2", "grid", "chords"])
+def test_ids_in_order(pj, n, ids, shape):
+    i = np.arange(n)
+    if ids == "halves":
+        to = np.where(i % 2 == 0, i // 2, (n + 1) // 2 + i // 2)
+    elif ids == "hundredths":
+        to = (i % 100) * (n // 100) + i // 100 if n % 100 == 0 else i
+    else:
+        to = i
+    src, dst = ordered_graph(shape, n, n)
+    p = np.random.default_rng(1).permutation(n)
+    random_ids = solve_ms(pj, p[src], p[dst], n)
+    ordered = solve_ms(pj, to[src], to[dst], n)
+    assert ordered < 8 * max(random_ids, 0.1), (ordered, random_ids)
