@@ -73,7 +73,7 @@ struct CcCtl {
 // chain climbs as far as the graph is long, with nobody else on the way (a ring of
 // 4 * 10^6 vertices in id order: 1.03 s, nearly all for the pair that closes it).
 // So a pair is given up after `most` steps, and its chunk of pairs is marked and
-// read again once a shortcut has flattened the chains (that ring: 0.37 ms).
+// read again once a shortcut has flattened the chains (that ring: 0.43 ms).
 //
 // The lanes of a wave that hook the same root send one swap: the pairs of a hub
 // with the largest id all meet at the hub's parent, and swaps on one word run at
@@ -82,17 +82,17 @@ constexpr int kHalveSmall = 3, kHalveLarge = 16;
 constexpr int64_t kHalveSmallBelow = 1 << 20;
 constexpr int kNever = INT32_MAX;
 
-// Steps before the path is halved, before a pair is given up, and before the
-// others of its thread are after that.  With random ids a few pairs of many
-// millions take more than 24 (8 M in paths 720 us with 24, 697 with 32 and 48).
+// Steps before the path is halved and before a pair is given up.  With random ids
+// a few pairs of many millions take more than 24 (8 M in paths 720 us with 24, 697
+// with 32 and 48).
 // Where ids follow the graph thousands may climb at once, and those that halve
 // their paths meet at the same few nodes (a path of 2 * 10^6 vertices and as many
 // between them, a grid of width 300: swaps of 1.6 ms, 41 us without halving).
 struct Climb {
-  int halve, most, after;
+  int halve, most;
 };
-constexpr Climb kClimbSmall{kHalveSmall, 48, 8}, kClimbLarge{kHalveLarge, 48, 8};
-constexpr Climb kClimbOrdered{kNever, 24, 4};
+constexpr Climb kClimbSmall{kHalveSmall, 48}, kClimbLarge{kHalveLarge, 48};
+constexpr Climb kClimbOrdered{kNever, 24};
 
 enum Joined { kSame, kHooked, kLeft };
 
@@ -172,10 +172,15 @@ __global__ void __launch_bounds__(256) cc_init(int32_t* __restrict__ D, int n, C
                                                int32_t* __restrict__ left, int64_t nchunks,
                                                const int32_t* __restrict__ src,
                                                const int32_t* __restrict__ dst, int64_t sampled) {
+  if (sampled > 0 && blockIdx.x == gridDim.x - 1) {  // a workgroup more, of its own
+    sample_order(src, dst, sampled, n, ctl);
+    return;
+  }
   const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-  const int stride = gridDim.x * blockDim.x;
-  if (tid < (int)(offsetof(CcCtl, parents) / 4)) reinterpret_cast<int32_t*>(ctl)[tid] = 0;
-  if (blockIdx.x == 0 && sampled > 0) sample_order(src, dst, sampled, n, ctl);
+  const int stride = (gridDim.x - (sampled > 0)) * blockDim.x;
+  if (tid < (int)(offsetof(CcCtl, parents) / 4) &&
+      !(sampled > 0 && tid == (int)(offsetof(CcCtl, ordered) / 4)))
+    reinterpret_cast<int32_t*>(ctl)[tid] = 0;
   const int n4 = (reinterpret_cast<uintptr_t>(D) & 15) == 0 ? n >> 2 : 0;
   for (int q = tid; q < n4; q += stride)
     reinterpret_cast<int4*>(D)[q] = make_int4(4 * q, 4 * q + 1, 4 * q + 2, 4 * q + 3);
@@ -255,7 +260,7 @@ __global__ void __launch_bounds__(256) cc_hook(const int32_t* __restrict__ src,
     bool any = false;
 #pragma unroll
     for (int t = 0; t < kPer; ++t)
-      any |= join(D, x[t], y[t], climb.halve, any ? climb.after : climb.most) == kLeft;
+      any |= join(D, x[t], y[t], climb.halve, climb.most) == kLeft;
     mark_left(left, c, any, how, ctl);
   }
   report(ctl, bad);
@@ -393,7 +398,7 @@ __device__ __forceinline__ void hook_rest(const int32_t* __restrict__ src,
     const int total = *queued;
     bool any = false;
     for (int q = threadIdx.x; q < total; q += 256)
-      any |= join(D, queue[q].x, queue[q].y, climb.halve, any ? climb.after : climb.most) == kLeft;
+      any |= join(D, queue[q].x, queue[q].y, climb.halve, climb.most) == kLeft;
     mark_left(left, c, any, kForLast, ctl);
     __syncthreads();  // the queue is reused by the next chunk
   }
@@ -1064,8 +1069,8 @@ int cc_enqueue(CcRun& r) {
   }
   const int64_t nchunks = hook_chunks(z.m);
   const bool sparse = 2 * z.m < 3 * z.n, gated = sparse && z.n >= kGatedFrom;
-  hipLaunchKernelGGL(cc_init, dim3(grid_for(z.n / 4, 256, cap)), dim3(256), 0, stream, r.D, n,
-                     b.ctl, b.left, nchunks, es, ed, gated ? z.m : 0);
+  hipLaunchKernelGGL(cc_init, dim3(grid_for(z.n / 4, 256, cap) + gated), dim3(256), 0, stream,
+                     r.D, n, b.ctl, b.left, nchunks, es, ed, gated ? z.m : 0);
   PJ_HIP(hipGetLastError());
   mark(r, "init");
   const auto flatten = [&](const int32_t* only_if = nullptr) {
