@@ -294,7 +294,7 @@ __global__ void __launch_bounds__(256) lr_headfind_batched(const int32_t* succ,
         if (tails) atomicAdd(&ltails[l], tails);
         acc = 0;
         tails = 0;
-        while (off[l + 1] <= g) ++l;
+        l = find_from(off, L, l, g);  // (past thousands of empty ones at a time)
         lbase = off[l];
         lend = off[l + 1];
       }
