@@ -533,6 +533,7 @@ constexpr int kLdsThreads = 1024;
 constexpr int kSubGraphs = 512;
 constexpr int kLdsPairs = 1 << 30;
 constexpr int kLdsPer = 8;         // pairs a lane loads at a time
+constexpr int kLdsPatience = 128;  // steps of a wave before it gives pairs up
 constexpr int kLdsChunk = kWave * kLdsPer;
 
 // Parent of x in `word`, which holds the parents of x & ~1 and x | 1.
@@ -620,6 +621,9 @@ __global__ void __launch_bounds__(kLdsThreads) cc_lds(
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int lane = lane_id();
   __shared__ int first_heavy, past;  // first graph that is heavy, that does not fit
+  __shared__ int gave_up;            // the last attempt at a part that gave pairs up
+  int attempt = 0;
+  if (tid == 0) gave_up = 0;
   // with a second set of `bins` workgroups, the first takes the heavy graphs
   const bool take_heavy = (int)gridDim.x > bins && (int)blockIdx.x < bins;
   const int block = (int)blockIdx.x % bins;
@@ -668,17 +672,26 @@ __global__ void __launch_bounds__(kLdsThreads) cc_lds(
     // by then, each part on a flat forest: joins on trees that are still being
     // built climb long ways.  A wave gathers the pairs that are not in one
     // tree yet in a queue of its own, and its lanes take the next one as soon
-    // as they are done with theirs.
+    // as they are done with theirs.  Where joins chain one vertex to the next,
+    // pairs climb as far as the graph is long: a wave that goes on for long gives
+    // up the pairs it has, and the part is done again on a flat forest, with twice
+    // the patience (a ring of 30000 vertices whose ids alternate between two
+    // halves: 1190 us).
     const int nchunks = (int)(((int64_t)ne + kLdsChunk - 1) / kLdsChunk);
     const int ratio = ne / max(nv, 1);
     const int s1 = max(1, ratio / 2);
     const int s2 = max(2, 2 * ratio);
     uint32_t* const q = queue[wave];
-    for (int part = 0; part < 3; ++part) {
+    int patience = kLdsPatience;
+    for (int part = 0; part < 3;) {
       // the part's chunks: 0, s1, ...; s2 - 1, 2 * s2 - 1, ...; all but those
       const int count = part == 0 ? (nchunks + s1 - 1) / s1
                                   : part == 1 ? nchunks / s2 : nchunks - nchunks / s2;
-      if (count == 0) continue;  // uniform over the workgroup
+      if (count == 0) {  // uniform over the workgroup
+        ++part;
+        continue;
+      }
+      ++attempt;
       const auto chunk_of = [&](int i) {
         return part == 0 ? i * s1 : part == 1 ? (i + 1) * s2 - 1 : i + i / (s2 - 1);
       };
@@ -699,7 +712,13 @@ __global__ void __launch_bounds__(kLdsThreads) cc_lds(
       LdsPair pair;
       int queued = 0;  // uniform over the wave
       const auto drain = [&](bool all) {
-        for (;;) {
+        for (int steps = 0;; ++steps) {
+          if (steps >= patience) {
+            if (__ballot(pair.x != pair.y) && lane == 0)
+              __hip_atomic_store(&gave_up, attempt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            pair = LdsPair{};
+            steps = 0;
+          }
           if (queued > 0) {
             const bool idle = pair.x == pair.y;
             const uint64_t mk = __ballot(idle);
@@ -777,7 +796,10 @@ __global__ void __launch_bounds__(kLdsThreads) cc_lds(
       }
       drain(true);
       __syncthreads();
+      const bool again = gave_up == attempt;
       deep = max(deep, lds_flatten(par, nv));
+      if (again) patience *= 2;
+      else ++part;
     }
     int g = 0;
     for (int c0 = wave * kLdsChunk; c0 < nv; c0 += kWaves * kLdsChunk) {

@@ -111,7 +111,7 @@ def ordered_graph(shape, n, seed):
     return np.concatenate([i[:-1], c[0]]), np.concatenate([i[:-1] + 1, c[1]])   # chords
 
 
-@pytest.mark.parametrize("n", [70_000, 300_000, (1 << 21) + 100])
+@pytest.mark.parametrize("n", [1000, 30_000, 65_500, 70_000, 300_000, (1 << 21) + 100])
 @pytest.mark.parametrize("ids", ["in_order", "halves", "hundredths"])
 @pytest.mark.parametrize("shape", ["ring", "ring_shuffled", "ring_x4", "rings_of_100", "two_paths",
                                    "closers", "ladder", "rows_of_2", "grid", "chords"])
