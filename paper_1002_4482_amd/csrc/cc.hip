@@ -19,7 +19,6 @@
 // of one workgroup each (cc_lds).
 #include <algorithm>
 #include <array>
-#include <cmath>
 #include <cstddef>
 #include <map>
 #include <mutex>
@@ -1229,6 +1228,10 @@ int cc_impl(const int32_t* src, const int32_t* dst, const CcSizes& z, const int6
   const bool want_status = o.validate && !o.d_status;
   if (z.n == 0 && !o.d_status) return PJ_OK;
 
+  // a workspace too small for the device-wide solve is refused on either path
+  if (o.workspace &&
+      o.workspace_bytes < cc_carve(z.n, z.m, z.G, r.batched, want_status, nullptr, &r.b))
+    return PJ_EINVAL;
   Workspace ws;
   if (!r.lds || want_status || st) {  // the LDS solve itself needs no memory
     PJ_TRY(workspace_acquire(ws, cc_need(r, want_status, nullptr, &r.b), &o, stream));
@@ -1395,24 +1398,12 @@ void cc_graph_cache_clear() {
   g_ccg.clear();
 }
 
-// Bytes reported to callers and charged to a server's budget.  The solve
-// needs less; the figure is the one that budgets were made for (two stamps and
-// a bit per vertex, two lists of pairs, the slices of their chunks, the flags
-// of every round up to a bound, and a batch's pairs), so that a budget admits
-// the requests it always did.
+// Bytes reported to callers and charged to a server's budget: what the device-wide
+// solve of a batch of these sizes takes, the most of any path.
 size_t cc_workspace(int64_t n, int64_t m, int64_t G, const pj_opts* user) {
-  pj_opts o = resolved_opts(user);
-  const bool status = o.validate && !o.d_status;
+  const pj_opts o = resolved_opts(user);
   CcBuffers b;
-  const double lg = n > 1 ? std::floor(std::log((double)n) / std::log(1.5)) : 0.0;
-  const size_t rounds = 4 * ((size_t)lg + 2) + 2;
-  const size_t nn = (size_t)std::max<int64_t>(n, 1), mm = (size_t)std::max<int64_t>(m, 1);
-  size_t bytes = ws_bytes(1, 8) + 2 * ws_bytes(nn, 4) + 2 * ws_bytes(rounds, 4) +
-                 ws_bytes(rounds, 8) + ws_bytes(8 * rounds, 4) + ws_bytes((nn + 63) / 64, 8) +
-                 2 * ws_bytes(mm, 8) + ws_bytes((mm + 2047) / 2048 * 9, 4) + 2 * ws_bytes(mm, 4) +
-                 ws_bytes((size_t)std::max<int64_t>(G, 1), 4);
-  if (status) bytes += ws_bytes((size_t)std::max<int64_t>(G, 1), 4);
-  return std::max(bytes, cc_carve(n, m, G, true, status, nullptr, &b));
+  return cc_carve(n, m, G, true, o.validate && !o.d_status, nullptr, &b);
 }
 
 }  // namespace pj
