@@ -131,8 +131,10 @@ typedef struct pj_stats {
     int32_t algo;                 /* algorithm actually run */
     int32_t levels;               /* ruling set: walk levels (recursion depth) */
     int32_t base_kind;            /* ruling set: 1 LDS workgroup, 2 device-wide pointer jumping */
-    int32_t rounds;               /* components: the hooks, and the parent steps of the deepest
-                                     vertex a shortcut pass found (1 + steps);
+    int32_t rounds;               /* components: 1 + the most parent steps that a vertex took
+                                     in a shortcut pass, counted from 2 up to 24 (1: none
+                                     took more than one); where one workgroup's LDS holds
+                                     the graphs, 1 + the most jumps of a shortcut there;
                                      Wyllie: pointer-jumping rounds, ceil(log2) of the
                                      longest list */
     int64_t level_nodes[PJ_MAX_LEVELS + 1]; /* nodes at each level (level 0 = input) */
@@ -301,8 +303,8 @@ int pj_connected_components_ex(const int32_t *src, const int32_t *dst, int64_t n
 
 /*
  * Batched components: G independent graphs, each solved as in the problem
- * statement of Section 4 (the batch is one disjoint union of the graphs,
- * solved by one Shiloach-Vishkin run).  vtx_off and edge_off are DEVICE
+ * statement of Section 4 (small graphs in one workgroup's LDS each, or the
+ * batch as one disjoint union of the graphs).  vtx_off and edge_off are DEVICE
  * int64[G+1] tables; graph g owns vertices [vtx_off[g], vtx_off[g+1]) and
  * pairs [edge_off[g], edge_off[g+1]), with LOCAL vertex ids.  label receives
  * local labels (smallest local id of each component).
@@ -326,8 +328,10 @@ int pj_connected_components_batched_ex(const int32_t *src, const int32_t *dst,
  * list-ranking graphs.
  */
 
-/* Bytes of workspace a components call needs (G = 1: enough for both the plain
- * call and a batched call holding one graph). */
+/* Bytes of workspace that suffice for a components call (G = 1: for both the
+ * plain call and a batched call holding one graph).  Less is accepted down to
+ * what the call's device-wide solve takes, which the plain call and a call
+ * whose graphs go to LDS stay under. */
 size_t pj_cc_workspace_bytes(int64_t n, int64_t m, int64_t G, const pj_opts *opts);
 
 /* ----------------------------------------------------------------- serving */

@@ -522,12 +522,11 @@ __global__ void __launch_bounds__(kThreads) cc_flatten(int32_t* D, int n, const 
 // device-wide path, 340 us here; 1000 vertices and 1500 pairs 65 and 14 us.
 //
 // A workgroup takes the graphs of its block of `bin` keys (graph_key: vertices,
-// pairs and graphs), up to kSubGraphs graphs of kCap vertices in all at a time, so
-// thousands of tiny graphs share a workgroup and a graph of any size up to kCap, or
+// pairs and graphs), up to kSubGraphs graphs of kLdsVertices vertices in all at a time, so
+// thousands of tiny graphs share a workgroup and a graph of any size up to that, or
 // with many pairs, has one of its own (blocks of vertices alone: 20 graphs of 100
 // vertices and 10^6 pairs in one workgroup, 7.9 ms).
 constexpr int kLdsVertices = 65536;
-constexpr int kLdsSmall = 16384;   // the smaller instance: two workgroups per CU
 constexpr int kLdsThreads = 1024;
 constexpr int kSubGraphs = 512;
 constexpr int kLdsPairs = 1 << 30;
@@ -605,13 +604,12 @@ __device__ __forceinline__ int lds_flatten(uint32_t* par, int nv) {
 
 // voff == nullptr: one graph of n vertices and m pairs.  The host has checked
 // the tables it planned with; what the device's hold is checked here against
-// n, m and kCap, and graphs that do not fit get PJ_EINVAL.
-template <int kCap>
+// n, m and kLdsVertices, and graphs that do not fit get PJ_EINVAL.
 __global__ void __launch_bounds__(kLdsThreads) cc_lds(
     const int32_t* __restrict__ src, const int32_t* __restrict__ dst, int64_t m, int n,
     const int64_t* __restrict__ voff, const int64_t* __restrict__ eoff, int G, int64_t bin,
     int bins, int heavy, int32_t* __restrict__ label, int32_t* __restrict__ status, int32_t* deepest) {
-  __shared__ uint32_t par[kCap / 2];
+  __shared__ uint32_t par[kLdsVertices / 2];
   __shared__ int sv[kSubGraphs + 1], se[kSubGraphs + 1];
   __shared__ uint32_t badbits[kSubGraphs / 32];
   constexpr int kWaves = kLdsThreads / kWave;
@@ -645,7 +643,7 @@ __global__ void __launch_bounds__(kLdsThreads) cc_lds(
     if (tid == 0) first_heavy = past = k;
     __syncthreads();
     if (tid < k) {
-      if (!(entry_fits(sv[tid], sv[tid + 1], kCap) && entry_fits(se[tid], se[tid + 1], kLdsPairs)))
+      if (!(entry_fits(sv[tid], sv[tid + 1], kLdsVertices) && entry_fits(se[tid], se[tid + 1], kLdsPairs)))
         atomicMin(&past, tid);
       if ((int)gridDim.x > bins && se[tid + 1] - se[tid] > heavy) atomicMin(&first_heavy, tid);
     }
@@ -663,7 +661,7 @@ __global__ void __launch_bounds__(kLdsThreads) cc_lds(
       ga += k;
       continue;
     }
-    for (int i = tid; i < (min(nv, kCap) + 1) / 2; i += kLdsThreads)
+    for (int i = tid; i < (min(nv, kLdsVertices) + 1) / 2; i += kLdsThreads)
       par[i] = (uint32_t)(2 * i) | (uint32_t)(2 * i + 1) << 16;
     __syncthreads();
     // As for a large graph: blind hooks of about two pairs a vertex, joins of
@@ -1067,9 +1065,8 @@ int cc_enqueue(CcRun& r) {
                          0, nullptr, nullptr, 0);
       deepest = &b.ctl->steps;
     }
-    const auto k = z.max_n <= kLdsSmall ? cc_lds<kLdsSmall> : cc_lds<kLdsVertices>;
     const int bins = cc_lds_bins(r);
-    hipLaunchKernelGGL(k, dim3(bins * cc_lds_sets(r)), dim3(kLdsThreads), 0, stream, r.src, r.dst,
+    hipLaunchKernelGGL(cc_lds, dim3(bins * cc_lds_sets(r)), dim3(kLdsThreads), 0, stream, r.src, r.dst,
                        z.m, n, r.d_voff, r.d_eoff, (int)z.G, r.bin, bins, cc_lds_heavy(r), r.D,
                        r.status, deepest);
     PJ_HIP(hipGetLastError());
@@ -1263,7 +1260,7 @@ int cc_impl(const int32_t* src, const int32_t* dst, const CcSizes& z, const int6
 // A components solve captured once into a hipGraph and replayed.  The cache
 // owns the workspace; the key holds every address and size the capture used,
 // and the choice of path, which follows from the largest graph.
-using CcGraphKey = std::array<int64_t, 14>;
+using CcGraphKey = std::array<int64_t, 13>;
 struct CcGraphEntry {
   hipGraphExec_t exec = nullptr;
   void* ws = nullptr;
@@ -1302,7 +1299,6 @@ int cc_graph(const int32_t* src, const int32_t* dst, const CcSizes& z, const int
                        z.m,
                        want_status ? 1 : 0,
                        r.lds ? 1 : 0,
-                       r.lds && z.max_n <= kLdsSmall ? 1 : 0,
                        r.lds ? cc_lds_sets(r) : 0};
   std::lock_guard<std::mutex> lk(g_ccg_mu);
   auto it = g_ccg.find(key);

@@ -624,7 +624,7 @@ __global__ void __launch_bounds__(1024) lr_walk(WalkArgs a) {
 //
 // A batch whose lists each fit an XCD's L2 gains more.  Workgroup ids are dealt
 // round-robin over the XCDs, and each XCD takes chunks of consecutive splitter
-// blocks (and the heads of the lists that start in them) from its own eighth
+// blocks (and heads of lists, see lr_rec_chunks) from its own eighth
 // of the nodes in order, so the lists its lanes walk at one time are a few
 // neighbours, which stay in its L2.  Nothing but the hit rate depends on the
 // mapping.  256 lists of 2^18 nodes, following successors: 69 G nodes/s over
@@ -1366,10 +1366,11 @@ __global__ void __launch_bounds__(kBaseThreads) lr_base_lds(const int2* __restri
 // counter, and a wave skips the rows it has no part in (12500 nodes: 35 -> 21.7
 // us, 8194: 29 -> 20).  A second workgroup of the same XCD reads the level into
 // their L2 meanwhile, as one CU alone reads 9 bytes a clock from beyond it (2 us
-// of 12500 nodes).  Blocks of 8 take more steps a walk and half the jumps:
-// lists of 100003 and 2^20 and 2^22 nodes, whose bases have 12502, 8194 and 8194
-// nodes, take 59.3, 131.1 and 263.7 us with them, 61.9, 131.2 and 262.4 with
-// blocks of 4.
+// of 12500 nodes).  Blocks of 8 take more steps a walk and half the jumps (calls,
+// blocks of 4 and of 8: one list of 5000 nodes 14.8 and 15.2 us, 7000 15.3 and
+// 16.1, 9000 17.7 and 16.3, 10240 18.6 both, 12000 20.9 and 18.9, 16384 24.7 and
+// 22.2; as bases, lists of 100003, 120000, 2^20 and 2^22 nodes 62.3 and 61.8, 64.2
+// and 61.0, 125.6 and 126.1, 263.3 and 262.2).
 //
 // word[x]: {weight, next (| kStop)} at first; {offset, splitter | kSeen} once a walk has
 // passed x; of a splitter {weight of its sublist, next splitter} after its walk

@@ -15,7 +15,7 @@ constexpr int kWave = 64;
 
 // ------------------------------------------------------------------ errors
 // Device-side error bits, OR-ed into a control word and turned into
-// PJ_EBADLIST / PJ_ENOCONV at the end of a call.
+// a status at the end of a call.
 enum : int32_t {
   kErrRange = 1,     // a successor outside its instance
   kErrTails = 2,     // an instance without exactly one tail
@@ -24,7 +24,6 @@ enum : int32_t {
   kErrBase = 16,     // the splitter list is not a list (branch or cycle)
   kErrTotal = 32,    // sublists do not cover every node exactly once
   kErrCheck = 64,    // the full output check failed
-  kErrNoConv = 128,  // components: round guard reached
   kErrSplitter = 256,  // a caller-chosen splitter out of range or repeated
 };
 
