@@ -7,11 +7,10 @@
  * solved either by Wyllie's pointer jumping (Section 3.1) or by the parallel
  * random-splitter (sparse ruling set) method of Reid-Miller (Section 3.2,
  * Algorithm "Parallel Random Splitter"), whose splitter list is itself ranked
- * recursively.  Connected components follow Section 4: a hook-and-shortcut
- * algorithm of the Shiloach-Vishkin family with the step split of the
- * paper's SV-GPU (shortcut and mark separated by a barrier, conditional and
- * stagnant-star hooking, shortcut, change flag), with labels canonicalised to
- * the smallest vertex id of each component.
+ * recursively.  Connected components follow Section 4: hook and shortcut over a
+ * parent forest, the family of the paper's SV-GPU, with hooks from larger to
+ * smaller ids by compare and swap instead of its rounds of stores, so that the
+ * labels are the smallest vertex id of each component.
  *
  * Conventions shared by every entry point
  * ---------------------------------------
@@ -22,7 +21,7 @@
  *    argument errors detected on the host before anything is enqueued, and HIP
  *    errors; 0 means enqueued.
  *  - Errors in the DATA (a successor array that is not one list per instance,
- *    a solve that does not converge) are found on the device.  They are
+ *    a pair with an id out of range) are found on the device.  They are
  *    written to opts->d_status when given (one int32 per instance); with
  *    opts->validate != 0 and no d_status, the call waits for the stream and
  *    returns the status itself.  Whatever the input, every kernel stays in
@@ -102,7 +101,8 @@ typedef struct pj_opts {
                                  convergence check */
     int32_t use_graph;        /* batched list ranking and components: replay a captured
                                  hipGraph (see pj_graph_cache_clear) */
-    int32_t *d_status;        /* optional device int32[instances]: PJ_OK / PJ_EBADLIST / PJ_ENOCONV */
+    int32_t *d_status;        /* optional device int32[instances]: PJ_OK, or PJ_EBADLIST for a
+                                 list, PJ_EINVAL for a graph */
     void *workspace;          /* optional caller-owned device workspace */
     size_t workspace_bytes;
     const int64_t *h_offsets;      /* batched: host copy of the (vertex) offset table */
@@ -192,9 +192,9 @@ int pj_list_rank_batched_ex(const int32_t *succ, const int64_t *offsets, int64_t
 /* Bytes of workspace a call with these sizes needs (L = 1: enough for both the
  * plain call and a batched call holding one list).  One list of 11 * 2^20 to
  * 2^26 nodes uses 14 to 19 bytes per node beyond that, and a batch of 2^20 nodes
- * or more whose lists have at most 2^21 about as much (at most 32 and 256 MiB; a
- * batch that would take more uses none), and they run faster, where the library
- * allocates or opts->workspace is that much larger. */
+ * or more whose lists have at most 2^21 about as much (at most 32 bytes per node
+ * and 256 MiB; a batch that would take more uses none), and they run faster, where
+ * the library allocates or opts->workspace is that much larger. */
 size_t pj_list_rank_workspace_bytes(int64_t total_nodes, int64_t L, const pj_opts *opts);
 
 /*

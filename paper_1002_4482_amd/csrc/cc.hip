@@ -12,7 +12,11 @@
 //             the pairs settles connectivity, with no rounds and no host check.
 //   shortcut  D[v] <- the root of v, one writer per word.
 // SV's stars, stamps and stagnant hooks exist because its hooks are blind
-// concurrent stores; a compare and swap needs none of them.
+// concurrent stores; a compare and swap needs none of them.  The hook is the
+// published lock-free form of union-find by ids (Rem's algorithm; with compare and
+// swap, Jayanti and Tarjan; on GPUs, ECL-CC by Jaiganesh and Burtscher), and joining
+// a sample of the pairs first, so that most of the rest need only be looked at, is
+// the idea of Afforest (Sutton, Ben-Nun and Barak).
 //
 // Large graphs run hook and shortcut kernels over the whole device (cc_hook,
 // cc_flatten); graphs of at most kLdsVertices vertices are solved in the LDS
@@ -76,17 +80,17 @@ struct CcCtl {
 //
 // The lanes of a wave that hook the same root send one swap: the pairs of a hub
 // with the largest id all meet at the hub's parent, and swaps on one word run at
-// 88 M/s (a star of 4 * 10^6 vertices 3.26 ms, with one swap a wave 0.18).
+// 88 M/s (a star of 4 * 10^6 vertices 3.26 ms, with one swap a wave 0.21).
 constexpr int kHalveSmall = 3, kHalveLarge = 16;
 constexpr int64_t kHalveSmallBelow = 1 << 20;
 constexpr int kNever = INT32_MAX;
 
 // Steps before the path is halved and before a pair is given up.  With random ids
 // a few pairs of many millions take more than 24 (8 M in paths 720 us with 24, 697
-// with 32 and 48).
-// Where ids follow the graph thousands may climb at once, and those that halve
-// their paths meet at the same few nodes (a path of 2 * 10^6 vertices and as many
-// between them, a grid of width 300: swaps of 1.6 ms, 41 us without halving).
+// with 32 and 48).  Where ids follow the graph thousands may climb at once, and
+// those that halve their paths meet at the same few nodes (a grid of 10^6 vertices,
+// 300 wide, numbered row by row with ids from two halves in turn: swaps of 1.6 ms;
+// without halving the whole solve takes 0.12).
 struct Climb {
   int halve, most;
 };
@@ -357,8 +361,9 @@ __global__ void __launch_bounds__(256) cc_class_fill(const int32_t* __restrict__
 }
 
 // Hooks the pairs of all the other chunks, and of the `swapped` ones where pairs
-// were given up, most of which lie in one tree by now: two reads (of classes, or of D) settle those, the rest is gathered in
-// LDS first so that the lanes of a wave climb together.
+// were given up, most of which lie in one tree by now: two reads (of classes, or
+// of D) settle those, the rest is gathered in LDS first so that the lanes of a wave
+// climb together.
 template <bool kClassed>
 __device__ __forceinline__ void hook_rest(const int32_t* __restrict__ src,
                                           const int32_t* __restrict__ dst, int64_t m, int n,
@@ -519,13 +524,13 @@ __global__ void __launch_bounds__(kThreads) cc_flatten(int32_t* D, int n, const 
 // Bound by vector instructions and LDS accesses of the 16 waves that fit, and
 // by the latency of the pair loads (two rows of chunks in flight, about 36 GB/s
 // per CU).  1024 graphs of 2^8..2^16 vertices, 5.9 * 10^7 pairs: 2109 us on the
-// device-wide path, 340 us here; 1000 vertices and 1500 pairs 65 and 14 us.
+// device-wide path, 345 us here; 1000 vertices and 1500 pairs 65 and 14 us.
 //
 // A workgroup takes the graphs of its block of `bin` keys (graph_key: vertices,
 // pairs and graphs), up to kSubGraphs graphs of kLdsVertices vertices in all at a time, so
 // thousands of tiny graphs share a workgroup and a graph of any size up to that, or
-// with many pairs, has one of its own (blocks of vertices alone: 20 graphs of 100
-// vertices and 10^6 pairs in one workgroup, 7.9 ms).
+// with many pairs, has one of its own (with blocks of vertices alone one workgroup
+// took 20 graphs of 100 vertices and 10^6 pairs, 7.9 ms; 0.15 now).
 constexpr int kLdsVertices = 65536;
 constexpr int kLdsThreads = 1024;
 constexpr int kSubGraphs = 512;
@@ -1008,8 +1013,7 @@ struct CcRun {
 // with a CU's share of all, and of the device-wide kernels' launches and
 // dependent passes (few for forests, long climbs in sparse graphs with cycles,
 // three parts otherwise), which then join 30000 pairs a microsecond, 75000 in
-// smaller graphs.  Measured,
-// LDS and device-wide, vertices / pairs: uniform 10000 / 20000 29 and 63, 20000 /
+// smaller graphs.  Measured, LDS and device-wide, vertices / pairs: uniform 10000 / 20000 29 and 63, 20000 /
 // 40000 48 and 71, 40000 / 80000 83 and 87, 60000 / 120000 119 and 85, 60000 /
 // 80000 99 and 113, 60000 / 40000 70 and 49; planted 10000 / 80000 46 and 57,
 // 20000 / 100000 65 and 57; paths of 30000 48 and 47, of 60000 87 and 51; 1024
