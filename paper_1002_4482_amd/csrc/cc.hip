@@ -1013,11 +1013,12 @@ struct CcRun {
 // with a CU's share of all, and of the device-wide kernels' launches and
 // dependent passes (few for forests, long climbs in sparse graphs with cycles,
 // three parts otherwise), which then join 30000 pairs a microsecond, 75000 in
-// smaller graphs.  Measured, LDS and device-wide, vertices / pairs: uniform 10000 / 20000 29 and 63, 20000 /
-// 40000 48 and 71, 40000 / 80000 83 and 87, 60000 / 120000 119 and 85, 60000 /
-// 80000 99 and 113, 60000 / 40000 70 and 49; planted 10000 / 80000 46 and 57,
-// 20000 / 100000 65 and 57; paths of 30000 48 and 47, of 60000 87 and 51; 1024
-// graphs of 2^8..2^16 vertices, 5.9 * 10^7 pairs, 341 us and 2.07 ms.
+// smaller graphs.  Measured, LDS and device-wide, vertices / pairs: uniform 10000 /
+// 20000 29 and 69, 20000 / 40000 48 and 80, 40000 / 80000 83 and 92, 60000 / 120000
+// 122 and 85, 60000 / 80000 100 and 111, 60000 / 40000 70 and 60, 20000 / 100000 72
+// and 80, 1000 / 300000 201 and 40 (1000 / 100000, still in LDS, 73 and 41); paths
+// of 36000 58 and 60 (in order 55 and 48), of 60000 88 and 62; 1024 graphs of
+// 2^8..2^16 vertices, 5.9 * 10^7 pairs, 344 us and 2.07 ms.
 void cc_plan(CcRun& r) {
   const CcSizes& z = r.z;
   const int cus = device_info().cus;
