@@ -527,9 +527,9 @@ __global__ void __launch_bounds__(kThreads) cc_flatten(int32_t* D, int n, const 
 // device-wide path, 345 us here; 1000 vertices and 1500 pairs 65 and 14 us.
 //
 // A workgroup takes the graphs of its block of `bin` keys (graph_key: vertices,
-// pairs and graphs), up to kSubGraphs graphs of kLdsVertices vertices in all at a time, so
-// thousands of tiny graphs share a workgroup and a graph of any size up to that, or
-// with many pairs, has one of its own (with blocks of vertices alone one workgroup
+// pairs and graphs), up to kSubGraphs graphs of kLdsVertices vertices in all at a
+// time, so thousands of tiny graphs share a workgroup and a graph of any size up to
+// that, or with many pairs, has one of its own (with blocks of vertices alone one workgroup
 // took 20 graphs of 100 vertices and 10^6 pairs, 7.9 ms; 0.15 now).
 constexpr int kLdsVertices = 65536;
 constexpr int kLdsThreads = 1024;
@@ -678,7 +678,7 @@ __global__ void __launch_bounds__(kLdsThreads) cc_lds(
     // pairs climb as far as the graph is long: a wave that goes on for long gives
     // up the pairs it has, and the part is done again on a flat forest, with twice
     // the patience (a ring of 30000 vertices whose ids alternate between two
-    // halves: 1190 us).
+    // halves: 1190 us, 85 like this).
     const int nchunks = (int)(((int64_t)ne + kLdsChunk - 1) / kLdsChunk);
     const int ratio = ne / max(nv, 1);
     const int s1 = max(1, ratio / 2);

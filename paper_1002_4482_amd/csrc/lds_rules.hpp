@@ -53,10 +53,10 @@ inline int64_t largest_instance(const int64_t* off, int64_t count) {
   return most;
 }
 
-// Of its instances a workgroup takes the ones that fit LDS together, and again.  The table is the
-// device's: it may hold anything, so only a run of entries that each fit after the
-// one before may be indexed with.  An entry relative to the group's first: what
-// no table of this size can hold does not fit.
+// Of its instances a workgroup takes the ones that fit LDS together, and again.
+// The table is the device's: it may hold anything, so only a run of entries that
+// each fit after the one before may be indexed with.  An entry relative to the
+// group's first: what no table of this size can hold does not fit.
 PJ_RULE int table_entry(int64_t d) { return d < 0 || d > INT32_MAX ? INT32_MAX : (int)d; }
 PJ_RULE bool entry_fits(int before, int entry, int cap) { return entry >= before && entry <= cap; }
 

@@ -73,8 +73,8 @@ bool capturing(hipStream_t stream) {
 // Small workspaces are kept between calls: allocating and freeing one from the
 // stream-ordered pool takes the host 25 us, and a call on 17000 to 70000 nodes
 // keeps the device busy for as long (a local list of 17000 or 32000 nodes: 47 us a
-// call, 30 us with the block kept).  Larger ones belong to calls that the device bounds, and
-// go back to the pool.
+// call, 30 us with the block kept).  Larger ones belong to calls that the device
+// bounds, and go back to the pool.
 //
 // A call takes a block out of the list, so that no other call has it, and puts
 // it back with an event recorded behind its last kernel; the next one has its
